@@ -66,7 +66,7 @@ __global__ __launch_bounds__(256) void cos_partial_kernel(
     const int c0 = (int)(((long long)nch * ks) / KS), c1 = (int)(((long long)nch * (ks + 1)) / KS);
     f32x4_t acc[G::FM][G::FN];
     float sa[G::FM], sb[G::FN];
-    G::template run<true>(row_ptr, c0, c1, acc, sa, sb);
+    G::template run<true>(row_ptr, c0, c1, acc, sa, sb, jt == 0, it == 0);
     const size_t kb = (size_t)ks * B + b;
     float *pb = part + kb * Nt * Nv;
 #pragma unroll

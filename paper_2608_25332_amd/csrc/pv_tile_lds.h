@@ -101,13 +101,16 @@ struct TileGemmLds {
     // must be valid (clamp past-the-end rows in the caller).  With WANT_SS,
     // ssa[fm] / ssb[fn] receive this lane's partial sums of squares of the A
     // rows (waves with wn == 0) and B rows (waves with wm == 0) it reads; see
-    // row_sumsq.  Must be called by every thread of the workgroup.
+    // row_sumsq; want_a / want_b (uniform over the workgroup) say whether this
+    // workgroup's are used at all.  Must be called by every thread of the
+    // workgroup.
     template <bool WANT_SS, typename RowPtr>
     __device__ __forceinline__ static void run(RowPtr row_ptr, int c_begin, int c_end,
                                                f32x4_t (&acc)[FM][FN], float (&ssa)[FM],
-                                               float (&ssb)[FN]) {
+                                               float (&ssb)[FN], bool want_a = true,
+                                               bool want_b = true) {
         __shared__ __attribute__((aligned(16))) char ring[LDS_BYTES];
-        run_in<WANT_SS>(ring, row_ptr, c_begin, c_end, acc, ssa, ssb);
+        run_in<WANT_SS>(ring, row_ptr, c_begin, c_end, acc, ssa, ssb, want_a, want_b);
     }
 
     // The same on a ring the caller provides (LDS_BYTES of LDS, 16-byte
@@ -116,7 +119,8 @@ struct TileGemmLds {
     template <bool WANT_SS, typename RowPtr>
     __device__ __forceinline__ static void run_in(char *ring, RowPtr row_ptr, int c_begin,
                                                   int c_end, f32x4_t (&acc)[FM][FN],
-                                                  float (&ssa)[FM], float (&ssb)[FN]) {
+                                                  float (&ssa)[FM], float (&ssb)[FN],
+                                                  bool want_a = true, bool want_b = true) {
         const int lane = threadIdx.x & 63;
         const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
         const int wm = wave / WN, wn = wave % WN;
@@ -188,11 +192,11 @@ struct TileGemmLds {
 #pragma unroll
                 for (int f = 0; f < FN; ++f) lds_after_wait(bfr[s][f]);
                 if (WANT_SS) {
-                    if (wn == 0) {
+                    if (wn == 0 && want_a) {
 #pragma unroll
                         for (int f = 0; f < FM; ++f) ssa[f] += sumsq16<DT>(af[s][f]);
                     }
-                    if (wm == 0) {
+                    if (wm == 0 && want_b) {
 #pragma unroll
                         for (int f = 0; f < FN; ++f) ssb[f] += sumsq16<DT>(bfr[s][f]);
                     }
