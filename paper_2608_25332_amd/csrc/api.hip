@@ -102,6 +102,7 @@ int pick_slices(long long tiles, int nchunks, int target = 768, bool whole_round
 struct DedupPlan {
     int nch;                       // 128-byte k chunks per row
     bool cos_full;                 // cosine in one full-k pass (small inputs)
+    int cos_tok;                   // cosine in one streaming pass: tokens per workgroup, or 0
     int ks_cos, njt;               // cosine: k slices, token tiles of the row sums
     int Mp;
     bool gram_big;                 // full-k 128x128 tiles (operands streamed into LDS)
@@ -124,7 +125,10 @@ DedupPlan plan_dedup(void *ws, int B, int Nv, int Nt, int d, int esz, int budget
                    ? pick_slices(n_tiles(Nv, Nt, B, pv::kWideTile), P.nch, 512, true)
                    : pick_slices(n_tiles(Nv, Nt, B, T), P.nch);
     P.cos_full = pv::cos_use_full(B, Nv, Nt, d * esz);
-    P.njt = P.cos_full ? pv::cos_full_row_tiles(Nv) : pv::cos_row_tiles(Nv);
+    P.cos_tok = P.cos_full ? 0 : pv::cos_stream_tokens(esz == 2 ? pv::kBF16 : pv::kF32, B, Nv, Nt, d * esz, P.ks_cos);
+    P.njt = P.cos_full ? pv::cos_full_row_tiles(Nv)
+            : P.cos_tok ? (Nv + P.cos_tok - 1) / P.cos_tok
+                        : pv::cos_row_tiles(Nv);
     P.Mp = Nv - budget;
     const int Mp1 = P.Mp > 0 ? P.Mp : 1;
     P.gram_big = (long long)((Mp1 + pv::kGramTileM - 1) / pv::kGramTileM) *
@@ -161,7 +165,7 @@ DedupPlan plan_dedup(void *ws, int B, int Nv, int Nt, int d, int esz, int budget
     }
     P.ntn = P.gram_big ? (budget + pv::kGramTileN - 1) / pv::kGramTileN : 1;
     Carve c(ws);
-    if (P.cos_full) {
+    if (P.cos_full || P.cos_tok) {
         P.cpart = P.ssv = P.ssa = nullptr;
     } else {
         P.cpart = c.take<float>((size_t)P.ks_cos * B * Nt * Nv);
@@ -237,6 +241,12 @@ bool launch_front(Trace &tr, const DedupPlan &P, int dt, const void *vis, const 
         if (!tr.launch("cos_full", [&] {
                 return pv::launch_cos_full(dt, vis, anchors, B, Nv, Nt, d, P.M, P.rowsum, P.invn,
                                            st);
+            }))
+            return false;
+    } else if (P.cos_tok) {
+        if (!tr.launch("cos_stream", [&] {
+                return pv::launch_cos_stream(dt, vis, anchors, B, Nv, Nt, d, P.cos_tok, P.M,
+                                             P.rowsum, P.invn, st);
             }))
             return false;
     } else {

@@ -270,6 +270,256 @@ __global__ __launch_bounds__(64 * NW) void cos_full_kernel(
 }
 
 // ----------------------------------------------------------------------------
+// cos_stream: the cosine over many tokens in one full-k pass (bf16), without
+// the fp32 partial products of the split-k form.  1-D grid over (sample,
+// anchor tile, token tile) in XCD order; a workgroup owns A anchors x `rr`
+// tokens (rr <= R, chosen by the host so that the workgroups fill whole rounds
+// of the CUs) and streams both over the whole width, 256 bytes per step.
+//
+// What bounds it: the rows that come from HBM arrive at full rate only in runs
+// of 512 bytes or more (measured on 11520 rows of 8 KB: 2.5 TB/s in runs of
+// 128 bytes, 4.2 in 256, 5.3 in 512), while the anchors sit in L2 and are
+// better taken in smaller pieces.  So the two operands have rings and producer
+// waves of their own (a wave's loads retire in order, so one wave cannot wait
+// for near data past far data): one wave keeps the next 512-byte pieces of
+// every token row in flight, two waves the next 256-byte pieces of every
+// anchor row.  A matrix wave multiplies one 64-byte window of every step for 64
+// anchors x all tokens (with a split over the anchors instead, LDS reads set
+// the pace: every wave reads every token fragment); the four windows' products
+// are added in window order at the end.  One workgroup per CU.
+//
+// Barrier j (j = 0 .. steps) closes the reads of step j - 1 and opens step j;
+// every wave passes steps + 1 of them.  Pieces past the end of a row are read
+// from a block of zeros, so the width need not be a multiple of a step.
+//
+// Writes M[b][Nt][Nv], the row sums over the tile's tokens
+// rowsum[b][token tile][Nt] and, for the first anchor tile, the inverse token
+// norms: what cos_partial and cos_reduce write in two launches.
+// ----------------------------------------------------------------------------
+constexpr int kStrStep = 256;  // bytes of a row per step
+constexpr int kStrTok = 512;   // bytes of a token row per piece in flight
+constexpr int kStrWin = kStrStep / 64;  // windows of a step: matrix waves per 64 anchors
+constexpr int kStrPA = 2;      // anchor producer waves
+constexpr int kStrChain = 8;   // steps added up on their own
+constexpr int str_threads(int A) { return 64 * (kStrWin * (A / 64) + 1 + kStrPA); }
+
+template <int A, int R>
+__global__ __launch_bounds__(str_threads(A)) void cos_stream_kernel(
+    const char *__restrict__ vis, const char *__restrict__ anchors, int Nv, int Nt, int d_bytes,
+    int rr, int njt, int nit, float *__restrict__ M, float *__restrict__ rowsum,
+    float *__restrict__ invn_vis) {
+    constexpr int MW = kStrWin * (A / 64), NT = str_threads(A);  // matrix waves, threads
+    constexpr int FM = 4, FN = (R + 15) / 16;
+    constexpr int NA = A == 64 ? 4 : 3, NTK = A == 64 ? 3 : 2;  // stages: anchors, tokens
+    constexpr int ASTAGE = A * kStrStep, TSTAGE = 16 * FN * kStrTok;
+    constexpr int IA = ASTAGE / 1024 / kStrPA;       // loads per anchor wave per step
+    constexpr int IT = R * kStrTok / 1024;           // loads of the token wave per piece
+    constexpr int SPT = kStrTok / kStrStep;          // steps per token piece
+    constexpr int RS = 16 * FN + 4;                  // row stride of the sums (bank spread)
+    constexpr int RING = NA * ASTAGE + NTK * TSTAGE;
+    static_assert(R % 2 == 0 && IA * (NA - 2) < 64 && IT * (NTK - 2) < 64, "wait counter");
+    static_assert(kStrWin * A * RS * 4 <= RING, "the waves' products reuse the ring");
+    __shared__ __attribute__((aligned(16))) char ring[RING];
+    __shared__ float ssa[kStrWin][A], sst[kStrWin][16 * FN];
+    char *const aring = ring, *const tring = ring + NA * ASTAGE;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int L = xcd_tile(blockIdx.x, gridDim.x);
+    const int jt = L % njt, it = (L / njt) % nit, b = L / (njt * nit);
+    const int i0 = it * A, j0 = jt * rr;
+    const int nstep = (d_bytes + kStrStep - 1) / kStrStep;
+    float *const red = reinterpret_cast<float *>(ring);  // [window][A][RS], after the last step
+
+    // LDS rows of a stage are one piece long; the 16-byte slots are permuted
+    // within 256 bytes by the row, so that the 16 rows of a fragment read fall
+    // in 16 different slots
+    if (wave == MW) {  // the token wave
+        const char *tbase = vis + (size_t)b * Nv * d_bytes;
+        const char *src[IT];
+        int off[IT];  // byte within the piece
+#pragma unroll
+        for (int q = 0; q < IT; ++q) {
+            const int pos = q * 64 + lane;  // 16-byte slot of the stage
+            const int r = pos / (kStrTok / 16), slot = pos % (kStrTok / 16);
+            off[q] = ((slot & ~15) | ((slot ^ r) & 15)) << 4;
+            src[q] = tbase + (size_t)min(j0 + min(r, rr - 1), Nv - 1) * d_bytes + off[q];
+        }
+        const int npiece = (d_bytes + kStrTok - 1) / kStrTok;
+        auto issue = [&](int i) {
+            char *dst = tring + (i % NTK) * TSTAGE;
+            if ((i + 1) * kStrTok <= d_bytes) {
+#pragma unroll
+                for (int q = 0; q < IT; ++q) lds_dma16(src[q] + (size_t)i * kStrTok, dst + q * 1024);
+            } else {
+#pragma unroll
+                for (int q = 0; q < IT; ++q)
+                    lds_dma16(i * kStrTok + off[q] < d_bytes ? src[q] + (size_t)i * kStrTok : zero16(),
+                              dst + q * 1024);
+            }
+        };
+#pragma unroll
+        for (int p = 0; p < NTK - 1; ++p)
+            if (p < npiece) issue(p);
+        for (int j = 0; j < nstep; ++j) {
+            if (j % SPT == 0) {
+                const int s = j / SPT;
+                if (s + NTK - 1 <= npiece) wait_vmcnt<IT * (NTK - 2)>();
+                else wait_vmcnt<0>();
+                bare_barrier();
+                if (s + NTK - 1 < npiece) issue(s + NTK - 1);
+            } else {
+                bare_barrier();
+            }
+        }
+        bare_barrier();
+    } else if (wave > MW) {  // the anchor waves
+        const int w = wave - MW - 1;
+        const char *abase = anchors + (size_t)b * Nt * d_bytes;
+        const char *src[IA];
+        int off[IA];
+#pragma unroll
+        for (int q = 0; q < IA; ++q) {
+            const int pos = (w * IA + q) * 64 + lane;
+            const int r = pos >> 4, slot = pos & 15;
+            off[q] = (slot ^ (r & 15)) << 4;
+            src[q] = abase + (size_t)min(i0 + r, Nt - 1) * d_bytes + off[q];
+        }
+        auto issue = [&](int i) {
+            char *dst = aring + (i % NA) * ASTAGE + w * IA * 1024;
+            if ((i + 1) * kStrStep <= d_bytes) {
+#pragma unroll
+                for (int q = 0; q < IA; ++q) lds_dma16(src[q] + (size_t)i * kStrStep, dst + q * 1024);
+            } else {
+#pragma unroll
+                for (int q = 0; q < IA; ++q)
+                    lds_dma16(i * kStrStep + off[q] < d_bytes ? src[q] + (size_t)i * kStrStep : zero16(),
+                              dst + q * 1024);
+            }
+        };
+#pragma unroll
+        for (int p = 0; p < NA - 1; ++p)
+            if (p < nstep) issue(p);
+        for (int j = 0; j < nstep; ++j) {
+            if (j + NA - 1 <= nstep) wait_vmcnt<IA * (NA - 2)>();
+            else wait_vmcnt<0>();
+            bare_barrier();
+            if (j + NA - 1 < nstep) issue(j + NA - 1);
+        }
+        bare_barrier();
+    } else {
+        const int win = wave % kStrWin, h0 = wave / kStrWin * 64;  // window, first anchor
+        const int rl = lane & 15, piece = win * 4 + (lane >> 4);   // piece of the step
+        // Products and sums of squares of kStrChain steps at a time (acc, s*),
+        // added to the whole (*_all): short chains of roundings, so the one
+        // pass is as exact as the k slices it replaces.
+        f32x4_t acc[FM][FN], acc_all[FM][FN];
+        float sa[FM], st[FN], sa_all[FM], st_all[FN];
+#pragma unroll
+        for (int f = 0; f < FM; ++f) {
+            sa[f] = sa_all[f] = 0.f;
+#pragma unroll
+            for (int g = 0; g < FN; ++g) acc[f][g] = acc_all[f][g] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+        }
+#pragma unroll
+        for (int g = 0; g < FN; ++g) st[g] = st_all[g] = 0.f;
+        for (int j = 0; j < nstep; ++j) {
+            bare_barrier();  // barrier j
+            uint4 a[FM], t[FN];
+            const char *ap = aring + (j % NA) * ASTAGE + (h0 + rl) * kStrStep + ((piece ^ rl) << 4);
+            const char *tp = tring + ((j / SPT) % NTK) * TSTAGE + rl * kStrTok +
+                             (j % SPT) * kStrStep + ((piece ^ rl) << 4);
+#pragma unroll
+            for (int f = 0; f < FM; ++f) a[f] = lds_read16(ap + f * 16 * kStrStep);
+#pragma unroll
+            for (int f = 0; f < FN; ++f) t[f] = lds_read16(tp + f * 16 * kStrTok);
+            lds_wait();
+#pragma unroll
+            for (int f = 0; f < FM; ++f) lds_after_wait(a[f]);
+#pragma unroll
+            for (int f = 0; f < FN; ++f) lds_after_wait(t[f]);
+#pragma unroll
+            for (int f = 0; f < FM; ++f) {
+#pragma unroll
+                for (int g = 0; g < FN; ++g) acc[f][g] = mma16<kBF16>(a[f], t[g], acc[f][g]);
+                sa[f] += sumsq16<kBF16>(a[f]);
+            }
+            if (h0 == 0) {
+#pragma unroll
+                for (int g = 0; g < FN; ++g) st[g] += sumsq16<kBF16>(t[g]);
+            }
+            if (j % kStrChain == kStrChain - 1 || j == nstep - 1) {
+#pragma unroll
+                for (int f = 0; f < FM; ++f) {
+                    sa_all[f] += sa[f];
+                    sa[f] = 0.f;
+#pragma unroll
+                    for (int g = 0; g < FN; ++g) {
+                        acc_all[f][g] += acc[f][g];
+                        acc[f][g] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+                    }
+                }
+#pragma unroll
+                for (int g = 0; g < FN; ++g) {
+                    st_all[g] += st[g];
+                    st[g] = 0.f;
+                }
+            }
+        }
+        bare_barrier();  // the last step's reads are done in every wave
+        // the products and the sums of squares of this window, in the ring's place
+        float *rw = red + ((size_t)win * A + h0) * RS;
+#pragma unroll
+        for (int f = 0; f < FM; ++f) {
+#pragma unroll
+            for (int g = 0; g < FN; ++g)
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    rw[(f * 16 + (lane >> 4) * 4 + e) * RS + g * 16 + rl] = acc_all[f][g][e];
+            float v = sa_all[f];
+            v += __shfl_xor(v, 16, 64);
+            v += __shfl_xor(v, 32, 64);
+            if (lane < 16) ssa[win][h0 + f * 16 + lane] = v;
+        }
+#pragma unroll
+        for (int g = 0; g < FN; ++g) {
+            float v = st_all[g];
+            v += __shfl_xor(v, 16, 64);
+            v += __shfl_xor(v, 32, 64);
+            if (lane < 16 && h0 == 0) sst[win][g * 16 + lane] = v;
+        }
+    }
+    __syncthreads();
+    // 16 lanes per anchor row, FN tokens each; the windows added in order
+    auto inv = [](float q) { return q > 0.f ? 1.0f / sqrtf(q) : 0.f; };
+    const int l16 = tid & 15;
+    float iv[FN];
+#pragma unroll
+    for (int g = 0; g < FN; ++g) {
+        const int c = g * 16 + l16;
+        iv[g] = inv(((sst[0][c] + sst[1][c]) + sst[2][c]) + sst[3][c]);
+        if (it == 0 && tid < 16 && c < rr && j0 + c < Nv) invn_vis[(size_t)b * Nv + j0 + c] = iv[g];
+    }
+    for (int r = tid >> 4; r < A && i0 + r < Nt; r += NT / 16) {  // uniform over 16 lanes
+        const float ia = inv(((ssa[0][r] + ssa[1][r]) + ssa[2][r]) + ssa[3][r]);
+        float rs = 0.f;
+#pragma unroll
+        for (int g = 0; g < FN; ++g) {
+            const int c = g * 16 + l16;
+            float dot = red[(size_t)r * RS + c];
+#pragma unroll
+            for (int w = 1; w < kStrWin; ++w) dot += red[((size_t)w * A + r) * RS + c];
+            if (c < rr && j0 + c < Nv) {
+                const float cs = dot * ia * iv[g];
+                M[((size_t)b * Nt + i0 + r) * Nv + j0 + c] = cs;
+                rs += cs;
+            }
+        }
+        rs = row16_sum(rs);
+        if (l16 == 0) rowsum[((size_t)b * njt + jt) * Nt + i0 + r] = rs;
+    }
+}
+
+// ----------------------------------------------------------------------------
 // center: grid (ceil(Nv / 64), B), 256 threads.  Two phases, each with all of
 // its loads in flight before the first is used, so that a phase costs one
 // memory latency: the row means from the per-tile partial sums (4 threads per
@@ -1005,6 +1255,31 @@ hipError_t launch_cos_full(int dt, const void *vis, const void *anchors, int B, 
         hipLaunchKernelGGL((cos_full_kernel<kF32, kFullW, kFullNS>), grid, dim3(64 * kFullW), 0, st,
                            (const char *)vis, (const char *)anchors, Nv, Nt, d_bytes, nit, njt, M,
                            rowsum, invn);
+    return hipGetLastError();
+}
+
+template <int A>
+static void cos_stream_go(dim3 grid, const void *vis, const void *anchors, int Nv, int Nt,
+                          int d_bytes, int rr, int njt, int nit, float *M, float *rowsum,
+                          float *invn, hipStream_t st) {
+#define PV_STR_CASE(r)                                                                             \
+    hipLaunchKernelGGL((cos_stream_kernel<A, r>), grid, dim3(str_threads(A)), 0, st, (const char *)vis, \
+                       (const char *)anchors, Nv, Nt, d_bytes, rr, njt, nit, M, rowsum, invn)
+    if (rr <= 24) PV_STR_CASE(24);
+    else if (rr <= 32) PV_STR_CASE(32);
+    else if (rr <= 40) PV_STR_CASE(40);
+    else PV_STR_CASE(48);
+#undef PV_STR_CASE
+}
+
+hipError_t launch_cos_stream(int dt, const void *vis, const void *anchors, int B, int Nv, int Nt,
+                             int d, int rr, float *M, float *rowsum, float *invn, hipStream_t st) {
+    if (dt != kBF16 || rr < 1 || rr > kStreamMaxTok) return hipErrorInvalidValue;
+    const int A = cos_stream_anchors(Nt);
+    const int njt = (Nv + rr - 1) / rr, nit = (Nt + A - 1) / A;
+    const dim3 grid(B * nit * njt);
+    if (A == 64) cos_stream_go<64>(grid, vis, anchors, Nv, Nt, d * 2, rr, njt, nit, M, rowsum, invn, st);
+    else cos_stream_go<128>(grid, vis, anchors, Nv, Nt, d * 2, rr, njt, nit, M, rowsum, invn, st);
     return hipGetLastError();
 }
 

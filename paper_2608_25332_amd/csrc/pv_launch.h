@@ -45,6 +45,34 @@ inline bool cos_use_full(int B, int Nv, int Nt, int d_bytes) {
                           ((double)((Nt + 15) / 16) * Nv + (double)((Nv + 15) / 16) * Nt);
     return reread <= 48.0 * (1 << 20);
 }
+// The one-pass cosine over many tokens (cos_stream): anchors per workgroup,
+// and the tokens per workgroup (at most kStreamMaxTok) that fill whole rounds
+// of the 256 CUs, or 0 where the split-k form is the better one.  Both forms
+// are bound by the row bytes a CU can load: the full-k workgroups load
+// (anchors + tokens) rows at about 55 KB/us each, one per CU; the split-k tiles
+// load theirs at about 9 MB/us for the chip, and write and read back the fp32
+// partial products (3.3 and 4.5 MB/us) in a second launch (about 5 us with its
+// fill and drain).  Measured, both launches of the split form against
+// cos_stream: 33 -> 20 us at 16 x 576 tokens x 64 anchors of 8 KB.
+constexpr int kStreamMaxTok = 48;
+inline int cos_stream_anchors(int Nt) { return Nt <= 64 ? 64 : 128; }
+inline int cos_stream_tokens(int dt, int B, int Nv, int Nt, int d_bytes, int ks_split) {
+    if (dt != kBF16) return 0;  // fp32 products are bound by the matrix cores, in any form
+    const int A = cos_stream_anchors(Nt), nit = (Nt + A - 1) / A;
+    const long long most = (long long)B * nit * ((Nv + kStreamMaxTok - 1) / kStreamMaxTok);
+    const long long rounds = (most + 255) / 256;
+    const int per = (int)(256 * rounds / ((long long)B * nit));  // token tiles per sample
+    const int rr = (Nv + per - 1) / per;
+    const int rows = rr <= 24 ? 24 : (rr + 7) / 8 * 8;  // rows staged
+    const double full = rounds * (double)(A + rows) * d_bytes / 55e3 + 2.0;
+    const int T = cos_uses_wide_tiles(Nt, Nv) ? kWideTile : kSplitTile;
+    const double loaded = (double)B * ((Nt + T - 1) / T) * ((Nv + T - 1) / T) * 2 * T * d_bytes;
+    const double partial = 4.0 * ks_split * B * (double)Nt * Nv;
+    const double split = loaded / 9e6 + partial * (1 / 3.3e6 + 1 / 4.5e6) + 5.0;
+    return full < split ? rr : 0;
+}
+hipError_t launch_cos_stream(int dt, const void *vis, const void *anchors, int B, int Nv, int Nt,
+                             int d, int rr, float *M, float *rowsum, float *invn, hipStream_t st);
 hipError_t launch_cos_full(int dt, const void *vis, const void *anchors, int B, int Nv, int Nt,
                            int d, float *M, float *rowsum, float *invn, hipStream_t st);
 hipError_t launch_cos_partial(int dt, const void *vis, const void *anchors, int B, int Nv, int Nt,

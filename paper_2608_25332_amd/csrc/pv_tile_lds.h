@@ -56,6 +56,11 @@ typedef __attribute__((address_space(3))) void lds_void_t;
 __device__ __forceinline__ void lds_dma16(const void *g, char *lds) {
     __builtin_amdgcn_global_load_lds(g, (lds_void_t *)lds, 16, 0, 0);
 }
+// 16 zero bytes in global memory: the source of a direct-to-LDS load for a
+// piece past the end of its row.
+static __device__ const uint4 kZero16 = {0u, 0u, 0u, 0u};
+__device__ __forceinline__ const char *zero16() { return (const char *)&kZero16; }
+
 typedef unsigned lds_u32x4_t __attribute__((ext_vector_type(4)));
 
 __device__ __forceinline__ uint4 lds_read16(const char *p) {
