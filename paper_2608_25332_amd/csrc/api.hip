@@ -560,8 +560,8 @@ int vis_heads_impl(const void *q, const void *k, int B, int H, int Nt, int N, in
 }
 
 struct TextPlan {
-    int ks;
-    float *part, *ssv, *ssa, *G;
+    int ks;  // k slices of the self-similarity; 0: one streaming pass
+    float *part, *G, *stats, *r;
     size_t bytes;
 };
 
@@ -579,13 +579,17 @@ size_t text_total_bytes(int B, int Nt, int d, int esz) {
 TextPlan plan_text(void *ws, int B, int Nt, int d, int esz) {
     TextPlan P;
     const int nch = d * esz / 128;
-    P.ks = pv::cos_uses_wide_tiles(Nt, Nt) ? pick_slices(n_tiles(Nt, Nt, B, pv::kWideTile), nch, 512, true)
-                                            : pick_slices(n_tiles(Nt, Nt, B, pv::kSplitTile), nch);
+    const bool wide = pv::cos_uses_wide_tiles(Nt, Nt);
+    const long long n = (Nt + (wide ? pv::kWideTile : pv::kSplitTile) - 1) /
+                        (wide ? pv::kWideTile : pv::kSplitTile);
+    const long long tiles = n * (n + 1) / 2 * B;  // of the upper triangle
+    P.ks = wide ? pick_slices(tiles, nch, 512, true) : pick_slices(tiles, nch);
+    if (pv::text_uses_stream(esz == 2 ? pv::kBF16 : pv::kF32, B, Nt, d * esz, P.ks)) P.ks = 0;
     Carve c(ws);
-    P.part = c.take<float>((size_t)P.ks * B * Nt * Nt);
-    P.ssv = c.take<float>((size_t)P.ks * B * Nt);
-    P.ssa = c.take<float>((size_t)P.ks * B * Nt);
+    P.part = P.ks ? c.take<float>((size_t)P.ks * B * Nt * Nt) : nullptr;
     P.G = c.take<float>((size_t)B * Nt * Nt);
+    P.stats = c.take<float>((size_t)B * Nt * 2);
+    P.r = c.take<float>((size_t)B * Nt);
     P.bytes = c.off + kAlign;
     return P;
 }
@@ -619,20 +623,31 @@ int text_impl(const void *text, int B, int Nt, int d, int dtype, int32_t *mask, 
             return PV_ERR_HIP;
         text_k = tp;
     }
-    // E E^T: the text rows are both operands of the split-k product
+    // E E^T: the text rows are both operands
     if (!tr.launch("text_gram", [&] {
-            return pv::launch_cos_partial(dt, text_k, text_k, B, Nt, Nt, dp, P.ks, P.part, P.ssv,
-                                          P.ssa, st);
+            return P.ks ? pv::launch_text_gram(dt, text_k, B, Nt, dp, P.ks, P.part, st)
+                        : pv::launch_text_gram_stream(text_k, B, Nt, dp, P.G, st);
         }))
         return PV_ERR_HIP;
-    if (!tr.launch("text_gram_sum", [&] {
-            return pv::launch_text_gram_sum(P.part, B, Nt, P.ks, P.G, st);
+    if (!tr.launch("text_rows", [&] {
+            return pv::launch_text_rows(P.part, B, Nt, P.ks, P.G, P.stats, st);
         }))
         return PV_ERR_HIP;
-    if (!tr.launch("text_rank", [&] {
-            return pv::launch_text_rank(P.G, B, Nt, r, mask, count, st);
-        }))
-        return PV_ERR_HIP;
+    if (pv::text_rank_fused(Nt)) {
+        if (!tr.launch("text_rank", [&] {
+                return pv::launch_text_rank(P.G, P.stats, B, Nt, r, mask, count, st);
+            }))
+            return PV_ERR_HIP;
+    } else {
+        float *rr = r ? r : P.r;
+        if (!tr.launch("text_cols", [&] {
+                return pv::launch_text_cols(P.G, P.stats, B, Nt, rr, st);
+            }) ||
+            !tr.launch("text_mark", [&] {
+                return pv::launch_text_mark(rr, B, Nt, mask, count, st);
+            }))
+            return PV_ERR_HIP;
+    }
     if (!tr.after_all()) return PV_ERR_HIP;
     if (n_kernels) *n_kernels = tr.launched;
     return PV_OK;

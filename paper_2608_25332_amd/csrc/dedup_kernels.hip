@@ -296,6 +296,16 @@ __global__ __launch_bounds__(64 * NW) void cos_full_kernel(
 // rowsum[b][token tile][Nt] and, for the first anchor tile, the inverse token
 // norms: what cos_partial and cos_reduce write in two launches.
 // ----------------------------------------------------------------------------
+// Tile t of the upper triangle (it <= jt) of n x n tiles, row by row.
+__device__ __forceinline__ void upper_tile(int t, int n, int &it, int &jt) {
+    it = 0;
+    while (t >= n - it) {
+        t -= n - it;
+        ++it;
+    }
+    jt = it + t;
+}
+
 constexpr int kStrStep = 256;  // bytes of a row per step
 constexpr int kStrTok = 512;   // bytes of a token row per piece in flight
 constexpr int kStrWin = kStrStep / 64;  // windows of a step: matrix waves per 64 anchors
@@ -303,14 +313,19 @@ constexpr int kStrPA = 2;      // anchor producer waves
 constexpr int kStrChain = 8;   // steps added up on their own
 constexpr int str_threads(int A) { return 64 * (kStrWin * (A / 64) + 1 + kStrPA); }
 
-template <int A, int R>
+// TEXT: the self-similarity of the text rows (vis == anchors, Nv == Nt), raw
+// products, on 64 x 64 tiles (A = R = rr = 64) of the upper triangle only:
+// M[b][i][j] and M[b][j][i] are the same number.  rowsum and invn_vis unused.
+template <int A, int R, bool TEXT = false>
 __global__ __launch_bounds__(str_threads(A)) void cos_stream_kernel(
     const char *__restrict__ vis, const char *__restrict__ anchors, int Nv, int Nt, int d_bytes,
     int rr, int njt, int nit, float *__restrict__ M, float *__restrict__ rowsum,
     float *__restrict__ invn_vis) {
     constexpr int MW = kStrWin * (A / 64), NT = str_threads(A);  // matrix waves, threads
     constexpr int FM = 4, FN = (R + 15) / 16;
-    constexpr int NA = A == 64 ? 4 : 3, NTK = A == 64 ? 3 : 2;  // stages: anchors, tokens
+    // stages: anchors, tokens
+    constexpr int NA = A == 64 ? 4 : 3, NTK = A == 64 && R < 64 ? 3 : 2;
+    static_assert(!TEXT || (A == 64 && R == 64), "square tiles");
     constexpr int ASTAGE = A * kStrStep, TSTAGE = 16 * FN * kStrTok;
     constexpr int IA = ASTAGE / 1024 / kStrPA;       // loads per anchor wave per step
     constexpr int IT = R * kStrTok / 1024;           // loads of the token wave per piece
@@ -325,7 +340,16 @@ __global__ __launch_bounds__(str_threads(A)) void cos_stream_kernel(
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int L = xcd_tile(blockIdx.x, gridDim.x);
-    const int jt = L % njt, it = (L / njt) % nit, b = L / (njt * nit);
+    int jt, it, b;
+    if constexpr (TEXT) {
+        const int ntri = njt * (njt + 1) / 2;
+        b = L / ntri;
+        upper_tile(L - b * ntri, njt, it, jt);
+    } else {
+        jt = L % njt;
+        it = (L / njt) % nit;
+        b = L / (njt * nit);
+    }
     const int i0 = it * A, j0 = jt * rr;
     const int nstep = (d_bytes + kStrStep - 1) / kStrStep;
     float *const red = reinterpret_cast<float *>(ring);  // [window][A][RS], after the last step
@@ -441,9 +465,9 @@ __global__ __launch_bounds__(str_threads(A)) void cos_stream_kernel(
             for (int f = 0; f < FM; ++f) {
 #pragma unroll
                 for (int g = 0; g < FN; ++g) acc[f][g] = mma16<kBF16>(a[f], t[g], acc[f][g]);
-                sa[f] += sumsq16<kBF16>(a[f]);
+                if (!TEXT) sa[f] += sumsq16<kBF16>(a[f]);
             }
-            if (h0 == 0) {
+            if (!TEXT && h0 == 0) {
 #pragma unroll
                 for (int g = 0; g < FN; ++g) st[g] += sumsq16<kBF16>(t[g]);
             }
@@ -489,6 +513,22 @@ __global__ __launch_bounds__(str_threads(A)) void cos_stream_kernel(
         }
     }
     __syncthreads();
+    if constexpr (TEXT) {
+        // one element per thread, the windows added in order; the mirrored
+        // tile column by column, so that its stores are contiguous too
+        float *Mb = M + (size_t)b * Nt * Nt;
+        for (int mirror = 0; mirror < (it == jt ? 1 : 2); ++mirror)
+            for (int e = tid; e < A * R; e += NT) {
+                const int hi = e >> 6, lo = e & 63;  // row, column of the tile written
+                const int r = mirror ? lo : hi, c = mirror ? hi : lo;
+                float dot = red[(size_t)r * RS + c];
+#pragma unroll
+                for (int w = 1; w < kStrWin; ++w) dot += red[((size_t)w * A + r) * RS + c];
+                const int i = i0 + r, j = j0 + c;
+                if (i < Nt && j < Nt) Mb[mirror ? (size_t)j * Nt + i : (size_t)i * Nt + j] = dot;
+            }
+        return;
+    }
     // 16 lanes per anchor row, FN tokens each; the windows added in order
     auto inv = [](float q) { return q > 0.f ? 1.0f / sqrtf(q) : 0.f; };
     const int l16 = tid & 15;
@@ -1280,6 +1320,78 @@ hipError_t launch_cos_stream(int dt, const void *vis, const void *anchors, int B
     const dim3 grid(B * nit * njt);
     if (A == 64) cos_stream_go<64>(grid, vis, anchors, Nv, Nt, d * 2, rr, njt, nit, M, rowsum, invn, st);
     else cos_stream_go<128>(grid, vis, anchors, Nv, Nt, d * 2, rr, njt, nit, M, rowsum, invn, st);
+    return hipGetLastError();
+}
+
+// text_gram: the self-similarity of the text rows on split-k tiles of the
+// upper triangle (it equals its transpose bit for bit, so each product is
+// formed once): partial products part[ks][b][i][j] and [j][i].
+template <int DT, int NS, int BT>
+__global__ __launch_bounds__(256) void text_gram_kernel(const char *__restrict__ text, int B, int Nt,
+                                                        int d_bytes, int nt, int KS,
+                                                        float *__restrict__ part) {
+    using G = TileGemmLds<DT, BT, BT, 2, 2, NS>;
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int wm = wave / 2, wn = wave % 2;
+    const int ntri = nt * (nt + 1) / 2;
+    const int tile = xcd_tile(blockIdx.x, gridDim.x);
+    int it, jt;
+    upper_tile(tile % ntri, nt, it, jt);
+    const int ks = (tile / ntri) % KS, b = tile / (ntri * KS);
+    const int i0 = it * BT, j0 = jt * BT;
+    const char *base = text + (size_t)b * Nt * d_bytes;
+    auto row_ptr = [&](int r) -> const char * {
+        return base + (size_t)min(r < BT ? i0 + r : j0 + r - BT, Nt - 1) * d_bytes;
+    };
+    const int nch = d_bytes / G::CHUNK;
+    const int c0 = (int)(((long long)nch * ks) / KS), c1 = (int)(((long long)nch * (ks + 1)) / KS);
+    f32x4_t acc[G::FM][G::FN];
+    float sa[G::FM], sb[G::FN];
+    G::template run<false>(row_ptr, c0, c1, acc, sa, sb);
+    float *pb = part + ((size_t)ks * B + b) * Nt * Nt;
+#pragma unroll
+    for (int fm = 0; fm < G::FM; ++fm)
+#pragma unroll
+        for (int fn = 0; fn < G::FN; ++fn) {
+            const int j = j0 + wn * G::SUB_N + fn * 16 + (lane & 15);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const int i = i0 + wm * G::SUB_M + fm * 16 + (lane >> 4) * 4 + e;
+                if (i < Nt && j < Nt) {
+                    pb[(size_t)i * Nt + j] = acc[fm][fn][e];
+                    if (it != jt) pb[(size_t)j * Nt + i] = acc[fm][fn][e];
+                }
+            }
+        }
+}
+
+hipError_t launch_text_gram(int dt, const void *text, int B, int Nt, int d, int KS, float *part,
+                            hipStream_t st) {
+    const int d_bytes = d * ((dt == kBF16) ? 2 : 4);
+    const int T = cos_uses_wide_tiles(Nt, Nt) ? kWideTile : kSplitTile;
+    const int nt = (Nt + T - 1) / T;
+    const dim3 grid(B * KS * (nt * (nt + 1) / 2));
+#define PV_TEXT_CASE(d, ns, t) \
+    hipLaunchKernelGGL((text_gram_kernel<d, ns, t>), grid, dim3(256), 0, st, (const char *)text, B, Nt, \
+                       d_bytes, nt, KS, part)
+    if (dt == kBF16) {
+        if (T == kWideTile) PV_TEXT_CASE(kBF16, 2, kWideTile);
+        else PV_TEXT_CASE(kBF16, kSplitNS, kPT);
+    } else {
+        if (T == kWideTile) PV_TEXT_CASE(kF32, 2, kWideTile);
+        else PV_TEXT_CASE(kF32, kSplitNS, kPT);
+    }
+#undef PV_TEXT_CASE
+    return hipGetLastError();
+}
+
+hipError_t launch_text_gram_stream(const void *text, int B, int Nt, int d, float *G,
+                                   hipStream_t st) {
+    const int nt = (Nt + 63) / 64;
+    hipLaunchKernelGGL((cos_stream_kernel<64, 64, true>), dim3(B * (nt * (nt + 1) / 2)),
+                       dim3(str_threads(64)), 0, st, (const char *)text, (const char *)text, Nt, Nt,
+                       d * 2, 64, nt, nt, G, nullptr, nullptr);
     return hipGetLastError();
 }
 

@@ -128,9 +128,31 @@ hipError_t launch_merge(int dt, const void *vis, int B, int Nv, int d, int N1,
                         const MergeCarry *with = nullptr);
 
 // ---- critical text tokens (Sec. 4.2)
-hipError_t launch_text_gram_sum(const float *part, int B, int Nt, int KS, float *G,
-                                hipStream_t st);
-hipError_t launch_text_rank(const float *G, int B, int Nt, float *r, int32_t *mask, int32_t *count,
+// Whether the self-similarity runs in one streaming pass over 64 x 64 tiles
+// (bf16) instead of split over k: as cos_stream_tokens, with the tiles of the
+// upper triangle only and no norms.
+inline bool text_uses_stream(int dt, int B, int Nt, int d_bytes, int ks_split) {
+    if (dt != kBF16) return false;
+    const long long nt = (Nt + 63) / 64, tiles = B * nt * (nt + 1) / 2;
+    const double full = (double)((tiles + 255) / 256) * 128 * d_bytes / 55e3 + 2.0;
+    const long long T = cos_uses_wide_tiles(Nt, Nt) ? kWideTile : kSplitTile, n = (Nt + T - 1) / T;
+    const double split = (double)B * (n * (n + 1) / 2) * 2 * T * d_bytes / 9e6 +
+                         4.0 * ks_split * B * (double)Nt * Nt * (1 / 3.3e6 + 1 / 4.5e6) + 2.0;
+    return full < split;
+}
+hipError_t launch_text_gram(int dt, const void *text, int B, int Nt, int d, int KS, float *part,
+                            hipStream_t st);
+hipError_t launch_text_gram_stream(const void *text, int B, int Nt, int d, float *G,
+                                   hipStream_t st);
+// stats: [B][Nt] pairs (row maximum, 1 / row sum); KS == 0: G holds the sums.
+hipError_t launch_text_rows(const float *part, int B, int Nt, int KS, float *G, float *stats,
+                            hipStream_t st);
+bool text_rank_fused(int Nt);  // one launch ranks a sample (r may be NULL), else cols + mark
+hipError_t launch_text_rank(const float *G, const float *stats, int B, int Nt, float *r,
+                            int32_t *mask, int32_t *count, hipStream_t st);
+hipError_t launch_text_cols(const float *G, const float *stats, int B, int Nt, float *r,
+                            hipStream_t st);
+hipError_t launch_text_mark(const float *r, int B, int Nt, int32_t *mask, int32_t *count,
                             hipStream_t st);
 
 // ---- head-aware pruning (Sec. 4.4)
