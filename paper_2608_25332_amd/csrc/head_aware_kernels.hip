@@ -52,6 +52,7 @@ __device__ __forceinline__ void lse_merge2(float &m, float &l, float &s, float m
 constexpr int kScoreCK = 64;     // keys per staged chunk
 constexpr int kScoreFlush = 8;   // chunks of column sums held in registers
 constexpr int kScoreLdsCap = 160 * 1024;
+constexpr long long kConfFill = 128;  // workgroups that fill half the CUs (head_conf)
 
 template <int NKS>
 struct ScoreStage {
@@ -64,35 +65,34 @@ struct ScoreStage {
     static_assert(STAGE % 4096 == 0, "chunk must split evenly over the waves");
 };
 
-// Where the head of list entry hi of sample b comes from.
-enum HeadSource { kHeadsArg = 0, kHeadsDevice = 1, kHeadsAll = 2 };
+// Address of the 16 bytes at `byte` of a row of row_bytes; past its end, zeros.
+__device__ __forceinline__ const char *row_piece(const char *base, int row, int row_bytes, int byte) {
+    return byte < row_bytes ? base + (size_t)row * row_bytes + byte : zero16();
+}
 
-// CONF = false: column sums of the normalised rows (the score).  CONF = true:
-// one pass only, also carrying the sum of squared probabilities of each row,
-// and one number per workgroup: the sum over its rows of the row variance
-// (the head confidence of this row block).
+// Where the head of list entry hi of sample b comes from.
+enum HeadSource { kHeadsArg = 0, kHeadsDevice = 1 };
 
 // One score workgroup; n_score: workgroups of the launch that score.
 // IDX: key j of the head is row kidx[b][j] of k ([B][H][n_src][hd], the keys
 // of every token; kidx[b] holds N indices), so the score needs no compacted
 // copy of the kept keys; the ring is then `ext_ring` (S::NS * S::STAGE bytes
 // of LDS, shared with the other workgroups of the launch).  N <= 256.
-template <int DT, int NKS, int MAXC, bool CONF, bool IDX = false>
+template <int DT, int NKS, int MAXC, bool IDX = false>
 __device__ __forceinline__ void score_partial_block(
     const char *__restrict__ q, const char *__restrict__ k, const HeadArgs &heads,
-    const int32_t *__restrict__ heads_dev, int head_src, const int32_t *__restrict__ row_mask,
-    const float *__restrict__ row_lse, int b0, int H, int Nt, int N, int n_heads,
-    float scale_log2e, float *__restrict__ partial, int cols_in_lds, int n_score,
+    const int32_t *__restrict__ heads_dev, int head_src, const float *__restrict__ row_lse, int b0,
+    int H, int Nt, int N, int n_heads, float scale_log2e, float *__restrict__ partial,
+    int cols_in_lds, int n_score,
     const int32_t *__restrict__ kidx = nullptr, int n_src = 0, char *ext_ring = nullptr) {
-    static_assert(!CONF || MAXC == 0, "the confidence needs no second pass");
-    static_assert(!IDX || (!CONF && MAXC > 0 && MAXC * kScoreCK <= 256),
+    static_assert(!IDX || (MAXC > 0 && MAXC * kScoreCK <= 256),
                   "indexed keys: one pass, at most 256 keys");
     using S = ScoreStage<NKS>;
     __shared__ __attribute__((aligned(16))) char own_ring[IDX ? 16 : S::NS * S::STAGE];
     __shared__ int32_t krow[IDX ? 256 : 1];  // IDX: the source row of every key
     char *const ring = IDX ? ext_ring : own_ring;
     __shared__ __attribute__((aligned(16))) char qrows[16 * S::RB];
-    __shared__ float sm_m[4][16], sm_l[4][16], sm_s[CONF ? 4 : 1][16];
+    __shared__ float sm_m[4][16], sm_l[4][16];
     __shared__ float row_m[16], row_il[16];
     const int nrb = (Nt + 15) / 16;
     const int L = xcd_tile(blockIdx.x, n_score);
@@ -103,8 +103,7 @@ __device__ __forceinline__ void score_partial_block(
     // branches (an MFMA does not honour the execution mask)
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     int h;
-    if (head_src == kHeadsAll) h = hi;
-    else if (head_src == kHeadsDevice) h = min(max(heads_dev[(size_t)b * n_heads + hi], 0), H - 1);
+    if (head_src == kHeadsDevice) h = min(max(heads_dev[(size_t)b * n_heads + hi], 0), H - 1);
     else h = heads.h[bl * n_heads + hi];
     const char *qb = q + ((size_t)b * H + h) * Nt * S::RB;
     const char *kb = k + ((size_t)b * H + h) * (IDX ? n_src : N) * S::RB;
@@ -207,20 +206,16 @@ __device__ __forceinline__ void score_partial_block(
 
     // pass 1: running (max, sum of exp) of the logits, per lane and row; with
     // MAXC > 0 the logit blocks also stay in registers for pass 2
-    float m[4], l[4], sq[4];
+    float m[4], l[4];
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
         m[i] = -INFINITY;
         l[i] = 0.f;
-        sq[i] = 0.f;
     }
     auto stats = [&](const f32x4_t &acc, int ch) {
         if (ch * kScoreCK + wave * 16 + (lane & 15) < N) {
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                if (CONF) lse_merge2(m[i], l[i], sq[i], acc[i] * scale_log2e, 1.f, 1.f);
-                else lse_merge(m[i], l[i], acc[i] * scale_log2e, 1.f);
-            }
+            for (int i = 0; i < 4; ++i) lse_merge(m[i], l[i], acc[i] * scale_log2e, 1.f);
         }
     };
     f32x4_t keep[MAXC > 0 ? MAXC : 1];
@@ -236,7 +231,7 @@ __device__ __forceinline__ void score_partial_block(
         for (int ch = 0; ch < nch; ++ch) stats(chunk(ch, false), ch);
     }
     finish();
-    if constexpr (MAXC > 0 && !CONF) {
+    if constexpr (MAXC > 0) {
         // Every logit at hand: the row maximum first (lanes, then waves),
         // then one exponential per logit, kept in place, and the row sums.
         // Keys past N are left out of both.
@@ -320,12 +315,7 @@ __device__ __forceinline__ void score_partial_block(
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
             const float m2 = xch(m[i]), l2 = xch(l[i]);
-            if (CONF) {
-                const float s2 = xch(sq[i]);
-                lse_merge2(m[i], l[i], sq[i], m2, l2, s2);
-            } else {
-                lse_merge(m[i], l[i], m2, l2);
-            }
+            lse_merge(m[i], l[i], m2, l2);
         }
     };
     merge_step([](float x) { return dpp_f32<0xB1>(x); });
@@ -337,50 +327,9 @@ __device__ __forceinline__ void score_partial_block(
         for (int i = 0; i < 4; ++i) {
             sm_m[wave][(lane >> 4) * 4 + i] = m[i];
             sm_l[wave][(lane >> 4) * 4 + i] = l[i];
-            if (CONF) sm_s[CONF ? wave : 0][(lane >> 4) * 4 + i] = sq[i];
         }
     }
     __syncthreads();
-    if constexpr (CONF) {
-        // rows outside row_mask add nothing (an empty mask means every row)
-        __shared__ int any_row;
-        if (row_mask) {
-            if (tid == 0) any_row = 0;
-            __syncthreads();
-            for (int i = tid; i < Nt; i += kScoreNT)
-                if (row_mask[(size_t)b * Nt + i] != 0) any_row = 1;
-            __syncthreads();
-        }
-        // Var_j(A[i][j]) = (sum_j A^2 - S^2 / N) / N over the N visual keys,
-        // with D the row's normaliser, S = l / D its visual mass and
-        // sum_j A^2 = s / D^2.  Over the visual keys alone D = l and S = 1;
-        // on the model's domain the other keys join D through their
-        // log-sum-exp (row_lse, natural log of the scaled logits), on the
-        // scale of the kept exponentials (relative to the row maximum).  The
-        // 16 rows are added in order (rows past Nt add nothing).
-        if (tid < 16) {
-            float mm = sm_m[0][tid], ll = sm_l[0][tid], ss = sm_s[0][tid];
-#pragma unroll
-            for (int w = 1; w < 4; ++w) lse_merge2(mm, ll, ss, sm_m[w][tid], sm_l[w][tid], sm_s[w][tid]);
-            const float inv_n = 1.0f / (float)N;
-            const int i = rb * 16 + tid;
-            const bool use = i < Nt && (!row_mask || !any_row || row_mask[(size_t)b * Nt + i] != 0);
-            float den = ll;
-            if (row_lse) {
-                const float t = row_lse[((size_t)b * H + h) * Nt + min(i, Nt - 1)] * 1.4426950408889634f;
-                den = ll + exp2_hw(t - mm);  // an overflow means the visual mass is 0 in fp32
-            }
-            const float mass = ll / den;
-            row_m[tid] = use ? (ss / (den * den) - mass * mass * inv_n) * inv_n : 0.f;
-        }
-        __syncthreads();
-        if (tid == 0) {
-            float c = 0.f;
-            for (int r = 0; r < 16; ++r) c += row_m[r];
-            partial[((size_t)b * H + h) * nrb + rb] = c;
-        }
-        return;
-    }
     if (tid < 16) {
         float mm = sm_m[0][tid], ll = sm_l[0][tid];
 #pragma unroll
@@ -447,15 +396,249 @@ __device__ __forceinline__ void score_partial_block(
     }
 }
 
-template <int DT, int NKS, int MAXC, bool CONF>
+template <int DT, int NKS, int MAXC>
 __global__ __launch_bounds__(kScoreNT) void score_partial_kernel(
     const char *__restrict__ q, const char *__restrict__ k, HeadArgs heads,
-    const int32_t *__restrict__ heads_dev, int head_src, const int32_t *__restrict__ row_mask,
-    const float *__restrict__ row_lse, int b0, int H, int Nt, int N, int n_heads,
-    float scale_log2e, float *__restrict__ partial, int cols_in_lds) {
-    score_partial_block<DT, NKS, MAXC, CONF>(q, k, heads, heads_dev, head_src, row_mask, row_lse,
-                                             b0, H, Nt, N, n_heads, scale_log2e, partial,
-                                             cols_in_lds, gridDim.x);
+    const int32_t *__restrict__ heads_dev, int head_src, const float *__restrict__ row_lse, int b0,
+    int H, int Nt, int N, int n_heads, float scale_log2e, float *__restrict__ partial,
+    int cols_in_lds) {
+    score_partial_block<DT, NKS, MAXC>(q, k, heads, heads_dev, head_src, row_lse, b0, H, Nt, N,
+                                       n_heads, scale_log2e, partial, cols_in_lds, gridDim.x);
+}
+
+// ----------------------------------------------------------------------------
+// head_conf: the head confidence of every head, sum over the rows of the row
+// variance, per block of 16 rows.  One pass over the keys.
+//
+// Grid: (row blocks of 16 RW rows) x H x B in XCD order, so that the row blocks
+// of one head share its keys in one L2.  Of the RW x KW waves, wave w takes the
+// 16 rows w % RW of the block and, of every chunk of 64 keys, the 4 / KW blocks
+// of 16 keys that are its own (w / RW).  RW = 4 streams a head's keys once per
+// 64 rows, RW = 1 once per 16, on four times the workgroups, for small batches.
+// The query rows and the key chunks go straight to LDS (waves 0 .. 3 issue the
+// loads), ScoreStage::NS chunks in flight.  Eight waves, so that one wave's LDS
+// reads and exponentials hide under another's products: with the same work on
+// four waves a chunk is one long chain per SIMD (17.5 against 15.4 us at 4 x 32
+// heads x 128 rows x 960 keys; short key lists are the other way round).
+//
+// Each lane carries (reference, sum, sum of squares) of the exponentials of its
+// keys; exponentials are one FMA and one v_exp_f32 each, and the vector
+// instructions per logit set the pace.  (One merge per logit with the library's
+// exp2f, on 16-row blocks, took 30.0 us at that size, a rescale of the sums in
+// every chunk 17.0.)
+// ----------------------------------------------------------------------------
+template <int DT, int NKS, int RW, int KW>
+__global__ __launch_bounds__(64 * RW * KW) void head_conf_kernel(
+    const char *__restrict__ q, const char *__restrict__ k, const int32_t *__restrict__ row_mask,
+    const float *__restrict__ row_lse, int H, int Nt, int N, int row_bytes, float scale_log2e,
+    float *__restrict__ partial) {
+    using S = ScoreStage<NKS>;
+    constexpr int NW = RW * KW, ROWS = 16 * RW;
+    constexpr int KB = 4 / KW;  // key blocks of a chunk per wave
+    static_assert(NW >= 4 && KW <= 4, "waves 0 .. 3 load; a key block is whole");
+    __shared__ __attribute__((aligned(16))) char ring[S::NS * S::STAGE];
+    __shared__ __attribute__((aligned(16))) char qrows[ROWS * S::RB];
+    __shared__ float sm_m[NW][16], sm_l[NW][16], sm_s[NW][16];
+    __shared__ float var[RW][16];
+    __shared__ int any_row;
+    const int nrb = (Nt + 15) / 16, nblk = (Nt + ROWS - 1) / ROWS;
+    const int L = xcd_tile(blockIdx.x, gridDim.x);
+    const int rb = L % nblk, h = (L / nblk) % H, b = L / (nblk * H);
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int rw = wave % RW, kw = wave / RW;
+    const char *qb = q + ((size_t)b * H + h) * Nt * row_bytes;
+    const char *kb = k + ((size_t)b * H + h) * N * row_bytes;
+    const int nch = (N + kScoreCK - 1) / kScoreCK;
+
+    int srow[S::IPW], sbyte[S::IPW];
+#pragma unroll
+    for (int t = 0; t < S::IPW; ++t) {
+        const int pos = (wave * S::IPW + t) * 64 + lane;
+        const int r = pos / S::PPR, slot = pos % S::PPR;
+        srow[t] = r;
+        sbyte[t] = (slot ^ (r & S::SWZ)) << 4;
+    }
+    auto issue = [&](int ch) {
+        char *dst = ring + (ch % S::NS) * S::STAGE + wave * S::IPW * 1024;
+#pragma unroll
+        for (int t = 0; t < S::IPW; ++t)
+            lds_dma16(row_piece(kb, min(ch * kScoreCK + srow[t], N - 1), row_bytes, sbyte[t]),
+                      dst + t * 1024);
+    };
+    const bool loads = wave < 4;
+    for (int p = wave; loads && p < NKS * RW; p += 4) {  // the query rows, 1 KiB per load
+        const int off = p * 1024 + lane * 16;
+        const int r = off / S::RB, slot = (off % S::RB) >> 4;
+        lds_dma16(row_piece(qb, min(rb * ROWS + r, Nt - 1), row_bytes, (slot ^ (r & S::SWZ)) << 4),
+                  qrows + p * 1024);
+    }
+#pragma unroll
+    for (int p = 0; p < S::NS; ++p)
+        if (loads && p < nch) issue(p);
+
+    uint4 qf[NKS];
+    float m[4], l[4], sq[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        m[i] = -3.402823466e38f;  // finite, so that a lane without keys adds zeros
+        l[i] = sq[i] = 0.f;
+    }
+    // The running statistics of this lane's keys, one chunk's logits at a
+    // time.  m is a reference no key exceeds by more than 2^kLag, not the
+    // maximum itself: the sums are rescaled only when some row of the wave
+    // outgrows it (floating point keeps its precision under any common factor,
+    // and 2^(2 kLag) N is far from the largest float).
+    constexpr float kLag = 16.f;
+    auto stats = [&](const f32x4_t(&v)[KB]) {
+        float top[4];
+        bool grow = false;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            top[i] = v[0][i];
+#pragma unroll
+            for (int kq = 1; kq < KB; ++kq) top[i] = fmaxf(top[i], v[kq][i]);
+            top[i] *= scale_log2e;
+            grow |= top[i] > m[i] + kLag;
+        }
+        if (__any(grow)) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const float mn = fmaxf(m[i], top[i]);
+                const float f = exp2_hw(m[i] - mn);
+                l[i] *= f;
+                sq[i] *= f * f;
+                m[i] = mn;
+            }
+        }
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+#pragma unroll
+            for (int kq = 0; kq < KB; ++kq) {
+                const float e = exp2_hw(fmaf(v[kq][i], scale_log2e, -m[i]));  // 0 past N
+                l[i] += e;
+                sq[i] = fmaf(e, e, sq[i]);
+            }
+        }
+    };
+    // fragments of BLK key blocks read together, their products interleaved
+    constexpr int BLK = KB * NKS <= 16 ? KB : 1;
+    f32x4_t v[KB];
+    for (int ch = 0; ch < nch; ++ch) {
+        const int issued = ch == 0 ? min(S::NS, nch) : min(ch + S::NS - 1, nch);
+        const int younger = issued - 1 - ch;
+        static_assert(S::NS <= 3, "at most two chunks younger than the one waited for");
+        if (!loads) {
+        } else if (younger >= 2) wait_vmcnt<S::IPW * 2>();
+        else if (younger == 1) wait_vmcnt<S::IPW>();
+        else wait_vmcnt<0>();
+        bare_barrier();  // chunk ch is in LDS; chunk ch - 1 has been read
+        if (loads && ch >= 1 && ch + S::NS - 1 < nch) issue(ch + S::NS - 1);
+        if (ch == 0) {
+#pragma unroll
+            for (int s = 0; s < NKS; ++s)
+                qf[s] = lds_read16(qrows + (rw * 16 + (lane & 15)) * S::RB +
+                                   (((s * 4 + (lane >> 4)) ^ ((lane & 15) & S::SWZ)) << 4));
+            lds_wait();
+#pragma unroll
+            for (int s = 0; s < NKS; ++s) lds_after_wait(qf[s]);
+        }
+        const char *sp = ring + (ch % S::NS) * S::STAGE;
+        f32x4_t w[KB];
+#pragma unroll
+        for (int k0 = 0; k0 < KB; k0 += BLK) {
+            uint4 kf[BLK][NKS];
+#pragma unroll
+            for (int kq = 0; kq < BLK; ++kq) {
+                const int r = (kw * KB + k0 + kq) * 16 + (lane & 15);
+#pragma unroll
+                for (int s = 0; s < NKS; ++s)
+                    kf[kq][s] = lds_read16(sp + r * S::RB + (((s * 4 + (lane >> 4)) ^ (r & S::SWZ)) << 4));
+            }
+            // the last chunk's statistics while this one's fragments arrive
+            if (k0 == 0 && ch > 0) stats(v);
+            lds_wait();
+#pragma unroll
+            for (int kq = 0; kq < BLK; ++kq) {
+                w[k0 + kq] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                for (int s = 0; s < NKS; ++s) lds_after_wait(kf[kq][s]);
+            }
+#pragma unroll
+            for (int s = 0; s < NKS; ++s)
+#pragma unroll
+                for (int kq = 0; kq < BLK; ++kq) w[k0 + kq] = mma16<DT>(qf[s], kf[kq][s], w[k0 + kq]);
+        }
+        if ((ch + 1) * kScoreCK > N) {  // the only chunk that can hold keys past N
+#pragma unroll
+            for (int kq = 0; kq < KB; ++kq) {
+                const bool col_ok = ch * kScoreCK + (kw * KB + kq) * 16 + (lane & 15) < N;
+#pragma unroll
+                for (int i = 0; i < 4; ++i) w[kq][i] = col_ok ? w[kq][i] : -INFINITY;
+            }
+        }
+#pragma unroll
+        for (int kq = 0; kq < KB; ++kq) v[kq] = w[kq];
+    }
+    stats(v);
+    // the 16 lanes that hold the same rows (DPP partners of an xor butterfly
+    // over 1, 2, 4, 8)
+    auto merge_step = [&](auto xch) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const float m2 = xch(m[i]), l2 = xch(l[i]), s2 = xch(sq[i]);
+            lse_merge2(m[i], l[i], sq[i], m2, l2, s2);
+        }
+    };
+    merge_step([](float x) { return dpp_f32<0xB1>(x); });
+    merge_step([](float x) { return dpp_f32<0x4E>(x); });
+    merge_step([](float x) { return dpp_f32<0x141>(x); });
+    merge_step([](float x) { return dpp_f32<0x140>(x); });
+    if ((lane & 15) == 0) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            sm_m[wave][(lane >> 4) * 4 + i] = m[i];
+            sm_l[wave][(lane >> 4) * 4 + i] = l[i];
+            sm_s[wave][(lane >> 4) * 4 + i] = sq[i];
+        }
+    }
+    // rows outside row_mask add nothing (an empty mask means every row)
+    if (tid == 0) any_row = 0;
+    __syncthreads();
+    if (row_mask) {
+        for (int i = tid; i < Nt; i += 64 * NW)
+            if (row_mask[(size_t)b * Nt + i] != 0) any_row = 1;
+        __syncthreads();
+    }
+    // Var_j(A[i][j]) = (sum_j A^2 - S^2 / N) / N over the N visual keys, with D
+    // the row's normaliser, S = l / D its visual mass and sum_j A^2 = s / D^2.
+    // Over the visual keys alone D = l and S = 1; on the model's domain the
+    // other keys join D through their log-sum-exp (row_lse, natural log of the
+    // scaled logits), on the scale of the kept exponentials (relative to the
+    // row maximum).  The 16 rows are added in order (rows past Nt add nothing).
+    if (tid < ROWS) {
+        const int g = tid >> 4, r = tid & 15;
+        float mm = sm_m[g][r], ll = sm_l[g][r], ss = sm_s[g][r];
+#pragma unroll
+        for (int w = 1; w < KW; ++w)
+            lse_merge2(mm, ll, ss, sm_m[w * RW + g][r], sm_l[w * RW + g][r], sm_s[w * RW + g][r]);
+        const float inv_n = 1.0f / (float)N;
+        const int i = rb * ROWS + tid;
+        const bool use = i < Nt && (!row_mask || !any_row || row_mask[(size_t)b * Nt + i] != 0);
+        float den = ll;
+        if (row_lse) {
+            const float t = row_lse[((size_t)b * H + h) * Nt + min(i, Nt - 1)] * 1.4426950408889634f;
+            den = ll + exp2_hw(t - mm);  // an overflow means the visual mass is 0 in fp32
+        }
+        const float mass = ll / den;
+        var[g][r] = use ? (ss / (den * den) - mass * mass * inv_n) * inv_n : 0.f;
+    }
+    __syncthreads();
+    if (tid < RW && rb * RW + tid < nrb) {
+        float c = 0.f;
+        for (int r = 0; r < 16; ++r) c += var[tid][r];
+        partial[((size_t)b * H + h) * nrb + rb * RW + tid] = c;
+    }
 }
 
 // ----------------------------------------------------------------------------
@@ -861,7 +1044,6 @@ struct ScoreLaunch {
     const int32_t *heads_host;  // kHeadsArg: host list [B][n_heads]
     const int32_t *heads_dev;   // kHeadsDevice: device list [B][n_heads]
     int src;
-    const int32_t *row_mask;    // confidence only: rows summed (may be NULL)
     const float *row_lse;       // [B][H][Nt] non-visual log-sum-exp (may be NULL)
     int B, H, Nt, N, n_heads;
     float sl2e;
@@ -872,14 +1054,14 @@ struct ScoreLaunch {
 
 // A host head list travels as a kernel argument of bounded size: a launch
 // covers as many samples as fit, and larger batches take several launches.
-// Device lists and the all-heads form need one launch.
-template <int DT, int NKS, int MAXC, bool CONF>
+// Device lists need one launch.
+template <int DT, int NKS, int MAXC>
 static hipError_t score_go(const ScoreLaunch &a) {
     using S = ScoreStage<NKS>;
     // two-pass form: the N column sums in dynamic LDS when they fit beside
     // the ring and the row statistics (at most 64 KiB of it)
     const size_t cols = (size_t)a.N * sizeof(float);
-    const bool in_lds = !CONF && MAXC == 0 && cols <= 65536 &&
+    const bool in_lds = MAXC == 0 && cols <= 65536 &&
                         (size_t)S::NS * S::STAGE + 16 * S::RB + 1024 + cols <= (size_t)kScoreLdsCap;
     const int nrb = (a.Nt + 15) / 16;
     const int per_launch = a.src == kHeadsArg ? kMaxHeadArgs / a.n_heads : a.B;
@@ -890,10 +1072,10 @@ static hipError_t score_go(const ScoreLaunch &a) {
             ha.h[i] = (a.src == kHeadsArg && i < nb * a.n_heads)
                           ? a.heads_host[(size_t)b0 * a.n_heads + i] : 0;
         dim3 grid(nrb * a.n_heads * nb);
-        hipLaunchKernelGGL((score_partial_kernel<DT, NKS, MAXC, CONF>), grid, dim3(kScoreNT),
+        hipLaunchKernelGGL((score_partial_kernel<DT, NKS, MAXC>), grid, dim3(kScoreNT),
                            in_lds ? cols : 0, a.st, (const char *)a.q, (const char *)a.k, ha,
-                           a.heads_dev, a.src, a.row_mask, a.row_lse, b0, a.H, a.Nt, a.N,
-                           a.n_heads, a.sl2e, a.partial, in_lds ? 1 : 0);
+                           a.heads_dev, a.src, a.row_lse, b0, a.H, a.Nt, a.N, a.n_heads, a.sl2e,
+                           a.partial, in_lds ? 1 : 0);
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
@@ -907,47 +1089,76 @@ static hipError_t score_go(const ScoreLaunch &a) {
 template <int NKS>
 constexpr int score_maxc_cap() { return NKS <= 4 ? 32 : (NKS <= 8 ? 8 : 4); }
 
-template <int DT, int NKS, bool CONF>
+template <int DT, int NKS>
 static hipError_t score_nks(const ScoreLaunch &a) {
-    if constexpr (CONF) {
-        return score_go<DT, NKS, 0, true>(a);
-    } else {
-        const int nch = (a.N + kScoreCK - 1) / kScoreCK;
-        constexpr int cap = score_maxc_cap<NKS>();
+    const int nch = (a.N + kScoreCK - 1) / kScoreCK;
+    constexpr int cap = score_maxc_cap<NKS>();
 #define PV_MAXC_CASE(mc) \
-    if (nch <= mc && mc <= cap) return score_go<DT, NKS, (mc <= cap ? mc : 0), false>(a);
-        PV_MAXC_CASE(1)
-        PV_MAXC_CASE(2)
-        PV_MAXC_CASE(4)
-        PV_MAXC_CASE(8)
-        PV_MAXC_CASE(16)
-        PV_MAXC_CASE(32)
+    if (nch <= mc && mc <= cap) return score_go<DT, NKS, (mc <= cap ? mc : 0)>(a);
+    PV_MAXC_CASE(1)
+    PV_MAXC_CASE(2)
+    PV_MAXC_CASE(4)
+    PV_MAXC_CASE(8)
+    PV_MAXC_CASE(16)
+    PV_MAXC_CASE(32)
 #undef PV_MAXC_CASE
-        return score_go<DT, NKS, 0, false>(a);
-    }
+    return score_go<DT, NKS, 0>(a);
 }
 
-template <int DT, bool CONF>
+#define PV_NKS_CASES \
+    PV_NKS_CASE(1)   \
+    PV_NKS_CASE(2)   \
+    PV_NKS_CASE(3)   \
+    PV_NKS_CASE(4)   \
+    PV_NKS_CASE(5)   \
+    PV_NKS_CASE(6)   \
+    PV_NKS_CASE(7)   \
+    PV_NKS_CASE(8)   \
+    PV_NKS_CASE(10)  \
+    PV_NKS_CASE(12)  \
+    PV_NKS_CASE(14)  \
+    PV_NKS_CASE(16)
+
+template <int DT>
 static hipError_t score_dt(int nks, const ScoreLaunch &a) {
 #define PV_NKS_CASE(n) \
     case n:            \
-        return score_nks<DT, n, CONF>(a);
-    switch (nks) {
-        PV_NKS_CASE(1)
-        PV_NKS_CASE(2)
-        PV_NKS_CASE(3)
-        PV_NKS_CASE(4)
-        PV_NKS_CASE(5)
-        PV_NKS_CASE(6)
-        PV_NKS_CASE(7)
-        PV_NKS_CASE(8)
-        PV_NKS_CASE(10)
-        PV_NKS_CASE(12)
-        PV_NKS_CASE(14)
-        PV_NKS_CASE(16)
-    }
+        return score_nks<DT, n>(a);
+    switch (nks) { PV_NKS_CASES }
 #undef PV_NKS_CASE
     return hipErrorInvalidValue;
+}
+
+// Rows per workgroup of the confidence (16 RW) and waves per row block (KW): the
+// fewest passes over the keys that still fill half the CUs; a second set of
+// waves once the keys are more than a few chunks.  Measured (us; RW, KW = 1, 4 /
+// 2, 2 / 4, 1 / 4, 2), 32 heads of 128: 4 x 128 rows x 960 keys 24.5 / 16.6 / 17.5 / 15.4;
+// 8 x 64 x 192 11.9 / 7.4 / 6.8 / 7.3; 1 x 64 x 192 (32 workgroups at RW = 4)
+// 5.7 / 5.8 / 6.6 / 7.0; 1 x 128 x 4096 (64 of them) 29 / 39 / 54 / 42.
+template <int DT, int NKS>
+static hipError_t head_conf_go(const char *q, const char *k, const int32_t *row_mask,
+                               const float *row_lse, int B, int H, int Nt, int N, int row_bytes,
+                               float sl2e, float *partial, hipStream_t st) {
+    auto wgs = [&](int rw) { return (long long)((Nt + 16 * rw - 1) / (16 * rw)) * H * B; };
+#define PV_CONF_GO(rw, kw)                                                                         \
+    hipLaunchKernelGGL((head_conf_kernel<DT, NKS, rw, kw>), dim3((unsigned)wgs(rw)),               \
+                       dim3(64 * rw * kw), 0, st, q, k, row_mask, row_lse, H, Nt, N, row_bytes, sl2e, \
+                       partial)
+    // (the query rows of the wider blocks would not fit beside a wide ring)
+    if constexpr (NKS <= 8) {
+        if (Nt > 32 && wgs(4) >= kConfFill) {
+            if (N > 4 * kScoreCK) PV_CONF_GO(4, 2);
+            else PV_CONF_GO(4, 1);
+            return hipGetLastError();
+        }
+        if (Nt > 16 && Nt <= 32 && wgs(2) >= kConfFill) {
+            PV_CONF_GO(2, 2);
+            return hipGetLastError();
+        }
+    }
+    PV_CONF_GO(1, 4);
+#undef PV_CONF_GO
+    return hipGetLastError();
 }
 
 template <int DT, int NKS>
@@ -1004,13 +1215,12 @@ static float scale_log2e_of(const ScoreLaunch &a, int hd) {
     return (float)(1.4426950408889634 / sqrt((double)(a.hd_scale > 0 ? a.hd_scale : hd)));
 }
 
-template <bool CONF>
 static hipError_t score_any(int dt, int hd, ScoreLaunch a) {
     const int esz = (dt == kBF16) ? 2 : 4;
     const int nks = hd * esz / 64;
     a.sl2e = scale_log2e_of(a, hd);
-    if (dt == kBF16) return score_dt<kBF16, CONF>(nks, a);
-    return score_dt<kF32, CONF>(nks, a);
+    if (dt == kBF16) return score_dt<kBF16>(nks, a);
+    return score_dt<kF32>(nks, a);
 }
 
 // The whole-head form pays once there are enough (head, sample) pairs to
@@ -1042,7 +1252,7 @@ hipError_t launch_score_partial(int dt, const void *q, const void *k, const int3
                                 const int32_t *heads_dev, const float *row_lse, int B, int H,
                                 int Nt, int N, int hd, int hd_scale, int n_heads, float *partial,
                                 float *split_stats, hipStream_t st) {
-    ScoreLaunch a{q, k, heads_host, heads_dev, heads_dev ? kHeadsDevice : kHeadsArg, nullptr,
+    ScoreLaunch a{q, k, heads_host, heads_dev, heads_dev ? kHeadsDevice : kHeadsArg,
                   row_lse, B, H, Nt, N, n_heads, 0.f, partial, st};
     a.hd_scale = hd_scale;
     const int nks = hd * ((dt == kBF16) ? 2 : 4) / 64;
@@ -1059,16 +1269,24 @@ hipError_t launch_score_partial(int dt, const void *q, const void *k, const int3
         if (dt == kBF16) return nks == 2 ? score_head_go<kBF16, 2>(a) : score_head_go<kBF16, 4>(a);
         return nks == 2 ? score_head_go<kF32, 2>(a) : score_head_go<kF32, 4>(a);
     }
-    return score_any<false>(dt, hd, a);
+    return score_any(dt, hd, a);
 }
 
 hipError_t launch_head_conf(int dt, const void *q, const void *k, const int32_t *row_mask,
                             const float *row_lse, int B, int H, int Nt, int N, int hd,
                             int hd_scale, float *partial, hipStream_t st) {
-    ScoreLaunch a{q, k, nullptr, nullptr, kHeadsAll, row_mask, row_lse, B, H, Nt, N, H, 0.f,
-                  partial, st};
-    a.hd_scale = hd_scale;
-    return score_any<true>(dt, hd, a);
+    const int row_bytes = hd * ((dt == kBF16) ? 2 : 4);
+    const float sl2e = (float)(1.4426950408889634 / sqrt((double)hd_scale));
+    const char *qc = (const char *)q, *kc = (const char *)k;
+#define PV_NKS_CASE(n)                                                                            \
+    case n:                                                                                       \
+        return dt == kBF16 ? head_conf_go<kBF16, n>(qc, kc, row_mask, row_lse, B, H, Nt, N,       \
+                                                    row_bytes, sl2e, partial, st)                 \
+                           : head_conf_go<kF32, n>(qc, kc, row_mask, row_lse, B, H, Nt, N,        \
+                                                   row_bytes, sl2e, partial, st);
+    switch (row_bytes / 64) { PV_NKS_CASES }
+#undef PV_NKS_CASE
+    return hipErrorInvalidValue;
 }
 
 // ----------------------------------------------------------------------------
@@ -1101,9 +1319,9 @@ __global__ __launch_bounds__(kScoreNT) void gram_score_kernel(
                                               gj.nblocks, (int)blockIdx.x - n_score, ring);
         return;
     }
-    score_partial_block<DT, NKS, MAXC, false, true>(q, k_full, heads, nullptr, kHeadsArg, nullptr,
-                                                    nullptr, 0, H, Nt, N, n_heads, scale_log2e,
-                                                    partial, 0, n_score, kidx, n_src, ring);
+    score_partial_block<DT, NKS, MAXC, true>(q, k_full, heads, nullptr, kHeadsArg, nullptr, 0, H, Nt,
+                                             N, n_heads, scale_log2e, partial, 0, n_score, kidx,
+                                             n_src, ring);
 }
 
 __global__ __launch_bounds__(kScoreNT) void reduce_select_gather_kernel(ReduceJob rj, SelectJob sj,
