@@ -33,10 +33,10 @@
  *     bits (no floating-point atomics; every reduction has a fixed order).
  *   - Widths: an embedding width d or head width hd may be any multiple of 8
  *     in range.  The matrix-core kernels stream 128-byte chunks of embedding
- *     rows and a multiple of 32 elements of head rows; a call whose rows
- *     have another width first copies them, zero-padded, into its workspace
- *     (zeros change no dot product and no norm; the attention scale keeps
- *     the true hd).  The workspace queries include those copies.
+ *     rows; a call whose embedding rows have another width first copies them,
+ *     zero-padded, into its workspace (zeros change no dot product and no
+ *     norm), and the workspace queries include those copies.  Head rows of
+ *     any such width are read in place.
  */
 #ifndef PROVIP_H
 #define PROVIP_H

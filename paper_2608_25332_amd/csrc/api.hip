@@ -38,10 +38,10 @@ bool aligned16(const void *p) { return ((uintptr_t)p & 15u) == 0; }
 size_t round_up(size_t x) { return (x + kAlign - 1) / kAlign * kAlign; }
 
 // Widths the matrix-core kernels stream: embedding rows in 128-byte k chunks,
-// head rows in 64-byte windows with a whole number of 128-byte chunks for
-// fp32 (a multiple of 32 elements either way).  A row of another width (any
-// multiple of 8 elements) is copied into a zero-padded row of the next such
-// width first; zeros change no dot product and no norm.
+// head rows in multiples of 32 elements.  An embedding row of another width
+// (any multiple of 8 elements) is copied into a zero-padded row of the next
+// such width first; the head kernels read zeros past the end of a row.  Zeros
+// change no dot product and no norm.
 int padded_d(int d, int esz) { return (d * esz + 127) / 128 * 128 / esz; }
 int padded_hd(int hd) { return (hd + 31) / 32 * 32; }
 
@@ -391,13 +391,8 @@ HeadPlan plan_head(void *ws, int B, int Nt, int N, int n_heads, bool want_v) {
     return P;
 }
 
-// Workspace of a head-aware call: its plan, plus zero-padded copies of Q and
-// K when hd is not a streamed width.
-size_t head_total_bytes(int B, int H, int Nt, int N, int hd, int esz, int n_heads, bool want_v) {
-    size_t b = round_up(plan_head(nullptr, B, Nt, N, n_heads, want_v).bytes);
-    const int hp = padded_hd(hd);
-    if (hp != hd) b += round_up((size_t)B * H * Nt * hp * esz) + round_up((size_t)B * H * N * hp * esz);
-    return b + kAlign;
+size_t head_total_bytes(int B, int Nt, int N, int n_heads, bool want_v) {
+    return round_up(plan_head(nullptr, B, Nt, N, n_heads, want_v).bytes) + kAlign;
 }
 
 int check_qk(const void *q, const void *k, int B, int H, int Nt, int N, int hd, int dtype) {
@@ -446,8 +441,7 @@ int head_impl(const void *q, const void *k, const int32_t *heads, const int32_t 
     if (row_lse && (uintptr_t)row_lse % 4) return PV_ERR_ALIGN;
     int rc = check_head(q, k, heads, heads_dev, n_heads, B, H, Nt, N, hd, dtype, budget, kept);
     if (rc != PV_OK) return rc;
-    const int esz = (dtype == PV_BF16) ? 2 : 4;
-    if (!workspace || ws_bytes < head_total_bytes(B, H, Nt, N, hd, esz, n_heads, score == nullptr))
+    if (!workspace || ws_bytes < head_total_bytes(B, Nt, N, n_heads, score == nullptr))
         return PV_ERR_WORKSPACE;
     for (const void *p : {q, k, (const void *)kept, (const void *)score, (const void *)workspace})
         if (p && !aligned16(p)) return PV_ERR_ALIGN;
@@ -458,31 +452,14 @@ int head_impl(const void *q, const void *k, const int32_t *heads, const int32_t 
     hipStream_t st = (hipStream_t)stream;
     Trace tr{events, n_events, names, reps, st};
     if (!tr.handles_ok()) return PV_ERR_NULL;
-    // the rows the products read: the inputs, or their zero-padded copies
-    const int hp = padded_hd(hd);
-    const void *q_k = q, *k_k = k;
-    if (hp != hd) {
-        char *qp = wsa + round_up(P.bytes);
-        char *kp = qp + round_up((size_t)B * H * Nt * hp * esz);
-        if (!tr.launch("pad", [&] {
-                return pv::launch_pad_rows(q, qp, (long long)B * H * Nt, hd * esz, hp * esz, st);
-            }) ||
-            !tr.launch("pad", [&] {
-                return pv::launch_pad_rows(k, kp, (long long)B * H * N, hd * esz, hp * esz, st);
-            }))
-            return PV_ERR_HIP;
-        q_k = qp;
-        k_k = kp;
-    }
-
     if (!tr.launch("score_partial", [&] {
-            return pv::launch_score_partial(dt, q_k, k_k, heads, heads_dev, row_lse, B, H, Nt, N,
-                                            hp, hd, n_heads, P.partial, P.stats, st);
+            return pv::launch_score_partial(dt, q, k, heads, heads_dev, row_lse, B, H, Nt, N, hd,
+                                            n_heads, P.partial, P.stats, st);
         }))
         return PV_ERR_HIP;
     const float inv_norm = (float)(1.0 / ((double)Nt * (double)n_heads));
     if (!tr.launch("score_select", [&] {
-            const int parts = pv::score_parts(dt, B, H, n_heads, Nt, N, hp);
+            const int parts = pv::score_parts(dt, B, H, n_heads, Nt, N, hd);
             return pv::launch_score_select(P.partial, B, n_heads * parts, N, inv_norm, v, budget,
                                            kept, st);
         }))
@@ -498,14 +475,6 @@ size_t vis_heads_bytes(int B, int H, int Nt) {
     return c.off + kAlign;
 }
 
-// The same plus zero-padded copies of Q and K when hd is not a streamed width.
-size_t vis_heads_total_bytes(int B, int H, int Nt, int N, int hd, int esz) {
-    size_t b = round_up(vis_heads_bytes(B, H, Nt));
-    const int hp = padded_hd(hd);
-    if (hp != hd) b += round_up((size_t)B * H * Nt * hp * esz) + round_up((size_t)B * H * N * hp * esz);
-    return b + kAlign;
-}
-
 int vis_heads_impl(const void *q, const void *k, int B, int H, int Nt, int N, int hd, int dtype,
                    int n_vis, int32_t *heads_out, float *conf, void *workspace, size_t ws_bytes,
                    void *stream, void *const *events, int n_events, int reps, int *n_kernels,
@@ -518,9 +487,7 @@ int vis_heads_impl(const void *q, const void *k, int B, int H, int Nt, int N, in
     int rc = check_qk(q, k, B, H, Nt, N, hd, dtype);
     if (rc != PV_OK) return rc;
     if (H > PV_MAX_HEADS || n_vis < 1 || n_vis > H) return PV_ERR_HEADS;
-    const int esz = (dtype == PV_BF16) ? 2 : 4;
-    if (!workspace || ws_bytes < vis_heads_total_bytes(B, H, Nt, N, hd, esz))
-        return PV_ERR_WORKSPACE;
+    if (!workspace || ws_bytes < vis_heads_bytes(B, H, Nt)) return PV_ERR_WORKSPACE;
     for (const void *p : {(const void *)heads_out, (const void *)conf, (const void *)workspace})
         if (p && !aligned16(p)) return PV_ERR_ALIGN;
     char *wsa = (char *)(((uintptr_t)workspace + kAlign - 1) / kAlign * kAlign);
@@ -529,25 +496,8 @@ int vis_heads_impl(const void *q, const void *k, int B, int H, int Nt, int N, in
     hipStream_t st = (hipStream_t)stream;
     Trace tr{events, n_events, names, reps, st};
     if (!tr.handles_ok()) return PV_ERR_NULL;
-    // the rows the products read: the inputs, or their zero-padded copies
-    const int hp = padded_hd(hd);
-    const void *q_k = q, *k_k = k;
-    if (hp != hd) {
-        char *qp = wsa + round_up(vis_heads_bytes(B, H, Nt));
-        char *kp = qp + round_up((size_t)B * H * Nt * hp * esz);
-        if (!tr.launch("pad", [&] {
-                return pv::launch_pad_rows(q, qp, (long long)B * H * Nt, hd * esz, hp * esz, st);
-            }) ||
-            !tr.launch("pad", [&] {
-                return pv::launch_pad_rows(k, kp, (long long)B * H * N, hd * esz, hp * esz, st);
-            }))
-            return PV_ERR_HIP;
-        q_k = qp;
-        k_k = kp;
-    }
     if (!tr.launch("head_conf", [&] {
-            return pv::launch_head_conf(dt, q_k, k_k, row_mask, row_lse, B, H, Nt, N, hp, hd, part,
-                                        st);
+            return pv::launch_head_conf(dt, q, k, row_mask, row_lse, B, H, Nt, N, hd, part, st);
         }))
         return PV_ERR_HIP;
     if (!tr.launch("conf_select", [&] {
@@ -755,7 +705,7 @@ PV_API size_t pv_head_aware_workspace_bytes(int B, int H, int Nt, int N, int hd,
     (void)budget;
     if (B < 1 || H < 1 || Nt < 1 || N < 1 || hd < 1 || n_heads < 1) return 0;
     if (dtype != PV_F32 && dtype != PV_BF16) return 0;
-    return head_total_bytes(B, H, Nt, N, hd, dtype == PV_BF16 ? 2 : 4, n_heads, true);
+    return head_total_bytes(B, Nt, N, n_heads, true);
 }
 
 PV_API int pv_prune_head_aware(const void *q, const void *k, const int32_t *heads_host, int n_heads,
@@ -829,7 +779,7 @@ PV_API size_t pv_visual_heads_workspace_bytes(int B, int H, int Nt) {
 PV_API size_t pv_visual_heads_workspace_bytes_hd(int B, int H, int Nt, int N, int hd, int dtype) {
     if (B < 1 || H < 1 || Nt < 1 || N < 1 || hd < 1) return 0;
     if (dtype != PV_F32 && dtype != PV_BF16) return 0;
-    return vis_heads_total_bytes(B, H, Nt, N, hd, dtype == PV_BF16 ? 2 : 4);
+    return vis_heads_bytes(B, H, Nt);
 }
 
 PV_API int pv_visual_heads(const void *q, const void *k, int B, int H, int Nt, int N, int hd,
@@ -1001,7 +951,7 @@ struct PipeSizes {
 
 PipeSizes pipe_sizes(int B, int Nv, int Nt, int d, int H, int hd, int esz, int N1, int n_heads) {
     const size_t D = round_up(dedup_total_bytes(B, Nv, Nt, d, esz, N1, false, false, true));
-    const size_t Hh = round_up(head_total_bytes(B, H, Nt, N1, hd, esz, n_heads, false));
+    const size_t Hh = round_up(head_total_bytes(B, Nt, N1, n_heads, false));
     const size_t S = round_up((size_t)B * N1 * sizeof(int32_t));  // each slot's place among the N_2
     return PipeSizes{D, Hh, S, D + Hh + S + kAlign};
 }
@@ -1198,9 +1148,9 @@ ProgPlan plan_prog(void *ws, int B, int Nv, int Nt, int d, int H, int hd, int es
     ProgPlan P;
     P.text = text_total_bytes(B, Nt, d, esz);
     P.dedup = dedup_total_bytes(B, Nv, Nt, d, esz, N1, true, false, true);
-    P.vh = vis_heads_total_bytes(B, H, Nt, N1, hd, esz);
-    P.head_b = head_total_bytes(B, H, Nt, N1, hd, esz, n_vis, !want_s2);
-    P.head_c = head_total_bytes(B, H, Nt, N2, hd, esz, H, !want_s3);
+    P.vh = vis_heads_bytes(B, H, Nt);
+    P.head_b = head_total_bytes(B, Nt, N1, n_vis, !want_s2);
+    P.head_c = head_total_bytes(B, Nt, N2, H, !want_s3);
     Carve c(ws);
     P.ws_text = c.take<char>(P.text);
     P.ws_dedup = c.take<char>(P.dedup);

@@ -21,6 +21,8 @@
 #include <math.h>
 #include <string.h>
 
+#include <type_traits>
+
 namespace pv {
 
 constexpr int kScoreNT = 256;
@@ -66,8 +68,21 @@ struct ScoreStage {
 };
 
 // Address of the 16 bytes at `byte` of a row of row_bytes; past its end, zeros.
+// Rows of any width (a multiple of 16 bytes) are thus read in place as rows of
+// 64 NKS bytes.  (Copying Q and K of every head into zero-padded rows first took
+// two launches of 2.8 and 9.2 us at 8 x 32 heads x 577 keys of 80, where the
+// score reads 6 of the heads in 9.0 us.)
 __device__ __forceinline__ const char *row_piece(const char *base, int row, int row_bytes, int byte) {
     return byte < row_bytes ? base + (size_t)row * row_bytes + byte : zero16();
+}
+
+// The same with FULL: the row is whole (row_bytes == RB), nothing to compare or
+// select.  (The comparison cost the whole-head form 1.1 us of 32 at 64 x 32
+// heads x 192 keys of 128.  A uniform branch around its loads costs nothing;
+// in the split form's short kernels the longer code cost 2 us of 11.)
+template <bool FULL, int RB>
+__device__ __forceinline__ const char *row_at(const char *base, int row, int row_bytes, int byte) {
+    return FULL ? base + (size_t)row * RB + byte : row_piece(base, row, row_bytes, byte);
 }
 
 // Where the head of list entry hi of sample b comes from.
@@ -82,8 +97,8 @@ template <int DT, int NKS, int MAXC, bool IDX = false>
 __device__ __forceinline__ void score_partial_block(
     const char *__restrict__ q, const char *__restrict__ k, const HeadArgs &heads,
     const int32_t *__restrict__ heads_dev, int head_src, const float *__restrict__ row_lse, int b0,
-    int H, int Nt, int N, int n_heads, float scale_log2e, float *__restrict__ partial,
-    int cols_in_lds, int n_score,
+    int H, int Nt, int N, int n_heads, int row_bytes, float scale_log2e,
+    float *__restrict__ partial, int cols_in_lds, int n_score,
     const int32_t *__restrict__ kidx = nullptr, int n_src = 0, char *ext_ring = nullptr) {
     static_assert(!IDX || (MAXC > 0 && MAXC * kScoreCK <= 256),
                   "indexed keys: one pass, at most 256 keys");
@@ -105,8 +120,8 @@ __device__ __forceinline__ void score_partial_block(
     int h;
     if (head_src == kHeadsDevice) h = min(max(heads_dev[(size_t)b * n_heads + hi], 0), H - 1);
     else h = heads.h[bl * n_heads + hi];
-    const char *qb = q + ((size_t)b * H + h) * Nt * S::RB;
-    const char *kb = k + ((size_t)b * H + h) * (IDX ? n_src : N) * S::RB;
+    const char *qb = q + ((size_t)b * H + h) * Nt * row_bytes;
+    const char *kb = k + ((size_t)b * H + h) * (IDX ? n_src : N) * row_bytes;
     if constexpr (IDX) {
         // ordinary loads, all retired at the barrier: the ring's loads below
         // are then the only ones in flight (see the ordering note)
@@ -133,7 +148,7 @@ __device__ __forceinline__ void score_partial_block(
         for (int t = 0; t < S::IPW; ++t) {
             const int key = min(ch * kScoreCK + srow[t], N - 1);  // past the end: last key
             const int row = IDX ? krow[key] : key;
-            lds_dma16(kb + (size_t)row * S::RB + sbyte[t], dst + t * 1024);
+            lds_dma16(row_piece(kb, row, row_bytes, sbyte[t]), dst + t * 1024);
         }
     };
     // Every global load of the kernel is a direct-to-LDS load, and those
@@ -150,7 +165,7 @@ __device__ __forceinline__ void score_partial_block(
             const int off = p * 1024 + lane * 16;
             const int r = off / S::RB, slot = (off % S::RB) >> 4;
             // the keys' piece swizzle, so the fragment reads spread over the banks
-            lds_dma16(qb + (size_t)min(rb * 16 + r, Nt - 1) * S::RB + ((slot ^ (r & S::SWZ)) << 4),
+            lds_dma16(row_piece(qb, min(rb * 16 + r, Nt - 1), row_bytes, (slot ^ (r & S::SWZ)) << 4),
                       qrows + p * 1024);
         }
     };
@@ -400,10 +415,11 @@ template <int DT, int NKS, int MAXC>
 __global__ __launch_bounds__(kScoreNT) void score_partial_kernel(
     const char *__restrict__ q, const char *__restrict__ k, HeadArgs heads,
     const int32_t *__restrict__ heads_dev, int head_src, const float *__restrict__ row_lse, int b0,
-    int H, int Nt, int N, int n_heads, float scale_log2e, float *__restrict__ partial,
-    int cols_in_lds) {
+    int H, int Nt, int N, int n_heads, int row_bytes, float scale_log2e,
+    float *__restrict__ partial, int cols_in_lds) {
     score_partial_block<DT, NKS, MAXC>(q, k, heads, heads_dev, head_src, row_lse, b0, H, Nt, N,
-                                       n_heads, scale_log2e, partial, cols_in_lds, gridDim.x);
+                                       n_heads, row_bytes, scale_log2e, partial, cols_in_lds,
+                                       gridDim.x);
 }
 
 // ----------------------------------------------------------------------------
@@ -743,7 +759,8 @@ template <int DT, int NKS>
 __global__ __launch_bounds__(kScoreNT) void score_head_kernel(
     const char *__restrict__ q, const char *__restrict__ k, HeadArgs8 heads,
     const int32_t *__restrict__ heads_dev, int head_src, const float *__restrict__ row_lse, int b0,
-    int H, int Nt, int N, int n_heads, float scale_log2e, float *__restrict__ partial) {
+    int H, int Nt, int N, int n_heads, int row_bytes, float scale_log2e,
+    float *__restrict__ partial) {
     using S = ScoreStage<NKS>;
     constexpr int MAXC = kHeadMaxChunks;
     // the key chunks in dynamic LDS, nch of them (so that three workgroups
@@ -761,8 +778,8 @@ __global__ __launch_bounds__(kScoreNT) void score_head_kernel(
         const int e = bl * n_heads + hi;
         h = (int)((heads.w[e >> 2] >> ((e & 3) * 8)) & 0xFFu);
     }
-    const char *qb = q + ((size_t)b * H + h) * Nt * S::RB;
-    const char *kb = k + ((size_t)b * H + h) * N * S::RB;
+    const char *qb = q + ((size_t)b * H + h) * Nt * row_bytes;
+    const char *kb = k + ((size_t)b * H + h) * N * row_bytes;
     const int nch = (N + kScoreCK - 1) / kScoreCK;  // <= MAXC (host-checked)
 
     // every load of the kernel is issued up front: this wave's query rows
@@ -772,24 +789,30 @@ __global__ __launch_bounds__(kScoreNT) void score_head_kernel(
     // workgroup onto a CU.
     const bool rows_live = wave * 16 < Nt;  // uniform: this wave has rows to score
     uint4 qf[NKS];
-    if (rows_live) {
-        const char *qrow = qb + (size_t)min(wave * 16 + (lane & 15), Nt - 1) * S::RB;
+    auto issue = [&](auto full) {
+        constexpr bool FULL = decltype(full)::value;
+        if (rows_live) {
+            const int row = min(wave * 16 + (lane & 15), Nt - 1);
 #pragma unroll
-        for (int s = 0; s < NKS; ++s) qf[s] = ld16(qrow + ((s * 4 + (lane >> 4)) << 4));
-    }
+            for (int s = 0; s < NKS; ++s)
+                qf[s] = ld16(row_at<FULL, S::RB>(qb, row, row_bytes, (s * 4 + (lane >> 4)) << 4));
+        }
 #pragma unroll
-    for (int ch = 0; ch < MAXC; ++ch) {
-        if (ch < nch) {
+        for (int ch = 0; ch < MAXC; ++ch) {
+            if (ch < nch) {
 #pragma unroll
-            for (int t = 0; t < S::IPW; ++t) {
-                const int pos = (wave * S::IPW + t) * 64 + lane;
-                const int r = pos / S::PPR, slot = pos % S::PPR;
-                const int row = min(ch * kScoreCK + r, N - 1);  // past the end: last key
-                lds_dma16(kb + (size_t)row * S::RB + ((slot ^ (r & S::SWZ)) << 4),
-                          kbuf(ch) + (wave * S::IPW + t) * 1024);
+                for (int t = 0; t < S::IPW; ++t) {
+                    const int pos = (wave * S::IPW + t) * 64 + lane;
+                    const int r = pos / S::PPR, slot = pos % S::PPR;
+                    const int row = min(ch * kScoreCK + r, N - 1);  // past the end: last key
+                    lds_dma16(row_at<FULL, S::RB>(kb, row, row_bytes, (slot ^ (r & S::SWZ)) << 4),
+                              kbuf(ch) + (wave * S::IPW + t) * 1024);
+                }
             }
         }
-    }
+    };
+    if (row_bytes == S::RB) issue(std::true_type{});
+    else issue(std::false_type{});
     wait_vmcnt<0>();
     bare_barrier();
 
@@ -888,54 +911,56 @@ __device__ __forceinline__ SplitCoord split_coord(const HeadArgs &heads,
     return c;
 }
 
-// The chunk's (at most 64) keys into LDS (rows past N repeat the last key).
-template <int NKS>
-__device__ __forceinline__ void split_load_keys(const char *kb, int key0, int N, char *kbuf,
-                                                int wave, int lane) {
+// The loads of the chunk's (at most 64) keys into LDS (rows past N repeat the
+// last key).
+template <bool FULL, int NKS>
+__device__ __forceinline__ void split_load_keys(const char *kb, int key0, int N, int row_bytes,
+                                                char *kbuf, int wave, int lane) {
     using S = ScoreStage<NKS>;
 #pragma unroll
     for (int t = 0; t < S::IPW; ++t) {
         const int pos = (wave * S::IPW + t) * 64 + lane;
         const int r = pos / S::PPR, slot = pos % S::PPR;
-        const int row = min(key0 + r, N - 1);
-        lds_dma16(kb + (size_t)row * S::RB + ((slot ^ (r & S::SWZ)) << 4),
+        lds_dma16(row_at<FULL, S::RB>(kb, min(key0 + r, N - 1), row_bytes,
+                                      (slot ^ (r & S::SWZ)) << 4),
                   kbuf + (wave * S::IPW + t) * 1024);
     }
-    wait_vmcnt<0>();
-    bare_barrier();
 }
 
 // Logits of this wave's 16 rows starting at r0 against the chunk:
 // keep[0][kq] = rows 4 (lane / 16) + i x keys 16 kq + lane % 16.
-template <int DT, int NKS>
-__device__ __forceinline__ void split_logits(const char *qb, int r0, int Nt, const char *kbuf,
-                                             int lane, f32x4_t (&keep)[1][4]) {
-    using S = ScoreStage<NKS>;
+template <bool FULL, int DT, int NKS>
+__device__ __forceinline__ void split_logits(const char *qb, int r0, int Nt, int row_bytes,
+                                             const char *kbuf, int lane, f32x4_t (&keep)[1][4]) {
+    constexpr int RB = ScoreStage<NKS>::RB;
     uint4 qf[NKS];
-    const char *qrow = qb + (size_t)min(r0 + (lane & 15), Nt - 1) * S::RB;
+    const int row = min(r0 + (lane & 15), Nt - 1);
 #pragma unroll
-    for (int s = 0; s < NKS; ++s) qf[s] = ld16(qrow + ((s * 4 + (lane >> 4)) << 4));
+    for (int s = 0; s < NKS; ++s)
+        qf[s] = ld16(row_at<FULL, RB>(qb, row, row_bytes, (s * 4 + (lane >> 4)) << 4));
     head_chunk_logits<DT, NKS>(kbuf, qf, lane, keep[0]);
 }
 
-template <int DT, int NKS>
+template <bool FULL, int DT, int NKS>
 __global__ __launch_bounds__(kScoreNT) void score_split_stats_kernel(
     const char *__restrict__ q, const char *__restrict__ k, HeadArgs heads,
     const int32_t *__restrict__ heads_dev, int head_src, int b0, int H, int Nt, int N,
-    int n_heads, int nsplit, float scale_log2e, float2 *__restrict__ stats) {
+    int n_heads, int nsplit, int row_bytes, float scale_log2e, float2 *__restrict__ stats) {
     using S = ScoreStage<NKS>;
     __shared__ __attribute__((aligned(16))) char kbuf[S::STAGE];
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const SplitCoord c = split_coord(heads, heads_dev, head_src, b0, H, nsplit, n_heads);
-    const char *qb = q + ((size_t)c.b * H + c.h) * Nt * S::RB;
-    const char *kb = k + ((size_t)c.b * H + c.h) * N * S::RB;
+    const char *qb = q + ((size_t)c.b * H + c.h) * Nt * row_bytes;
+    const char *kb = k + ((size_t)c.b * H + c.h) * N * row_bytes;
     const int key0 = c.s * kScoreCK;
-    split_load_keys<NKS>(kb, key0, N, kbuf, wave, lane);
+    split_load_keys<FULL, NKS>(kb, key0, N, row_bytes, kbuf, wave, lane);
+    wait_vmcnt<0>();
+    bare_barrier();
     float2 *out = stats + (((size_t)c.b * n_heads + c.hi) * nsplit + c.s) * Nt;
     for (int r0 = wave * 16; r0 < Nt; r0 += kSplitRowsPerPass) {  // uniform per wave
         f32x4_t keep[1][4];
-        split_logits<DT, NKS>(qb, r0, Nt, kbuf, lane, keep);
+        split_logits<FULL, DT, NKS>(qb, r0, Nt, row_bytes, kbuf, lane, keep);
         float m[4], l[4] = {0.f, 0.f, 0.f, 0.f};
         head_row_max<1>(keep, 1, N - key0, lane, scale_log2e, m);  // keys past N left out
         head_row_exp<1>(keep, 1, scale_log2e, m, l);
@@ -953,11 +978,11 @@ __global__ __launch_bounds__(kScoreNT) void score_split_stats_kernel(
 
 constexpr int kSplitStatU = 8;  // chunk statistics in flight per row
 
-template <int DT, int NKS>
+template <bool FULL, int DT, int NKS>
 __global__ __launch_bounds__(kScoreNT) void score_split_cols_kernel(
     const char *__restrict__ q, const char *__restrict__ k, HeadArgs heads,
     const int32_t *__restrict__ heads_dev, int head_src, const float *__restrict__ row_lse,
-    int b0, int H, int Nt, int N, int n_heads, int nsplit, float scale_log2e,
+    int b0, int H, int Nt, int N, int n_heads, int nsplit, int row_bytes, float scale_log2e,
     const float2 *__restrict__ stats, float *__restrict__ partial) {
     using S = ScoreStage<NKS>;
     __shared__ __attribute__((aligned(16))) char kbuf[S::STAGE];
@@ -966,20 +991,11 @@ __global__ __launch_bounds__(kScoreNT) void score_split_cols_kernel(
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const SplitCoord c = split_coord(heads, heads_dev, head_src, b0, H, nsplit, n_heads);
-    const char *qb = q + ((size_t)c.b * H + c.h) * Nt * S::RB;
-    const char *kb = k + ((size_t)c.b * H + c.h) * N * S::RB;
+    const char *qb = q + ((size_t)c.b * H + c.h) * Nt * row_bytes;
+    const char *kb = k + ((size_t)c.b * H + c.h) * N * row_bytes;
     const int key0 = c.s * kScoreCK;
     // the keys' loads first; the rows' statistics are merged while they fly
-    {
-#pragma unroll
-        for (int t = 0; t < S::IPW; ++t) {
-            const int pos = (wave * S::IPW + t) * 64 + lane;
-            const int r = pos / S::PPR, slot = pos % S::PPR;
-            const int row = min(key0 + r, N - 1);
-            lds_dma16(kb + (size_t)row * S::RB + ((slot ^ (r & S::SWZ)) << 4),
-                      kbuf + (wave * S::IPW + t) * 1024);
-        }
-    }
+    split_load_keys<FULL, NKS>(kb, key0, N, row_bytes, kbuf, wave, lane);
     // every row's statistics over all chunks, merged in chunk order
     const float2 *st = stats + ((size_t)c.b * n_heads + c.hi) * nsplit * Nt;
     for (int row = tid; row < Nt; row += kScoreNT) {
@@ -1004,7 +1020,7 @@ __global__ __launch_bounds__(kScoreNT) void score_split_cols_kernel(
     const int nkeys = N - key0;
     for (int r0 = wave * 16; r0 < Nt; r0 += kSplitRowsPerPass) {  // uniform per wave
         f32x4_t keep[1][4];
-        split_logits<DT, NKS>(qb, r0, Nt, kbuf, lane, keep);
+        split_logits<FULL, DT, NKS>(qb, r0, Nt, row_bytes, kbuf, lane, keep);
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
             const int row = r0 + (lane >> 4) * 4 + i;
@@ -1046,10 +1062,10 @@ struct ScoreLaunch {
     int src;
     const float *row_lse;       // [B][H][Nt] non-visual log-sum-exp (may be NULL)
     int B, H, Nt, N, n_heads;
+    int row_bytes;
     float sl2e;
     float *partial;
     hipStream_t st;
-    int hd_scale = 0;  // head width of the attention scale (0: the row width)
 };
 
 // A host head list travels as a kernel argument of bounded size: a launch
@@ -1074,8 +1090,8 @@ static hipError_t score_go(const ScoreLaunch &a) {
         dim3 grid(nrb * a.n_heads * nb);
         hipLaunchKernelGGL((score_partial_kernel<DT, NKS, MAXC>), grid, dim3(kScoreNT),
                            in_lds ? cols : 0, a.st, (const char *)a.q, (const char *)a.k, ha,
-                           a.heads_dev, a.src, a.row_lse, b0, a.H, a.Nt, a.N, a.n_heads, a.sl2e,
-                           a.partial, in_lds ? 1 : 0);
+                           a.heads_dev, a.src, a.row_lse, b0, a.H, a.Nt, a.N, a.n_heads, a.row_bytes,
+                           a.sl2e, a.partial, in_lds ? 1 : 0);
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
@@ -1175,7 +1191,7 @@ static hipError_t score_head_go(const ScoreLaunch &a) {
         const size_t kbytes = (size_t)((a.N + kScoreCK - 1) / kScoreCK) * ScoreStage<NKS>::STAGE;
         hipLaunchKernelGGL((score_head_kernel<DT, NKS>), dim3(a.n_heads * nb), dim3(kScoreNT),
                            kbytes, a.st, (const char *)a.q, (const char *)a.k, ha, a.heads_dev, a.src,
-                           a.row_lse, b0, a.H, a.Nt, a.N, a.n_heads, a.sl2e, a.partial);
+                           a.row_lse, b0, a.H, a.Nt, a.N, a.n_heads, a.row_bytes, a.sl2e, a.partial);
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
@@ -1184,7 +1200,7 @@ static hipError_t score_head_go(const ScoreLaunch &a) {
 
 // The split form: two launches per bounded head list, statistics then
 // column sums.
-template <int DT, int NKS>
+template <bool FULL, int DT, int NKS>
 static hipError_t score_split_go(const ScoreLaunch &a, float2 *stats) {
     const int nsplit = (a.N + kScoreCK - 1) / kScoreCK;
     const int per_launch = a.src == kHeadsArg ? kMaxHeadArgs / a.n_heads : a.B;
@@ -1195,39 +1211,41 @@ static hipError_t score_split_go(const ScoreLaunch &a, float2 *stats) {
             ha.h[i] = (a.src == kHeadsArg && i < nb * a.n_heads)
                           ? a.heads_host[(size_t)b0 * a.n_heads + i] : 0;
         const dim3 grid(nsplit * a.n_heads * nb);
-        hipLaunchKernelGGL((score_split_stats_kernel<DT, NKS>), grid, dim3(kScoreNT), 0, a.st,
+        hipLaunchKernelGGL((score_split_stats_kernel<FULL, DT, NKS>), grid, dim3(kScoreNT), 0, a.st,
                            (const char *)a.q, (const char *)a.k, ha, a.heads_dev, a.src, b0, a.H,
-                           a.Nt, a.N, a.n_heads, nsplit, a.sl2e, stats);
+                           a.Nt, a.N, a.n_heads, nsplit, a.row_bytes, a.sl2e, stats);
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
-        hipLaunchKernelGGL((score_split_cols_kernel<DT, NKS>), grid, dim3(kScoreNT),
+        hipLaunchKernelGGL((score_split_cols_kernel<FULL, DT, NKS>), grid, dim3(kScoreNT),
                            (size_t)a.Nt * sizeof(float2), a.st, (const char *)a.q,
                            (const char *)a.k, ha, a.heads_dev, a.src, a.row_lse, b0, a.H, a.Nt,
-                           a.N, a.n_heads, nsplit, a.sl2e, stats, a.partial);
+                           a.N, a.n_heads, nsplit, a.row_bytes, a.sl2e, stats, a.partial);
         e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
     return hipSuccess;
 }
 
-// log2(e) / sqrt(head width): the attention scale in base-2 units.
-static float scale_log2e_of(const ScoreLaunch &a, int hd) {
-    return (float)(1.4426950408889634 / sqrt((double)(a.hd_scale > 0 ? a.hd_scale : hd)));
+template <int DT>
+static hipError_t score_split_dt(int nks, const ScoreLaunch &a, float2 *stats) {
+    const bool full = a.row_bytes == nks * 64;
+    if (nks == 2)
+        return full ? score_split_go<true, DT, 2>(a, stats) : score_split_go<false, DT, 2>(a, stats);
+    return full ? score_split_go<true, DT, 4>(a, stats) : score_split_go<false, DT, 4>(a, stats);
 }
 
-static hipError_t score_any(int dt, int hd, ScoreLaunch a) {
-    const int esz = (dt == kBF16) ? 2 : 4;
-    const int nks = hd * esz / 64;
-    a.sl2e = scale_log2e_of(a, hd);
-    if (dt == kBF16) return score_dt<kBF16>(nks, a);
-    return score_dt<kF32>(nks, a);
-}
+// log2(e) / sqrt(head width): the attention scale in base-2 units.
+static float scale_log2e_of(int hd) { return (float)(1.4426950408889634 / sqrt((double)hd)); }
+
+// 64-byte windows of a head row: widths are streamed in multiples of 32
+// elements, the pieces past the row's end read as zeros.
+static int head_windows(int dt, int hd) { return (hd + 31) / 32 * 32 * ((dt == kBF16) ? 2 : 4) / 64; }
 
 // The whole-head form pays once there are enough (head, sample) pairs to
 // fill the chip (measured: from 128 pairs it is faster, below it the
 // 16-row blocks spread over more CUs and win by ~0.5 us).
 bool score_uses_head_form(int dt, int B, int H, int n_heads, int Nt, int N, int hd) {
-    const int nks = hd * ((dt == kBF16) ? 2 : 4) / 64;
+    const int nks = head_windows(dt, hd);
     return (nks == 2 || nks == 4) && H <= 256 && Nt <= kHeadMaxRows &&
            N <= kHeadMaxChunks * kScoreCK && (long long)B * n_heads >= 128;
 }
@@ -1235,7 +1253,7 @@ bool score_uses_head_form(int dt, int B, int H, int n_heads, int Nt, int N, int 
 // The split form pays for long key lists when the 16-row blocks would not
 // give every CU a workgroup (one per 16 rows, selected head and sample).
 bool score_uses_split_form(int dt, int B, int H, int n_heads, int Nt, int N, int hd) {
-    const int nks = hd * ((dt == kBF16) ? 2 : 4) / 64;
+    const int nks = head_windows(dt, hd);
     if (score_uses_head_form(dt, B, H, n_heads, Nt, N, hd)) return false;
     return (nks == 2 || nks == 4) && N > 4 * kScoreCK &&
            (long long)((Nt + 15) / 16) * n_heads * B < 256;
@@ -1250,33 +1268,29 @@ int score_parts(int dt, int B, int H, int n_heads, int Nt, int N, int hd) {
 
 hipError_t launch_score_partial(int dt, const void *q, const void *k, const int32_t *heads_host,
                                 const int32_t *heads_dev, const float *row_lse, int B, int H,
-                                int Nt, int N, int hd, int hd_scale, int n_heads, float *partial,
+                                int Nt, int N, int hd, int n_heads, float *partial,
                                 float *split_stats, hipStream_t st) {
-    ScoreLaunch a{q, k, heads_host, heads_dev, heads_dev ? kHeadsDevice : kHeadsArg,
-                  row_lse, B, H, Nt, N, n_heads, 0.f, partial, st};
-    a.hd_scale = hd_scale;
-    const int nks = hd * ((dt == kBF16) ? 2 : 4) / 64;
+    const int nks = head_windows(dt, hd);
+    const ScoreLaunch a{q, k, heads_host, heads_dev, heads_dev ? kHeadsDevice : kHeadsArg, row_lse,
+                        B, H, Nt, N, n_heads, hd * ((dt == kBF16) ? 2 : 4), scale_log2e_of(hd),
+                        partial, st};
     if (score_uses_split_form(dt, B, H, n_heads, Nt, N, hd)) {
         if (!split_stats) return hipErrorInvalidValue;
-        a.sl2e = scale_log2e_of(a, hd);
         float2 *stats = reinterpret_cast<float2 *>(split_stats);
-        if (dt == kBF16)
-            return nks == 2 ? score_split_go<kBF16, 2>(a, stats) : score_split_go<kBF16, 4>(a, stats);
-        return nks == 2 ? score_split_go<kF32, 2>(a, stats) : score_split_go<kF32, 4>(a, stats);
+        return dt == kBF16 ? score_split_dt<kBF16>(nks, a, stats) : score_split_dt<kF32>(nks, a, stats);
     }
     if (score_uses_head_form(dt, B, H, n_heads, Nt, N, hd)) {
-        a.sl2e = scale_log2e_of(a, hd);
         if (dt == kBF16) return nks == 2 ? score_head_go<kBF16, 2>(a) : score_head_go<kBF16, 4>(a);
         return nks == 2 ? score_head_go<kF32, 2>(a) : score_head_go<kF32, 4>(a);
     }
-    return score_any(dt, hd, a);
+    return dt == kBF16 ? score_dt<kBF16>(nks, a) : score_dt<kF32>(nks, a);
 }
 
 hipError_t launch_head_conf(int dt, const void *q, const void *k, const int32_t *row_mask,
                             const float *row_lse, int B, int H, int Nt, int N, int hd,
-                            int hd_scale, float *partial, hipStream_t st) {
+                            float *partial, hipStream_t st) {
     const int row_bytes = hd * ((dt == kBF16) ? 2 : 4);
-    const float sl2e = (float)(1.4426950408889634 / sqrt((double)hd_scale));
+    const float sl2e = scale_log2e_of(hd);
     const char *qc = (const char *)q, *kc = (const char *)k;
 #define PV_NKS_CASE(n)                                                                            \
     case n:                                                                                       \
@@ -1284,7 +1298,7 @@ hipError_t launch_head_conf(int dt, const void *q, const void *k, const int32_t 
                                                     row_bytes, sl2e, partial, st)                 \
                            : head_conf_go<kF32, n>(qc, kc, row_mask, row_lse, B, H, Nt, N,        \
                                                    row_bytes, sl2e, partial, st);
-    switch (row_bytes / 64) { PV_NKS_CASES }
+    switch (head_windows(dt, hd)) { PV_NKS_CASES }
 #undef PV_NKS_CASE
     return hipErrorInvalidValue;
 }
@@ -1320,8 +1334,8 @@ __global__ __launch_bounds__(kScoreNT) void gram_score_kernel(
         return;
     }
     score_partial_block<DT, NKS, MAXC, true>(q, k_full, heads, nullptr, kHeadsArg, nullptr, 0, H, Nt,
-                                             N, n_heads, scale_log2e, partial, 0, n_score, kidx,
-                                             n_src, ring);
+                                             N, n_heads, S::RB, scale_log2e, partial, 0, n_score,
+                                             kidx, n_src, ring);
 }
 
 __global__ __launch_bounds__(kScoreNT) void reduce_select_gather_kernel(ReduceJob rj, SelectJob sj,
@@ -1364,7 +1378,7 @@ hipError_t launch_gram_score(int dt, const void *q, const void *k_full, const in
     if (!gram_score_supported(dt, B, n_heads, N, hd) || N < 1) return hipErrorInvalidValue;
     HeadArgs ha;
     for (int i = 0; i < kMaxHeadArgs; ++i) ha.h[i] = i < B * n_heads ? heads_host[i] : 0;
-    const float sl2e = (float)(1.4426950408889634 / sqrt((double)hd));
+    const float sl2e = scale_log2e_of(hd);
     const dim3 grid(((Nt + 15) / 16) * n_heads * B + gj.nblocks);
     const int nch = (N + kScoreCK - 1) / kScoreCK;
 #define PV_GS_CASE(mc)                                                                            \

@@ -177,12 +177,11 @@ inline size_t score_split_stats_bytes(int B, int n_heads, int Nt, int N) {
 // row_lse [B][H][Nt] (may be NULL): log-sum-exp of each row's scaled logits
 // over the non-visual keys, which join the softmax normaliser.
 // split_stats: workspace of score_split_stats_bytes (used by the split form).
-// hd: the width of the q and k rows (a multiple of 32); hd_scale: the head
-// width of the attention scale 1 / sqrt(hd_scale) (the rows may be padded
-// with zeros past it).
+// hd: the width of the q and k rows (a multiple of 8; 16-byte pieces past a
+// row's end are read as zeros).
 hipError_t launch_score_partial(int dt, const void *q, const void *k, const int32_t *heads_host,
                                 const int32_t *heads_dev, const float *row_lse, int B, int H,
-                                int Nt, int N, int hd, int hd_scale, int n_heads, float *partial,
+                                int Nt, int N, int hd, int n_heads, float *partial,
                                 float *split_stats, hipStream_t st);
 // Head confidence of every head, per 16-row block: partial[b][h][rb].
 // row_mask as for launch_center: the rows summed into the confidence.
@@ -190,7 +189,7 @@ hipError_t launch_score_partial(int dt, const void *q, const void *k, const int3
 // taken over the visual slice of the model's softmax.
 hipError_t launch_head_conf(int dt, const void *q, const void *k, const int32_t *row_mask,
                             const float *row_lse, int B, int H, int Nt, int N, int hd,
-                            int hd_scale, float *partial, hipStream_t st);
+                            float *partial, hipStream_t st);
 hipError_t launch_conf_select(const float *partial, int B, int H, int Nt, float *conf, int n_vis,
                               int32_t *heads, hipStream_t st);
 hipError_t launch_score_select(const float *partial, int B, int nparts, int N, float inv_norm,

@@ -59,3 +59,40 @@ def test_head_conf_forms(B, H, Nt, N, hd, dt, grow):
         conf = to_host(o["conf"])
         order = np.argsort(-conf, axis=1, kind="stable")[:, :n_vis]
         assert np.array_equal(to_host(o["heads"]), np.sort(order, axis=1))
+
+
+# (B, H, Nt, N, hd, n_heads, dtype): head widths between the streamed ones, in every form of
+# the score: 16-row blocks with the logits held and with two passes, split keys, whole heads
+WIDTHS = [(2, 4, 21, 65, 8, 2, "bf16"), (2, 4, 21, 300, 136, 2, "bf16"), (1, 2, 40, 2100, 104, 2, "bf16"),
+          (1, 2, 18, 700, 248, 1, "f32"), (2, 4, 37, 321, 48, 3, "bf16"), (1, 4, 65, 257, 56, 3, "f32"),
+          (32, 8, 63, 255, 120, 4, "bf16"), (64, 4, 17, 66, 40, 2, "bf16"), (64, 4, 33, 129, 24, 2, "f32")]
+
+
+@pytest.mark.parametrize("B,H,Nt,N,hd,n_heads,dt", WIDTHS)
+def test_head_widths_read_in_place(B, H, Nt, N, hd, n_heads, dt):
+    """Q and K stand inside NaN: a piece read past the last row would spoil the sums, and one
+    read past any other row would add the next row's elements."""
+    from paper_2608_25332_amd import provip
+    print(f"[head width] B={B} H={H} Nt={Nt} N={N} hd={hd} {dt}", flush=True)
+    rng = np.random.default_rng(hd * 100 + N)
+    q = rng.standard_normal((B, H, Nt, hd), dtype=np.float32)
+    k = rng.standard_normal((B, H, N, hd), dtype=np.float32)
+    if dt == "bf16":
+        q, k = W.bf16_round(q), W.bf16_round(k)
+
+    def inside_nan(x):
+        d = to_dev(x, dt)
+        buf = torch.full((d.numel() + 1024,), float("nan"), dtype=d.dtype, device=d.device)
+        buf[512:512 + d.numel()] = d.reshape(-1)
+        return buf[512:512 + d.numel()].view(d.shape)
+
+    qd, kd = inside_nan(q), inside_nan(k)
+    heads = np.stack([rng.permutation(H)[:n_heads] for _ in range(B)]).astype(np.int32)
+    r = provip.pv_prune_head_aware(qd, kd, heads, max(1, N // 3))
+    c = provip.pv_visual_heads(qd, kd, 1)
+    torch.cuda.synchronize()
+    for b in {0, B - 1}:
+        _, v = oracle.head_aware(q[b:b + 1], k[b:b + 1], heads[b:b + 1], max(1, N // 3))
+        assert rel_err(to_host(r["score"])[b], v[0]) <= 1e-5
+        _, conf = oracle.visual_heads(q[b:b + 1], k[b:b + 1], 1)
+        assert rel_err(to_host(c["conf"])[b], conf[0]) <= 1e-5
