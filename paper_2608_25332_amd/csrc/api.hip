@@ -231,6 +231,16 @@ struct Fork {
     hipEvent_t merged_done;
 };
 
+// What the argmax and member-list launches of a dedup carry for the one-call
+// step: the score, its top-N_2 (unless split) and the compaction of K and V;
+// and what its merge carries.
+struct StepCarry {
+    pv::ScoreChain score;
+    pv::SelectJob select;  // nblocks 0: not carried
+    pv::GatherJob gather;
+    pv::MergeCsrCarry merge;
+};
+
 // The kernels of the dedup up to the top-N_1: the cosine to the anchors,
 // centring and max-pool into p, and the selection (kept, the pruned list
 // and, with slot_of, each kept token's own slot).
@@ -273,7 +283,7 @@ int dedup_impl(const void *vis, const void *anchors, int B, int Nv, int Nt, int 
                int budget, int32_t *kept, float *score, int32_t *assign, void *merged,
                void *workspace, size_t ws_bytes, void *stream, void *const *events, int n_events,
                int reps, int *n_kernels, const char **names, const Fork *fork = nullptr,
-               const int32_t *anchor_mask = nullptr) {
+               const int32_t *anchor_mask = nullptr, const StepCarry *carry = nullptr) {
     if (reps < 1) return PV_ERR_SHAPE;
     int rc = check_dedup(vis, anchors, B, Nv, Nt, d, dtype, budget, kept);
     if (rc != PV_OK) return rc;
@@ -330,7 +340,13 @@ int dedup_impl(const void *vis, const void *anchors, int B, int Nv, int Nt, int 
                                                 P.invn, P.best_val, P.best_slot, asg, sm);
                 }))
                 return PV_ERR_HIP;
-            if (P.ntn > 1) {
+            if (carry) {
+                pv::AssignJob aj{};
+                if (P.ntn > 1)
+                    aj.f = pv::FinishJob{P.best_val, P.best_slot, P.ntn, P.Mp, Nv, P.pruned, asg,
+                                         B * ((P.Mp + pv::kFinNT - 1) / pv::kFinNT)};
+                if (pv::launch_assign_score(carry->score, aj, sm) != hipSuccess) return PV_ERR_HIP;
+            } else if (P.ntn > 1) {
                 if (!tr.launch("gram_finish", [&] {
                         return pv::launch_gram_finish(P.best_val, P.best_slot, B, P.ntn, P.Mp, Nv,
                                                       P.pruned, asg, sm);
@@ -343,7 +359,13 @@ int dedup_impl(const void *vis, const void *anchors, int B, int Nv, int Nt, int 
                                                    P.Mp, P.ks_gram, P.gpart, P.gram_wide, sm);
                 }))
                 return PV_ERR_HIP;
-            if (!tr.launch("gram_reduce", [&] {
+            if (carry) {
+                pv::AssignJob aj{};
+                aj.r = pv::ReduceJob{P.gpart, B, P.Mp, budget, Nv, P.ks_gram, P.invn, P.pruned, kept,
+                                     asg, B * ((P.Mp + pv::kReduceRowsPerBlock - 1) /
+                                               pv::kReduceRowsPerBlock)};
+                if (pv::launch_assign_score(carry->score, aj, sm) != hipSuccess) return PV_ERR_HIP;
+            } else if (!tr.launch("gram_reduce", [&] {
                     return pv::launch_gram_reduce(P.gpart, B, P.Mp, budget, Nv, P.ks_gram, P.invn,
                                                   P.pruned, kept, asg, sm);
                 }))
@@ -351,13 +373,19 @@ int dedup_impl(const void *vis, const void *anchors, int B, int Nv, int Nt, int 
         }
     }
     if (merged && P.lists) {
-        if (!tr.launch("bucket", [&] {
+        if (carry) {
+            const int ng = (budget + pv::kBucketSlotsPerGroup - 1) / pv::kBucketSlotsPerGroup;
+            const pv::BucketJob bj{asg, Nv, budget, P.mcount, P.mstart, P.mlist, ng, ng * B};
+            if (pv::launch_bucket_carry(carry->score, bj, carry->select, carry->gather, sm) !=
+                hipSuccess)
+                return PV_ERR_HIP;
+        } else if (!tr.launch("bucket", [&] {
                 return pv::launch_bucket(asg, B, Nv, budget, P.mcount, P.mstart, P.mlist, sm);
             }))
             return PV_ERR_HIP;
         if (!tr.launch("merge", [&] {
                 return pv::launch_merge_csr(dt, vis, B, Nv, d, budget, P.mcount, P.mstart, P.mlist,
-                                            merged, sm);
+                                            merged, sm, carry ? &carry->merge : nullptr);
             }))
             return PV_ERR_HIP;
     } else if (merged) {
@@ -1022,6 +1050,42 @@ int pipeline_impl(const void *vis, const void *anchors, const void *q, const voi
                        pv::gram_score_supported(dt, B, n_heads, N1, hd) &&
                        !pv::score_uses_head_form(dt, B, H, n_heads, Nt, N1, hd) &&
                        !pv::score_uses_split_form(dt, B, H, n_heads, Nt, N1, hd);
+    // with member lists the score chain and the K/V compaction ride in the
+    // launches of the argmax and of the member lists
+    const int form = pv::shared_score_form(dt, B, H, n_heads, Nt, N1, hd);
+    if (!force_separate && !carry && P.Mp > 0 && form != pv::kSharedNone &&
+        pv::merge_uses_lists(B, N1, padded_d(d, esz) * esz)) {
+        const HeadPlan Hh = plan_head(ws_head, B, Nt, N1, n_heads, false);
+        const int parts = n_heads * (form == pv::kSharedRows ? Hh.nrb : 1);
+        const float inv_norm = (float)(1.0 / ((double)Nt * (double)n_heads));
+        const pv::SelectJob sj{Hh.partial, parts, N1, inv_norm, score2, N2, kept2, B, nullptr};
+        StepCarry sc{pv::ScoreChain{form, dt, q, k_full, heads, B, H, Nt, N1, Nv, hd, n_heads, kept1,
+                                    Hh.partial, Hh.stats},
+                     sj, pv::GatherJob{ga1, kept1, N1, ga1.bstart[ga1.n]}, pv::MergeCsrCarry{}};
+        // 16-row blocks: the top-N_2 beside the member lists, so that the merge
+        // can write the hidden rows of the N_2 kept and carry their K and V.
+        // Split: the top-N_2 beside the merge, on the merge's workgroups of 256
+        // threads up to kMergeSelCols columns each.
+        const bool rows = form == pv::kSharedRows;
+        const bool in_merge = !rows && N1 <= pv::kMergeSelCols * 256;
+        if (rows) {
+            sc.select.slot_of = slot_of2;
+            sc.merge.mc = pv::MergeCarry{slot_of2, (char *)hidden2, N2,
+                                         pv::GatherJob{ga2kv, kept2, N2, ga2kv.bstart[ga2kv.n]}};
+        } else {
+            sc.select.nblocks = 0;
+            if (in_merge) sc.merge.sj = sj;
+        }
+        rc = dedup_impl(vis, anchors, B, Nv, Nt, d, dtype, N1, kept1, score1, assign, merged, wsa,
+                        sz.dedup, stream, nullptr, 0, 1, nullptr, nullptr, nullptr, nullptr, &sc);
+        if (rc != PV_OK) return rc;
+        if (rows) return PV_OK;
+        if (!in_merge && pv::launch_score_select(Hh.partial, B, parts, N1, inv_norm, score2, N2,
+                                                 kept2, st) != hipSuccess)
+            return PV_ERR_HIP;
+        if (pv::launch_gather(ga2, kept2, B, N2, st) != hipSuccess) return PV_ERR_HIP;
+        return PV_OK;
+    }
     if (!carry) {
         rc = dedup_impl(vis, anchors, B, Nv, Nt, d, dtype, N1, kept1, score1, assign, merged, wsa,
                         sz.dedup, stream, nullptr, 0, 1, nullptr, nullptr);

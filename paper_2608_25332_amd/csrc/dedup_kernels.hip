@@ -669,42 +669,9 @@ __global__ __launch_bounds__(NT) void select_kernel(const float *__restrict__ p,
 // Nearest centroid: best (cosine, slot) of every pruned row, with the total
 // order of `better` (higher cosine, then lower slot).
 // ----------------------------------------------------------------------------
-// gram_finish: grid (ceil(Mp / 256), B).  Best column tile of every pruned
-// row, combined in tile order with the total order above.  The candidates of
-// kFinU tiles are loaded at once (a loop that compares each one as it arrives
-// waits for every load in turn); past the last tile the last one repeats,
-// which cannot change a maximum under a total order.
-constexpr int kFinNT = 256;
-constexpr int kFinU = 16;
-
-__global__ __launch_bounds__(kFinNT) void gram_finish_kernel(const float *__restrict__ best_val,
-                                                             const int32_t *__restrict__ best_slot,
-                                                             int ntn, int Mp, int Nv,
-                                                             const int32_t *__restrict__ pruned,
-                                                             int32_t *__restrict__ assign) {
-    const int b = blockIdx.y;
-    const int m = blockIdx.x * kFinNT + threadIdx.x;
-    if (m >= Mp) return;
-    const int tok = pruned[(size_t)b * Mp + m];
-    float bv = -INFINITY;
-    int bs = 0x7FFFFFFF;
-    for (int t0 = 0; t0 < ntn; t0 += kFinU) {
-        float v[kFinU];
-        int s[kFinU];
-#pragma unroll
-        for (int u = 0; u < kFinU; ++u) {
-            const size_t at = ((size_t)b * ntn + min(t0 + u, ntn - 1)) * Mp + m;
-            v[u] = best_val[at];
-            s[u] = best_slot[at];
-        }
-#pragma unroll
-        for (int u = 0; u < kFinU; ++u)
-            if (better(v[u], s[u], bv, bs)) {
-                bv = v[u];
-                bs = s[u];
-            }
-    }
-    assign[(size_t)b * Nv + tok] = bs;
+// gram_finish: grid (ceil(Mp / 256), B), one thread per pruned row.
+__global__ __launch_bounds__(kFinNT) void gram_finish_kernel(FinishJob j) {
+    gram_finish_row(j, blockIdx.x * kFinNT + threadIdx.x, blockIdx.y);
 }
 
 template <int DT, int NS, int BM, int BN>
@@ -903,7 +870,7 @@ __global__ __launch_bounds__(kMergeNT) void merge_kernel(const char *__restrict_
     // the grid: workgroup (x, N1 + r, 0) runs its block r * gridDim.x + x
     if (s >= N1) {
         const int g = (s - N1) * (int)gridDim.x + bx;
-        if (b == 0 && g < mc.gj.nblocks) gather_block(mc.gj.ga, mc.gj.idx, mc.gj.k, g);
+        if (b == 0 && g < mc.gj.nblocks) gather_block(mc.gj.ga, mc.gj.idx, mc.gj.k, g, threadIdx.x);
         return;
     }
     // the slot's row among the N_2 kept, when the head-aware top-N_2 kept it
@@ -948,118 +915,12 @@ __global__ __launch_bounds__(kMergeNT) void merge_kernel(const char *__restrict_
                          merged + ((size_t)b * N1 + s) * d_bytes, out2);
 }
 
-// ----------------------------------------------------------------------------
-// Member lists for large inputs, where every merge workgroup scanning the whole
-// assignment would cost more than the rows it adds.
-//
-// bucket: grid (ceil(N1 / 256), B), 512 or 1024 threads.  Lists the members of the
-// 256 slots [256 g, 256 g + 256) in ascending token order: mcount[b][s],
-// mstart[b][s] (offset in the sample's list region) and the lists themselves
-// in mlist[b][g * Nv ...].  The assignment is staged in LDS; the waves take
-// consecutive token segments and sweep them twice, 64 tokens per
-// step: per-slot counts (integer atomics on the wave's counters in LDS), then
-// placement at offsets that keep the segments in order.  In the placement the
-// lanes of a step that hold the same slot are found with one ballot per bit
-// of the slot offset (the lanes whose offsets agree on every bit), so a step
-// costs the same whatever the number of distinct slots in it; each lane takes
-// the next places in lane order and the lowest such lane advances the wave's
-// counter of that slot.
-// ----------------------------------------------------------------------------
-constexpr int kBucketBits = 8;
-constexpr int kBucketSlots = 1 << kBucketBits;
-static_assert(kBucketSlots == kBucketSlotsPerGroup, "slots per bucket group");
-// threads: 512, or 1024 from kBucketWideNv tokens (measured: 16 waves sweep
-// the longer assignments faster, 8 cost less on short ones)
-constexpr int kBucketWideNv = 2048;
-
-// Lanes whose value v agrees with this lane's on the low kBucketBits bits,
-// among the lanes in `act`.
-__device__ __forceinline__ unsigned long long same_slot_lanes(int v, unsigned long long act) {
-    unsigned long long same = act;
-#pragma unroll
-    for (int bit = 0; bit < kBucketBits; ++bit) {
-        const bool on = (v >> bit) & 1;
-        const unsigned long long ones = __ballot(on);
-        same &= on ? ones : ~ones;
-    }
-    return same;
-}
-
-template <int kBucketNT>
-__global__ __launch_bounds__(kBucketNT) void bucket_kernel(const int32_t *__restrict__ assign,
-                                                           int Nv, int N1,
-                                                           int32_t *__restrict__ mcount,
-                                                           int32_t *__restrict__ mstart,
-                                                           int32_t *__restrict__ mlist) {
-    extern __shared__ int32_t sa[];  // [Nv] the sample's assignment
-    constexpr int kBucketW = kBucketNT / 64;
-    __shared__ int cur[kBucketW][kBucketSlots];
-    __shared__ int wsum[kBucketW];
-    const int g = blockIdx.x, b = blockIdx.y, tid = threadIdx.x, lane = tid & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int ngroups = gridDim.x;
-    const int s0 = g * kBucketSlots;
-    const int32_t *as = assign + (size_t)b * Nv;
-    int32_t *lst = mlist + ((size_t)b * ngroups + g) * Nv;
-    const unsigned long long lt = (1ull << lane) - 1ull;
-
-    for (int e = lane; e < kBucketSlots; e += 64) cur[wave][e] = 0;
-    // stage: eight loads per thread in flight per round
-    for (int j0 = 0; j0 < Nv; j0 += kBucketNT * 8) {
-        int v[8];
-#pragma unroll
-        for (int u = 0; u < 8; ++u) v[u] = as[min(j0 + u * kBucketNT + tid, Nv - 1)];
-#pragma unroll
-        for (int u = 0; u < 8; ++u)
-            if (j0 + u * kBucketNT + tid < Nv) sa[j0 + u * kBucketNT + tid] = v[u];
-    }
-    __syncthreads();
-    // this wave's token segment [t0, t1), whole 64-token steps
-    const int seg = ((Nv + kBucketW - 1) / kBucketW + 63) / 64 * 64;
-    const int t0 = min(wave * seg, Nv), t1 = min(t0 + seg, Nv);
-    int *wc = cur[wave];
-
-    // pass 1: this wave's count of every slot (integer atomics in LDS: the
-    // counts do not depend on their order)
-    for (int c0 = t0; c0 < t1; c0 += 64) {
-        const int j = c0 + lane;
-        const int v = (j < t1) ? sa[j] - s0 : -1;
-        if (v >= 0 && v < kBucketSlots) atomicAdd(&wc[v], 1);
-    }
-    __syncthreads();
-    // slot totals and offsets; then each wave's first position per slot
-    int tot = 0;
-    if (tid < kBucketSlots) {
-#pragma unroll
-        for (int w = 0; w < kBucketW; ++w) tot += cur[w][tid];
-    }
-    int all;
-    const int base = block_excl_scan<kBucketNT>(tot, wsum, &all);
-    if (tid < kBucketSlots) {
-        if (s0 + tid < N1) {
-            mcount[(size_t)b * N1 + s0 + tid] = tot;
-            mstart[(size_t)b * N1 + s0 + tid] = g * Nv + base;
-        }
-        int run = base;
-#pragma unroll
-        for (int w = 0; w < kBucketW; ++w) {
-            const int c = cur[w][tid];
-            cur[w][tid] = run;
-            run += c;
-        }
-    }
-    __syncthreads();
-    // pass 2: placement in token order
-    for (int c0 = t0; c0 < t1; c0 += 64) {
-        const int j = c0 + lane;
-        const int v = (j < t1) ? sa[j] - s0 : -1;
-        const bool rel = v >= 0 && v < kBucketSlots;
-        const unsigned long long same = same_slot_lanes(v, __ballot(rel));
-        if (rel) {
-            lst[wc[v] + __popcll(same & lt)] = j;
-            if ((same & lt) == 0ull) wc[v] += __popcll(same);
-        }
-    }
+// bucket: grid (ceil(N1 / 256), B), the member lists of one sample's slots
+// (bucket_block).
+template <int NT>
+__global__ __launch_bounds__(NT) void bucket_kernel(BucketJob bj) {
+    extern __shared__ int32_t sa[];  // [Nv]
+    bucket_block<NT>(bj, blockIdx.x, blockIdx.y, sa);
 }
 
 // merge_csr: as merge, with the member list read from the bucket output and
@@ -1075,15 +936,47 @@ __global__ __launch_bounds__(kBucketNT) void bucket_kernel(const int32_t *__rest
 // saves.)
 constexpr int kMergeFew = 8;
 constexpr int kMergeHeavyU = 4;
-template <int DT, int CPL>
+//
+// CARRY (the one-call step): the first `front` rows of slots of sample 0's
+// plane are the workgroups of the top-N_2 (the longest ones, so first in the
+// grid; the merge's sums and theirs share the LDS), the rows past N1 those of
+// the K/V compaction, and a slot kept by the top-N_2 also writes its row there.
+template <int DT, int CPL, bool CARRY>
 __global__ __launch_bounds__(kMergeNT) void merge_csr_kernel(
     const char *__restrict__ vis, int Nv, int d_bytes, const int32_t *__restrict__ mcount,
     const int32_t *__restrict__ mstart, const int32_t *__restrict__ mlist, int N1, int ngroups,
-    char *__restrict__ merged) {
+    char *__restrict__ merged, int front, MergeCsrCarry carry) {
     constexpr int EPC = (DT == kBF16) ? 8 : 4;
     constexpr int NW = kMergeNT / 64;
-    __shared__ float part[NW][CPL][EPC][64];
-    const int s = blockIdx.y, b = blockIdx.z;
+    struct SelectLds {
+        TopkSmem topk;
+        float v[kMergeSelCols * kMergeNT];
+    };
+    constexpr size_t kPartBytes = sizeof(float) * NW * CPL * EPC * 64;
+    constexpr size_t kLds = CARRY && sizeof(SelectLds) > kPartBytes ? sizeof(SelectLds) : kPartBytes;
+    __shared__ __attribute__((aligned(16))) char lds[kLds];
+    auto part = reinterpret_cast<float(*)[CPL][EPC][64]>(lds);
+    const int s = (int)blockIdx.y - (CARRY ? front : 0), b = blockIdx.z;
+    char *out2 = nullptr;
+    if constexpr (CARRY) {
+        if (s < 0) {
+            const int blk = (int)blockIdx.y * (int)gridDim.x + (int)blockIdx.x;
+            SelectLds &sl = *reinterpret_cast<SelectLds *>(lds);
+            if (b == 0 && blk < carry.sj.nblocks)
+                score_select_block<kMergeNT, kMergeSelCols>(carry.sj, blk, sl.topk, sl.v);
+            return;
+        }
+        if (s >= N1) {
+            const int g = (s - N1) * (int)gridDim.x + (int)blockIdx.x;
+            const GatherJob &gj = carry.mc.gj;
+            if (b == 0 && g < gj.nblocks) gather_block(gj.ga, gj.idx, gj.k, g, threadIdx.x);
+            return;
+        }
+        if (carry.mc.slot_of2) {
+            const int pos = carry.mc.slot_of2[(size_t)b * N1 + s];
+            if (pos >= 0) out2 = carry.mc.hidden2 + ((size_t)b * carry.mc.N2 + pos) * d_bytes;
+        }
+    }
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int nchunk = d_bytes >> 4;
@@ -1158,6 +1051,7 @@ __global__ __launch_bounds__(kMergeNT) void merge_csr_kernel(
                 for (int q = 0; q < 4; ++q) w4[q] = __float_as_uint(acc[t][q] / cntf);
             }
             st16(out + (size_t)cc[t] * 16, uint4{w4[0], w4[1], w4[2], w4[3]});
+            if (CARRY && out2) st16(out2 + (size_t)cc[t] * 16, uint4{w4[0], w4[1], w4[2], w4[3]});
         }
     }
 }
@@ -1502,20 +1396,18 @@ hipError_t launch_gram_finish(const float *best_val, const int32_t *best_slot, i
                               int Mp, int Nv, const int32_t *pruned, int32_t *assign,
                               hipStream_t st) {
     dim3 grid((Mp + kFinNT - 1) / kFinNT, B);
-    hipLaunchKernelGGL(gram_finish_kernel, grid, dim3(kFinNT), 0, st, best_val, best_slot, ntn, Mp,
-                       Nv, pruned, assign);
+    const FinishJob j{best_val, best_slot, ntn, Mp, Nv, pruned, assign, 0};
+    hipLaunchKernelGGL(gram_finish_kernel, grid, dim3(kFinNT), 0, st, j);
     return hipGetLastError();
 }
 
 hipError_t launch_bucket(const int32_t *assign, int B, int Nv, int N1, int32_t *mcount,
                          int32_t *mstart, int32_t *mlist, hipStream_t st) {
     const dim3 grid((N1 + kBucketSlots - 1) / kBucketSlots, B);
-    if (Nv >= kBucketWideNv)
-        hipLaunchKernelGGL(bucket_kernel<1024>, grid, dim3(1024), (size_t)Nv * sizeof(int32_t), st,
-                           assign, Nv, N1, mcount, mstart, mlist);
-    else
-        hipLaunchKernelGGL(bucket_kernel<512>, grid, dim3(512), (size_t)Nv * sizeof(int32_t), st,
-                           assign, Nv, N1, mcount, mstart, mlist);
+    const BucketJob bj{assign, Nv, N1, mcount, mstart, mlist, (int)grid.x, (int)grid.x * B};
+    const size_t lds = (size_t)Nv * sizeof(int32_t);
+    if (Nv >= kBucketWideNv) hipLaunchKernelGGL(bucket_kernel<1024>, grid, dim3(1024), lds, st, bj);
+    else hipLaunchKernelGGL(bucket_kernel<512>, grid, dim3(512), lds, st, bj);
     return hipGetLastError();
 }
 
@@ -1523,18 +1415,27 @@ constexpr int kMergeCPL = 2;  // chunks per lane of merge_csr
 
 hipError_t launch_merge_csr(int dt, const void *vis, int B, int Nv, int d, int N1,
                             const int32_t *mcount, const int32_t *mstart, const int32_t *mlist,
-                            void *merged, hipStream_t st) {
+                            void *merged, hipStream_t st, const MergeCsrCarry *with) {
     const int d_bytes = d * ((dt == kBF16) ? 2 : 4);
     const int ngroups = (N1 + kBucketSlots - 1) / kBucketSlots;
-    const dim3 grid((d_bytes / 16 + 64 * kMergeCPL - 1) / (64 * kMergeCPL), N1, B);
-    if (dt == kBF16)
-        hipLaunchKernelGGL((merge_csr_kernel<kBF16, kMergeCPL>), grid, dim3(kMergeNT), 0, st,
-                           (const char *)vis, Nv, d_bytes, mcount, mstart, mlist, N1, ngroups,
-                           (char *)merged);
-    else
-        hipLaunchKernelGGL((merge_csr_kernel<kF32, kMergeCPL>), grid, dim3(kMergeNT), 0, st,
-                           (const char *)vis, Nv, d_bytes, mcount, mstart, mlist, N1, ngroups,
-                           (char *)merged);
+    const int gx = (d_bytes / 16 + 64 * kMergeCPL - 1) / (64 * kMergeCPL);
+    MergeCsrCarry c{};
+    if (with) c = *with;
+    if (c.sj.nblocks > 0 && c.sj.N > kMergeSelCols * kMergeNT) return hipErrorInvalidValue;
+    const int front = (c.sj.nblocks + gx - 1) / gx, back = (c.mc.gj.nblocks + gx - 1) / gx;
+    const dim3 grid(gx, front + N1 + back, B);
+#define PV_MC_CASE(dtv, cy)                                                                       \
+    hipLaunchKernelGGL((merge_csr_kernel<dtv, kMergeCPL, cy>), grid, dim3(kMergeNT), 0, st,       \
+                       (const char *)vis, Nv, d_bytes, mcount, mstart, mlist, N1, ngroups,        \
+                       (char *)merged, front, c)
+    if (dt == kBF16) {
+        if (with) PV_MC_CASE(kBF16, true);
+        else PV_MC_CASE(kBF16, false);
+    } else {
+        if (with) PV_MC_CASE(kF32, true);
+        else PV_MC_CASE(kF32, false);
+    }
+#undef PV_MC_CASE
     return hipGetLastError();
 }
 

@@ -12,7 +12,7 @@ namespace pv {
 
 __global__ __launch_bounds__(kGatherNT) void gather_kernel(GatherArgs ga,
                                                            const int32_t *__restrict__ idx, int k) {
-    gather_block(ga, idx, k, blockIdx.x);
+    gather_block(ga, idx, k, blockIdx.x, threadIdx.x);
 }
 
 hipError_t launch_gather(const GatherArgs &ga, const int32_t *idx, int B, int k, hipStream_t st) {

@@ -91,9 +91,9 @@ enum HeadSource { kHeadsArg = 0, kHeadsDevice = 1 };
 // One score workgroup; n_score: workgroups of the launch that score.
 // IDX: key j of the head is row kidx[b][j] of k ([B][H][n_src][hd], the keys
 // of every token; kidx[b] holds N indices), so the score needs no compacted
-// copy of the kept keys; the ring is then `ext_ring` (S::NS * S::STAGE bytes
+// copy of the kept keys; the ring (NS chunks) is then `ext_ring` (NS * S::STAGE bytes
 // of LDS, shared with the other workgroups of the launch).  N <= 256.
-template <int DT, int NKS, int MAXC, bool IDX = false>
+template <int DT, int NKS, int MAXC, bool IDX = false, int NS = ScoreStage<NKS>::NS>
 __device__ __forceinline__ void score_partial_block(
     const char *__restrict__ q, const char *__restrict__ k, const HeadArgs &heads,
     const int32_t *__restrict__ heads_dev, int head_src, const float *__restrict__ row_lse, int b0,
@@ -103,7 +103,7 @@ __device__ __forceinline__ void score_partial_block(
     static_assert(!IDX || (MAXC > 0 && MAXC * kScoreCK <= 256),
                   "indexed keys: one pass, at most 256 keys");
     using S = ScoreStage<NKS>;
-    __shared__ __attribute__((aligned(16))) char own_ring[IDX ? 16 : S::NS * S::STAGE];
+    __shared__ __attribute__((aligned(16))) char own_ring[IDX ? 16 : NS * S::STAGE];
     __shared__ int32_t krow[IDX ? 256 : 1];  // IDX: the source row of every key
     char *const ring = IDX ? ext_ring : own_ring;
     __shared__ __attribute__((aligned(16))) char qrows[16 * S::RB];
@@ -143,7 +143,7 @@ __device__ __forceinline__ void score_partial_block(
         sbyte[t] = (slot ^ (r & S::SWZ)) << 4;
     }
     auto issue = [&](int ch) {
-        char *dst = ring + (ch % S::NS) * S::STAGE + wave * S::IPW * 1024;
+        char *dst = ring + (ch % NS) * S::STAGE + wave * S::IPW * 1024;
 #pragma unroll
         for (int t = 0; t < S::IPW; ++t) {
             const int key = min(ch * kScoreCK + srow[t], N - 1);  // past the end: last key
@@ -176,7 +176,7 @@ __device__ __forceinline__ void score_partial_block(
     // refilled by a later pass.
     auto start = [&]() {
 #pragma unroll
-        for (int pp = 0; pp < S::NS; ++pp)
+        for (int pp = 0; pp < NS; ++pp)
             if (pp < nch) issue(pp);
     };
     // the query fragments, once the first wait has covered their loads
@@ -191,16 +191,16 @@ __device__ __forceinline__ void score_partial_block(
     };
     auto chunk = [&](int ch, bool drain) -> f32x4_t {
         // chunks issued so far, and how many of them are younger than ch
-        const int issued = ch == 0 ? min(S::NS, nch) : min(ch + S::NS - 1, nch);
+        const int issued = ch == 0 ? min(NS, nch) : min(ch + NS - 1, nch);
         const int younger = drain ? 0 : issued - 1 - ch;
-        static_assert(S::NS <= 3, "at most two chunks younger than the one waited for");
+        static_assert(NS <= 3, "at most two chunks younger than the one waited for");
         if (younger >= 2) wait_vmcnt<S::IPW * 2>();
         else if (younger == 1) wait_vmcnt<S::IPW>();
         else wait_vmcnt<0>();
         bare_barrier();  // chunk ch is in LDS; chunk ch - 1 has been read
-        if (ch >= 1 && ch + S::NS - 1 < nch) issue(ch + S::NS - 1);
+        if (ch >= 1 && ch + NS - 1 < nch) issue(ch + NS - 1);
         if (ch == 0) read_q();
-        const char *sp = ring + (ch % S::NS) * S::STAGE;
+        const char *sp = ring + (ch % NS) * S::STAGE;
         const int r = wave * 16 + (lane & 15);
         uint4 kf[NKS];
 #pragma unroll
@@ -899,9 +899,9 @@ struct SplitCoord {
 __device__ __forceinline__ SplitCoord split_coord(const HeadArgs &heads,
                                                   const int32_t *__restrict__ heads_dev,
                                                   int head_src, int b0, int H, int nsplit,
-                                                  int n_heads) {
+                                                  int n_heads, int blk, int total) {
     SplitCoord c;
-    const int L = xcd_tile(blockIdx.x, gridDim.x);
+    const int L = xcd_tile(blk, total);
     c.s = L % nsplit;
     c.hi = (L / nsplit) % n_heads;
     const int bl = L / (nsplit * n_heads);
@@ -912,17 +912,19 @@ __device__ __forceinline__ SplitCoord split_coord(const HeadArgs &heads,
 }
 
 // The loads of the chunk's (at most 64) keys into LDS (rows past N repeat the
-// last key).
-template <bool FULL, int NKS>
+// last key).  IDX: key j is row kidx[j] of kb's n_src rows, else row j.
+template <bool FULL, bool IDX, int NKS>
 __device__ __forceinline__ void split_load_keys(const char *kb, int key0, int N, int row_bytes,
-                                                char *kbuf, int wave, int lane) {
+                                                const int32_t *kidx, int n_src, char *kbuf,
+                                                int wave, int lane) {
     using S = ScoreStage<NKS>;
 #pragma unroll
     for (int t = 0; t < S::IPW; ++t) {
         const int pos = (wave * S::IPW + t) * 64 + lane;
         const int r = pos / S::PPR, slot = pos % S::PPR;
-        lds_dma16(row_at<FULL, S::RB>(kb, min(key0 + r, N - 1), row_bytes,
-                                      (slot ^ (r & S::SWZ)) << 4),
+        int row = min(key0 + r, N - 1);
+        if constexpr (IDX) row = min(max(kidx[row], 0), n_src - 1);
+        lds_dma16(row_at<FULL, S::RB>(kb, row, row_bytes, (slot ^ (r & S::SWZ)) << 4),
                   kbuf + (wave * S::IPW + t) * 1024);
     }
 }
@@ -941,29 +943,55 @@ __device__ __forceinline__ void split_logits(const char *qb, int r0, int Nt, int
     head_chunk_logits<DT, NKS>(kbuf, qf, lane, keep[0]);
 }
 
-template <bool FULL, int DT, int NKS>
-__global__ __launch_bounds__(kScoreNT) void score_split_stats_kernel(
-    const char *__restrict__ q, const char *__restrict__ k, HeadArgs heads,
-    const int32_t *__restrict__ heads_dev, int head_src, int b0, int H, int Nt, int N,
-    int n_heads, int nsplit, int row_bytes, float scale_log2e, float2 *__restrict__ stats) {
+// What both passes read.  kidx: [B][N] rows of k ([B][H][n_src][hd], the keys
+// of every token) that are the keys, or NULL: k holds the N keys themselves.
+struct SplitScore {
+    const char *q, *k;
+    const int32_t *heads_dev;
+    int head_src;
+    const float *row_lse;
+    int b0, H, Nt, N, n_heads, nsplit, row_bytes;
+    const int32_t *kidx;
+    int n_src;
+    float scale_log2e;
+    float2 *stats;
+    float *partial;
+    int nblocks;  // workgroups (nsplit * n_heads * samples)
+
+    __device__ __forceinline__ const char *queries(const SplitCoord &c) const {
+        return q + ((size_t)c.b * H + c.h) * Nt * row_bytes;
+    }
+    template <bool IDX>
+    __device__ __forceinline__ const char *keys(const SplitCoord &c) const {
+        return k + ((size_t)c.b * H + c.h) * (IDX ? n_src : N) * row_bytes;
+    }
+    template <bool IDX>
+    __device__ __forceinline__ const int32_t *rows(const SplitCoord &c) const {
+        return IDX ? kidx + (size_t)c.b * N : nullptr;
+    }
+};
+
+template <bool FULL, bool IDX, int DT, int NKS>
+__device__ __forceinline__ void split_stats_block(const SplitScore &a, const HeadArgs &heads,
+                                                  int blk) {
     using S = ScoreStage<NKS>;
     __shared__ __attribute__((aligned(16))) char kbuf[S::STAGE];
-    const int lane = threadIdx.x & 63;
+    const int lane = threadIdx.x & 63, N = a.N, Nt = a.Nt;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const SplitCoord c = split_coord(heads, heads_dev, head_src, b0, H, nsplit, n_heads);
-    const char *qb = q + ((size_t)c.b * H + c.h) * Nt * row_bytes;
-    const char *kb = k + ((size_t)c.b * H + c.h) * N * row_bytes;
+    const SplitCoord c = split_coord(heads, a.heads_dev, a.head_src, a.b0, a.H, a.nsplit, a.n_heads,
+                                     blk, a.nblocks);
+    const char *qb = a.queries(c);
     const int key0 = c.s * kScoreCK;
-    split_load_keys<FULL, NKS>(kb, key0, N, row_bytes, kbuf, wave, lane);
+    split_load_keys<FULL, IDX, NKS>(a.template keys<IDX>(c), key0, N, a.row_bytes, a.template rows<IDX>(c), a.n_src, kbuf, wave, lane);
     wait_vmcnt<0>();
     bare_barrier();
-    float2 *out = stats + (((size_t)c.b * n_heads + c.hi) * nsplit + c.s) * Nt;
+    float2 *out = a.stats + (((size_t)c.b * a.n_heads + c.hi) * a.nsplit + c.s) * Nt;
     for (int r0 = wave * 16; r0 < Nt; r0 += kSplitRowsPerPass) {  // uniform per wave
         f32x4_t keep[1][4];
-        split_logits<FULL, DT, NKS>(qb, r0, Nt, row_bytes, kbuf, lane, keep);
+        split_logits<FULL, DT, NKS>(qb, r0, Nt, a.row_bytes, kbuf, lane, keep);
         float m[4], l[4] = {0.f, 0.f, 0.f, 0.f};
-        head_row_max<1>(keep, 1, N - key0, lane, scale_log2e, m);  // keys past N left out
-        head_row_exp<1>(keep, 1, scale_log2e, m, l);
+        head_row_max<1>(keep, 1, N - key0, lane, a.scale_log2e, m);  // keys past N left out
+        head_row_exp<1>(keep, 1, a.scale_log2e, m, l);
 #pragma unroll
         for (int i = 0; i < 4; ++i) l[i] = row16_sum(l[i]);
         if ((lane & 15) == 0) {
@@ -976,29 +1004,33 @@ __global__ __launch_bounds__(kScoreNT) void score_split_stats_kernel(
     }
 }
 
+template <bool FULL, bool IDX, int DT, int NKS>
+__global__ __launch_bounds__(kScoreNT) void score_split_stats_kernel(SplitScore a, HeadArgs heads) {
+    split_stats_block<FULL, IDX, DT, NKS>(a, heads, blockIdx.x);
+}
+
 constexpr int kSplitStatU = 8;  // chunk statistics in flight per row
 
-template <bool FULL, int DT, int NKS>
-__global__ __launch_bounds__(kScoreNT) void score_split_cols_kernel(
-    const char *__restrict__ q, const char *__restrict__ k, HeadArgs heads,
-    const int32_t *__restrict__ heads_dev, int head_src, const float *__restrict__ row_lse,
-    int b0, int H, int Nt, int N, int n_heads, int nsplit, int row_bytes, float scale_log2e,
-    const float2 *__restrict__ stats, float *__restrict__ partial) {
+// rowstat: LDS, [Nt] of (row maximum, 1 / normaliser).  Of NT threads the first
+// four waves form the products (the sums keep one order whatever NT is).
+template <bool FULL, bool IDX, int DT, int NKS, int NT>
+__device__ __forceinline__ void split_cols_block(const SplitScore &a, const HeadArgs &heads,
+                                                 int blk, float2 *rowstat) {
     using S = ScoreStage<NKS>;
     __shared__ __attribute__((aligned(16))) char kbuf[S::STAGE];
     __shared__ float colpart[4][kScoreCK];
-    extern __shared__ float2 rowstat[];  // [Nt]: (row maximum, 1 / normaliser)
-    const int tid = threadIdx.x, lane = tid & 63;
+    const int tid = threadIdx.x, lane = tid & 63, N = a.N, Nt = a.Nt, nsplit = a.nsplit;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const SplitCoord c = split_coord(heads, heads_dev, head_src, b0, H, nsplit, n_heads);
-    const char *qb = q + ((size_t)c.b * H + c.h) * Nt * row_bytes;
-    const char *kb = k + ((size_t)c.b * H + c.h) * N * row_bytes;
+    const SplitCoord c = split_coord(heads, a.heads_dev, a.head_src, a.b0, a.H, nsplit, a.n_heads,
+                                     blk, a.nblocks);
+    const char *qb = a.queries(c);
     const int key0 = c.s * kScoreCK;
     // the keys' loads first; the rows' statistics are merged while they fly
-    split_load_keys<FULL, NKS>(kb, key0, N, row_bytes, kbuf, wave, lane);
+    if (NT == kScoreNT || wave < 4)
+        split_load_keys<FULL, IDX, NKS>(a.template keys<IDX>(c), key0, N, a.row_bytes, a.template rows<IDX>(c), a.n_src, kbuf, wave, lane);
     // every row's statistics over all chunks, merged in chunk order
-    const float2 *st = stats + ((size_t)c.b * n_heads + c.hi) * nsplit * Nt;
-    for (int row = tid; row < Nt; row += kScoreNT) {
+    const float2 *st = a.stats + ((size_t)c.b * a.n_heads + c.hi) * nsplit * Nt;
+    for (int row = tid; row < Nt; row += NT) {
         float mm = -INFINITY, ll = 0.f;
         for (int s0 = 0; s0 < nsplit; s0 += kSplitStatU) {
             float2 v[kSplitStatU];
@@ -1011,16 +1043,17 @@ __global__ __launch_bounds__(kScoreNT) void score_split_cols_kernel(
         }
         // the model's row also runs over the non-visual keys: their
         // log-sum-exp (natural log, scaled logits) joins the normaliser
-        if (row_lse) lse_merge(mm, ll, row_lse[((size_t)c.b * H + c.h) * Nt + row] * 1.4426950408889634f, 1.f);
+        if (a.row_lse)
+            lse_merge(mm, ll, a.row_lse[((size_t)c.b * a.H + c.h) * Nt + row] * 1.4426950408889634f, 1.f);
         rowstat[row] = make_float2(mm, 1.0f / ll);
     }
     wait_vmcnt<0>();
     __syncthreads();  // the keys and every row's statistics are in LDS
     float cs[4] = {0.f, 0.f, 0.f, 0.f};
     const int nkeys = N - key0;
-    for (int r0 = wave * 16; r0 < Nt; r0 += kSplitRowsPerPass) {  // uniform per wave
+    for (int r0 = wave * 16; (NT == kScoreNT || wave < 4) && r0 < Nt; r0 += kSplitRowsPerPass) {  // uniform per wave
         f32x4_t keep[1][4];
-        split_logits<FULL, DT, NKS>(qb, r0, Nt, row_bytes, kbuf, lane, keep);
+        split_logits<FULL, DT, NKS>(qb, r0, Nt, a.row_bytes, kbuf, lane, keep);
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
             const int row = r0 + (lane >> 4) * 4 + i;
@@ -1029,7 +1062,7 @@ __global__ __launch_bounds__(kScoreNT) void score_split_cols_kernel(
 #pragma unroll
             for (int kq = 0; kq < 4; ++kq) {
                 const bool col_ok = kq * 16 + (lane & 15) < nkeys;
-                const float e = exp2_hw(fmaf(keep[0][kq][i], scale_log2e, -rs.x));
+                const float e = exp2_hw(fmaf(keep[0][kq][i], a.scale_log2e, -rs.x));
                 cs[kq] += col_ok ? e * il : 0.f;
             }
         }
@@ -1040,17 +1073,25 @@ __global__ __launch_bounds__(kScoreNT) void score_split_cols_kernel(
         float v = cs[kq];
         v += __shfl_xor(v, 16, 64);
         v += __shfl_xor(v, 32, 64);
-        if (lane < 16) colpart[wave][kq * 16 + lane] = v;
+        if (lane < 16 && (NT == kScoreNT || wave < 4)) colpart[wave][kq * 16 + lane] = v;
     }
     __syncthreads();
     if (tid < kScoreCK && tid < nkeys)
-        partial[((size_t)c.b * n_heads + c.hi) * N + key0 + tid] =
+        a.partial[((size_t)c.b * a.n_heads + c.hi) * N + key0 + tid] =
             ((colpart[0][tid] + colpart[1][tid]) + colpart[2][tid]) + colpart[3][tid];
+}
+
+template <bool FULL, bool IDX, int DT, int NKS>
+__global__ __launch_bounds__(kScoreNT) void score_split_cols_kernel(SplitScore a, HeadArgs heads) {
+    extern __shared__ float2 rowstat[];
+    split_cols_block<FULL, IDX, DT, NKS, kScoreNT>(a, heads, blockIdx.x, rowstat);
 }
 
 template <int NT, int EMAX>
 __global__ __launch_bounds__(NT) void score_select_kernel(SelectJob sj) {
-    score_select_block<NT, EMAX>(sj, blockIdx.x);
+    __shared__ TopkSmem sm;
+    __shared__ float vs[EMAX > 1 ? EMAX * NT : 1];
+    score_select_block<NT, EMAX>(sj, blockIdx.x, sm, vs);
 }
 
 // The head lists travel as a kernel argument of bounded size: a launch covers
@@ -1066,6 +1107,8 @@ struct ScoreLaunch {
     float sl2e;
     float *partial;
     hipStream_t st;
+    const int32_t *kidx = nullptr;  // [B][N] rows of k that are the keys (NULL: all N of k)
+    int n_src = 0;                  // rows of k per head with kidx
 };
 
 // A host head list travels as a kernel argument of bounded size: a launch
@@ -1198,11 +1241,19 @@ static hipError_t score_head_go(const ScoreLaunch &a) {
     return hipSuccess;
 }
 
+// The split form's arguments for nb samples from b0.
+static SplitScore split_score(const ScoreLaunch &a, float2 *stats, int b0, int nb) {
+    const int nsplit = (a.N + kScoreCK - 1) / kScoreCK;
+    return SplitScore{(const char *)a.q, (const char *)a.k, a.heads_dev, a.src,       a.row_lse,
+                      b0,                a.H,               a.Nt,        a.N,         a.n_heads,
+                      nsplit,            a.row_bytes,       a.kidx,      a.n_src,     a.sl2e,
+                      stats,             a.partial,         nsplit * a.n_heads * nb};
+}
+
 // The split form: two launches per bounded head list, statistics then
 // column sums.
-template <bool FULL, int DT, int NKS>
+template <bool FULL, bool IDX, int DT, int NKS>
 static hipError_t score_split_go(const ScoreLaunch &a, float2 *stats) {
-    const int nsplit = (a.N + kScoreCK - 1) / kScoreCK;
     const int per_launch = a.src == kHeadsArg ? kMaxHeadArgs / a.n_heads : a.B;
     HeadArgs ha;
     for (int b0 = 0; b0 < a.B; b0 += per_launch) {
@@ -1210,28 +1261,28 @@ static hipError_t score_split_go(const ScoreLaunch &a, float2 *stats) {
         for (int i = 0; i < kMaxHeadArgs; ++i)
             ha.h[i] = (a.src == kHeadsArg && i < nb * a.n_heads)
                           ? a.heads_host[(size_t)b0 * a.n_heads + i] : 0;
-        const dim3 grid(nsplit * a.n_heads * nb);
-        hipLaunchKernelGGL((score_split_stats_kernel<FULL, DT, NKS>), grid, dim3(kScoreNT), 0, a.st,
-                           (const char *)a.q, (const char *)a.k, ha, a.heads_dev, a.src, b0, a.H,
-                           a.Nt, a.N, a.n_heads, nsplit, a.row_bytes, a.sl2e, stats);
+        const SplitScore s = split_score(a, stats, b0, nb);
+        hipLaunchKernelGGL((score_split_stats_kernel<FULL, IDX, DT, NKS>), dim3(s.nblocks), dim3(kScoreNT), 0,
+                           a.st, s, ha);
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
-        hipLaunchKernelGGL((score_split_cols_kernel<FULL, DT, NKS>), grid, dim3(kScoreNT),
-                           (size_t)a.Nt * sizeof(float2), a.st, (const char *)a.q,
-                           (const char *)a.k, ha, a.heads_dev, a.src, a.row_lse, b0, a.H, a.Nt,
-                           a.N, a.n_heads, nsplit, a.row_bytes, a.sl2e, stats, a.partial);
+        hipLaunchKernelGGL((score_split_cols_kernel<FULL, IDX, DT, NKS>), dim3(s.nblocks), dim3(kScoreNT),
+                           (size_t)a.Nt * sizeof(float2), a.st, s, ha);
         e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
     return hipSuccess;
 }
 
+template <int DT, int NKS>
+static hipError_t score_split_nks(const ScoreLaunch &a, float2 *stats) {
+    return a.row_bytes == NKS * 64 ? score_split_go<true, false, DT, NKS>(a, stats)
+                                   : score_split_go<false, false, DT, NKS>(a, stats);
+}
+
 template <int DT>
 static hipError_t score_split_dt(int nks, const ScoreLaunch &a, float2 *stats) {
-    const bool full = a.row_bytes == nks * 64;
-    if (nks == 2)
-        return full ? score_split_go<true, DT, 2>(a, stats) : score_split_go<false, DT, 2>(a, stats);
-    return full ? score_split_go<true, DT, 4>(a, stats) : score_split_go<false, DT, 4>(a, stats);
+    return nks == 2 ? score_split_nks<DT, 2>(a, stats) : score_split_nks<DT, 4>(a, stats);
 }
 
 // log2(e) / sqrt(head width): the attention scale in base-2 units.
@@ -1344,7 +1395,8 @@ __global__ __launch_bounds__(kScoreNT) void reduce_select_gather_kernel(ReduceJo
     static_assert(kScoreNT == kGatherNT, "the gather's workgroup size");
     int blk = blockIdx.x;
     if (blk < sj.nblocks) {
-        score_select_block<kScoreNT, 1>(sj, blk);
+        __shared__ TopkSmem sm;
+        score_select_block<kScoreNT, 1>(sj, blk, sm, nullptr);
         return;
     }
     blk -= sj.nblocks;
@@ -1355,7 +1407,189 @@ __global__ __launch_bounds__(kScoreNT) void reduce_select_gather_kernel(ReduceJo
         return;
     }
     blk -= rj.nblocks;
-    if (blk < gj.nblocks) gather_block(gj.ga, gj.idx, gj.k, blk);
+    if (blk < gj.nblocks) gather_block(gj.ga, gj.idx, gj.k, blk, threadIdx.x);
+}
+
+// The launches of the one-call step with member lists (larger batches).  The
+// chain after the selection that ends in the merge spends two launches on few
+// or idle workgroups (the argmax, the member lists); the score chain rides in
+// them, again on keys read through the kept list, and the K/V compaction, which
+// fills HBM on its own, hides the member lists and the score's second half:
+//   assign_score: 16-row score blocks, or the split form's statistics, and the
+//     argmax of the Gram;
+//   bucket_carry: the member lists, the score's column sums (split form) or its
+//     top-N_2, and the compaction of K and V.
+// The member lists come first in the grid (few, long workgroups), the
+// compaction last.  Each body is its own launch's, so the bits are the same.
+// Measured, alone and shared: 16 x 576 tokens of 8 KB, 4 heads: argmax 6.6 + score
+// 5.6 -> 9.4 us, member lists 4.1 + top-N_2 4.0 + compaction 18.9 -> 19.0; with
+// the merge's carry the step 124.1 -> 113.9 us; 2 x 4608 x 10 KB 217.4 -> 204.
+template <int DT, int MAXC>
+__global__ __launch_bounds__(kScoreNT) void assign_score_kernel(
+    const char *__restrict__ q, const char *__restrict__ k_full, HeadArgs heads, int H, int Nt,
+    int N, int n_src, const int32_t *__restrict__ kidx, int n_heads, int row_bytes,
+    float scale_log2e, float *__restrict__ partial, int n_score, AssignJob aj) {
+    // two chunks, so that four workgroups fit on a CU: with three chunks (two
+    // or three workgroups) the argmax's rows had too few waves in flight and the
+    // launch took as long as its two halves apart
+    constexpr int NS = 2;
+    __shared__ __attribute__((aligned(16))) char ring[NS * ScoreStage<4>::STAGE];
+    if ((int)blockIdx.x >= n_score) {
+        assign_block(aj, (int)blockIdx.x - n_score);
+        return;
+    }
+    score_partial_block<DT, 4, MAXC, true, NS>(q, k_full, heads, nullptr, kHeadsArg, nullptr, 0, H, Nt, N,
+                                           n_heads, row_bytes, scale_log2e, partial, 0, n_score,
+                                           kidx, n_src, ring);
+}
+
+template <int DT, int NKS>
+__global__ __launch_bounds__(kScoreNT) void assign_split_kernel(SplitScore a, HeadArgs heads,
+                                                                AssignJob aj) {
+    if ((int)blockIdx.x >= a.nblocks) assign_block(aj, (int)blockIdx.x - a.nblocks);
+    else split_stats_block<true, true, DT, NKS>(a, heads, blockIdx.x);
+}
+
+// Workgroups of NT threads carry NT / kGatherNT workgroups' work of the gather.
+template <int NT>
+__device__ __forceinline__ void gather_wide(const GatherJob &gj, int blk) {
+    const int sub = __builtin_amdgcn_readfirstlane(threadIdx.x / kGatherNT);
+    blk = blk * (NT / kGatherNT) + sub;
+    if (blk < gj.nblocks) gather_block(gj.ga, gj.idx, gj.k, blk, threadIdx.x % kGatherNT);
+}
+
+template <int NT>
+__global__ __launch_bounds__(NT) void bucket_select_gather_kernel(BucketJob bj, SelectJob sj,
+                                                                  GatherJob gj) {
+    extern __shared__ int32_t sa[];
+    int blk = blockIdx.x;
+    if (blk < bj.nblocks) {
+        bucket_block<NT>(bj, blk % bj.ngroups, blk / bj.ngroups, sa);
+        return;
+    }
+    blk -= bj.nblocks;
+    if (blk < sj.nblocks) {
+        __shared__ TopkSmem sm;
+        score_select_block<NT, 1>(sj, blk, sm, nullptr);
+        return;
+    }
+    gather_wide<NT>(gj, blk - sj.nblocks);
+}
+
+template <int DT, int NKS, int NT>
+__global__ __launch_bounds__(NT) void bucket_cols_gather_kernel(BucketJob bj, SplitScore a,
+                                                                HeadArgs heads, GatherJob gj) {
+    extern __shared__ int32_t sa[];
+    int blk = blockIdx.x;
+    if (blk < bj.nblocks) {
+        bucket_block<NT>(bj, blk % bj.ngroups, blk / bj.ngroups, sa);
+        return;
+    }
+    blk -= bj.nblocks;
+    if (blk < a.nblocks) {
+        split_cols_block<true, true, DT, NKS, NT>(a, heads, blk, (float2 *)sa);
+        return;
+    }
+    gather_wide<NT>(gj, blk - a.nblocks);
+}
+
+// The form the score takes in those launches: 16-row blocks with indexed keys
+// hold every logit of at most 256 keys of 256 streamed bytes.
+int shared_score_form(int dt, int B, int H, int n_heads, int Nt, int N, int hd) {
+    if ((long long)B * n_heads > kMaxHeadArgs) return kSharedNone;  // one launch's head list
+    if (score_uses_head_form(dt, B, H, n_heads, Nt, N, hd)) return kSharedNone;
+    if (score_uses_split_form(dt, B, H, n_heads, Nt, N, hd))  // on whole rows only
+        return hd % 32 == 0 ? kSharedSplit : kSharedNone;
+    return head_windows(dt, hd) == 4 && N <= 4 * kScoreCK ? kSharedRows : kSharedNone;
+}
+
+static ScoreLaunch shared_score(const ScoreChain &c) {
+    ScoreLaunch a{c.q, c.k_full, c.heads, nullptr, kHeadsArg, nullptr, c.B, c.H, c.Nt, c.N, c.n_heads,
+                  c.hd * ((c.dt == kBF16) ? 2 : 4), scale_log2e_of(c.hd), c.partial, nullptr};
+    a.kidx = c.kept;
+    a.n_src = c.n_src;
+    return a;
+}
+
+static HeadArgs shared_heads(const ScoreChain &c) {
+    HeadArgs ha;
+    for (int i = 0; i < kMaxHeadArgs; ++i) ha.h[i] = i < c.B * c.n_heads ? c.heads[i] : 0;
+    return ha;
+}
+
+hipError_t launch_assign_score(const ScoreChain &c, const AssignJob &aj, hipStream_t st) {
+    const ScoreLaunch a = shared_score(c);
+    const HeadArgs ha = shared_heads(c);
+    const int n_assign = aj.r.nblocks + aj.f.nblocks;
+    if (c.form == kSharedSplit) {
+        const SplitScore s = split_score(a, (float2 *)c.stats, 0, c.B);
+        const int nks = head_windows(c.dt, c.hd);
+#define PV_AS_CASE(dtv, n)                                                                        \
+    if (c.dt == dtv && nks == n) {                                                                \
+        hipLaunchKernelGGL((assign_split_kernel<dtv, n>), dim3(s.nblocks + n_assign),             \
+                           dim3(kScoreNT), 0, st, s, ha, aj);                                     \
+        return hipGetLastError();                                                                 \
+    }
+        PV_AS_CASE(kBF16, 2)
+        PV_AS_CASE(kBF16, 4)
+        PV_AS_CASE(kF32, 2)
+        PV_AS_CASE(kF32, 4)
+#undef PV_AS_CASE
+        return hipErrorInvalidValue;
+    }
+    if (c.form != kSharedRows) return hipErrorInvalidValue;
+    const int n_score = ((c.Nt + 15) / 16) * c.n_heads * c.B;
+    const int nch = (c.N + kScoreCK - 1) / kScoreCK;
+#define PV_AS_CASE(dtv, mc)                                                                       \
+    if (c.dt == dtv && nch <= mc) {                                                               \
+        hipLaunchKernelGGL((assign_score_kernel<dtv, mc>), dim3(n_score + n_assign),              \
+                           dim3(kScoreNT), 0, st, (const char *)c.q, (const char *)c.k_full, ha,  \
+                           c.H, c.Nt, c.N, c.n_src, c.kept, c.n_heads, a.row_bytes, a.sl2e,       \
+                           c.partial, n_score, aj);                                               \
+        return hipGetLastError();                                                                 \
+    }
+    PV_AS_CASE(kBF16, 1)
+    PV_AS_CASE(kBF16, 2)
+    PV_AS_CASE(kBF16, 4)
+    PV_AS_CASE(kF32, 1)
+    PV_AS_CASE(kF32, 2)
+    PV_AS_CASE(kF32, 4)
+#undef PV_AS_CASE
+    return hipErrorInvalidValue;
+}
+
+hipError_t launch_bucket_carry(const ScoreChain &c, const BucketJob &bj, const SelectJob &sj,
+                               const GatherJob &gj, hipStream_t st) {
+    const size_t lds_b = (size_t)bj.Nv * sizeof(int32_t), lds_c = (size_t)c.Nt * sizeof(float2);
+    const bool wide = bj.Nv >= kBucketWideNv;
+    const int nt = wide ? 1024 : 512, n_gather = (gj.nblocks + nt / kGatherNT - 1) / (nt / kGatherNT);
+    if (c.form == kSharedSplit) {
+        const SplitScore s = split_score(shared_score(c), (float2 *)c.stats, 0, c.B);
+        const HeadArgs ha = shared_heads(c);
+        const int nks = head_windows(c.dt, c.hd);
+        const dim3 grid(bj.nblocks + s.nblocks + n_gather);
+#define PV_BC_CASE(dtv, n, t)                                                                     \
+    if (c.dt == dtv && nks == n && nt == t) {                                                     \
+        hipLaunchKernelGGL((bucket_cols_gather_kernel<dtv, n, t>), grid, dim3(t),                 \
+                           lds_b > lds_c ? lds_b : lds_c, st, bj, s, ha, gj);                     \
+        return hipGetLastError();                                                                 \
+    }
+        PV_BC_CASE(kBF16, 2, 512)
+        PV_BC_CASE(kBF16, 4, 512)
+        PV_BC_CASE(kF32, 2, 512)
+        PV_BC_CASE(kF32, 4, 512)
+        PV_BC_CASE(kBF16, 2, 1024)
+        PV_BC_CASE(kBF16, 4, 1024)
+        PV_BC_CASE(kF32, 2, 1024)
+        PV_BC_CASE(kF32, 4, 1024)
+#undef PV_BC_CASE
+        return hipErrorInvalidValue;
+    }
+    if (sj.nblocks > 0 && sj.N > 512) return hipErrorInvalidValue;
+    const dim3 grid(bj.nblocks + sj.nblocks + n_gather);
+    if (wide) hipLaunchKernelGGL(bucket_select_gather_kernel<1024>, grid, dim3(1024), lds_b, st, bj, sj, gj);
+    else hipLaunchKernelGGL(bucket_select_gather_kernel<512>, grid, dim3(512), lds_b, st, bj, sj, gj);
+    return hipGetLastError();
 }
 
 bool gram_score_supported(int dt, int B, int n_heads, int N, int hd) {

@@ -31,8 +31,9 @@ struct GatherJob {
 // Workgroup blk of the gather: a contiguous span of 16-byte pieces of one
 // plane (sample x head group) of one tensor; rows whose index is out of
 // range are written as zeros.
+// tid: this thread among the kGatherNT of the workgroup's work.
 __device__ __forceinline__ void gather_block(const GatherArgs &ga, const int32_t *__restrict__ idx,
-                                             int k, int blk) {
+                                             int k, int blk, int tid) {
     int t = 0;
 #pragma unroll
     for (int u = 1; u < kMaxGather; ++u)
@@ -51,7 +52,7 @@ __device__ __forceinline__ void gather_block(const GatherArgs &ga, const int32_t
     // between two index loads would be waited for with the next index
 #pragma unroll
     for (int it = 0; it < kGatherIT; ++it) {
-        const int e = (sub * kGatherIT + it) * kGatherNT + threadIdx.x;
+        const int e = (sub * kGatherIT + it) * kGatherNT + tid;
         const int ec = e < ppp ? e : ppp - 1;
         const int r = ec / g.cpr, c = ec - r * g.cpr;
         rr[it] = e < ppp ? r : -1;
@@ -177,6 +178,73 @@ __device__ __forceinline__ void gram_reduce_row(const ReduceJob &j, int m, int b
 // Rows of gram_reduce_row per carried workgroup (one per wave of 256).
 constexpr int kReduceRowsPerBlock = 4;
 
+// Best column tile of every pruned row of the full-k Gram, combined in tile
+// order with the total order above.
+struct FinishJob {
+    const float *best_val;     // [B][ntn][Mp]
+    const int32_t *best_slot;  // [B][ntn][Mp]
+    int ntn, Mp, Nv;
+    const int32_t *pruned;     // [B][Mp]
+    int32_t *assign;           // [B][Nv]
+    int nblocks;               // workgroups of kFinNT rows carried by another launch; 0: none
+};
+constexpr int kFinNT = 256;
+constexpr int kFinU = 16;
+
+// One thread, pruned row m of sample b.  The candidates of kFinU tiles are
+// loaded at once (a loop that compares each one as it arrives waits for every
+// load in turn); past the last tile the last one repeats, which cannot change
+// a maximum under a total order.
+__device__ __forceinline__ void gram_finish_row(const FinishJob &j, int m, int b) {
+    if (m >= j.Mp) return;
+    const int tok = j.pruned[(size_t)b * j.Mp + m];
+    float bv = -INFINITY;
+    int bs = 0x7FFFFFFF;
+    for (int t0 = 0; t0 < j.ntn; t0 += kFinU) {
+        float v[kFinU];
+        int s[kFinU];
+#pragma unroll
+        for (int u = 0; u < kFinU; ++u) {
+            const size_t at = ((size_t)b * j.ntn + min(t0 + u, j.ntn - 1)) * j.Mp + m;
+            v[u] = j.best_val[at];
+            s[u] = j.best_slot[at];
+        }
+#pragma unroll
+        for (int u = 0; u < kFinU; ++u)
+            if (better(v[u], s[u], bv, bs)) {
+                bv = v[u];
+                bs = s[u];
+            }
+    }
+    j.assign[(size_t)b * j.Nv + tok] = bs;
+}
+
+// The Gram's argmax carried by another launch: one of the two forms, or none.
+struct AssignJob {
+    ReduceJob r;
+    FinishJob f;
+};
+
+// Workgroup blk (of 256 threads) of the carried argmax; the slices loaded per
+// round follow their number, as in the argmax's own launch.
+__device__ __forceinline__ void assign_block(const AssignJob &aj, int blk) {
+    if (blk < aj.r.nblocks) {
+        const int per = (aj.r.Mp + kReduceRowsPerBlock - 1) / kReduceRowsPerBlock;
+        const int m = (blk % per) * kReduceRowsPerBlock + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+        if (m >= aj.r.Mp) return;
+        const int b = blk / per, lane = threadIdx.x & 63;
+        if (aj.r.KS <= 2) gram_reduce_row<2>(aj.r, m, b, lane);
+        else if (aj.r.KS <= 4) gram_reduce_row<4>(aj.r, m, b, lane);
+        else gram_reduce_row<8>(aj.r, m, b, lane);
+        return;
+    }
+    blk -= aj.r.nblocks;
+    if (blk < aj.f.nblocks) {
+        const int per = (aj.f.Mp + kFinNT - 1) / kFinNT;
+        gram_finish_row(aj.f, (blk % per) * kFinNT + (int)threadIdx.x, blk / per);
+    }
+}
+
 // ----------------------------------------------------------------------------
 // Split-k products (the cosine, and the Grams that are too small to fill the
 // chip with full-k tiles).
@@ -261,16 +329,123 @@ struct GramJob {
     int nblocks;            // tile workgroups (B * KS * ntm * ntn); 0: none
 };
 
-// What the merge launch of the one-call step carries besides the merge: the
-// merged rows of the slots the head-aware top-N_2 kept, written straight to
-// their compacted places, and the compaction of K and V to those slots.
-struct MergeCarry {
-    const int32_t *slot_of2;  // [B][N1] position of each slot among the N_2 kept, or -1
-    char *hidden2;            // [B][N2] rows of d_bytes
-    int N2;
-    GatherJob gj;             // K and V of the N_2 kept slots
+// ----------------------------------------------------------------------------
+// Member lists for large inputs, where every merge workgroup scanning the whole
+// assignment would cost more than the rows it adds.
+//
+// A workgroup of 512 or 1024 threads lists the members of the
+// 256 slots [256 g, 256 g + 256) in ascending token order: mcount[b][s],
+// mstart[b][s] (offset in the sample's list region) and the lists themselves
+// in mlist[b][g * Nv ...].  The assignment is staged in LDS; the waves take
+// consecutive token segments and sweep them twice, 64 tokens per
+// step: per-slot counts (integer atomics on the wave's counters in LDS), then
+// placement at offsets that keep the segments in order.  In the placement the
+// lanes of a step that hold the same slot are found with one ballot per bit
+// of the slot offset (the lanes whose offsets agree on every bit), so a step
+// costs the same whatever the number of distinct slots in it; each lane takes
+// the next places in lane order and the lowest such lane advances the wave's
+// counter of that slot.
+// ----------------------------------------------------------------------------
+constexpr int kBucketBits = 8;
+constexpr int kBucketSlots = 1 << kBucketBits;
+static_assert(kBucketSlots == kBucketSlotsPerGroup, "slots per bucket group");
+// threads: 512, or 1024 from kBucketWideNv tokens (measured: 16 waves sweep
+// the longer assignments faster, 8 cost less on short ones)
+constexpr int kBucketWideNv = 2048;
+
+// Lanes whose value v agrees with this lane's on the low kBucketBits bits,
+// among the lanes in `act`.
+__device__ __forceinline__ unsigned long long same_slot_lanes(int v, unsigned long long act) {
+    unsigned long long same = act;
+#pragma unroll
+    for (int bit = 0; bit < kBucketBits; ++bit) {
+        const bool on = (v >> bit) & 1;
+        const unsigned long long ones = __ballot(on);
+        same &= on ? ones : ~ones;
+    }
+    return same;
+}
+
+struct BucketJob {
+    const int32_t *assign;  // [B][Nv]
+    int Nv, N1;
+    int32_t *mcount, *mstart, *mlist;
+    int ngroups;            // groups of kBucketSlots slots
+    int nblocks;            // workgroups (ngroups * B)
 };
 
+// Group g of sample b; sa: LDS for the sample's assignment, [Nv].
+template <int kBucketNT>
+__device__ __forceinline__ void bucket_block(const BucketJob &bj, int g, int b, int32_t *sa) {
+    constexpr int kBucketW = kBucketNT / 64;
+    __shared__ int cur[kBucketW][kBucketSlots];
+    __shared__ int wsum[kBucketW];
+    const int Nv = bj.Nv, N1 = bj.N1, ngroups = bj.ngroups;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int s0 = g * kBucketSlots;
+    const int32_t *as = bj.assign + (size_t)b * Nv;
+    int32_t *lst = bj.mlist + ((size_t)b * ngroups + g) * Nv;
+    const unsigned long long lt = (1ull << lane) - 1ull;
+
+    for (int e = lane; e < kBucketSlots; e += 64) cur[wave][e] = 0;
+    // stage: eight loads per thread in flight per round
+    for (int j0 = 0; j0 < Nv; j0 += kBucketNT * 8) {
+        int v[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) v[u] = as[min(j0 + u * kBucketNT + tid, Nv - 1)];
+#pragma unroll
+        for (int u = 0; u < 8; ++u)
+            if (j0 + u * kBucketNT + tid < Nv) sa[j0 + u * kBucketNT + tid] = v[u];
+    }
+    __syncthreads();
+    // this wave's token segment [t0, t1), whole 64-token steps
+    const int seg = ((Nv + kBucketW - 1) / kBucketW + 63) / 64 * 64;
+    const int t0 = min(wave * seg, Nv), t1 = min(t0 + seg, Nv);
+    int *wc = cur[wave];
+
+    // pass 1: this wave's count of every slot (integer atomics in LDS: the
+    // counts do not depend on their order)
+    for (int c0 = t0; c0 < t1; c0 += 64) {
+        const int j = c0 + lane;
+        const int v = (j < t1) ? sa[j] - s0 : -1;
+        if (v >= 0 && v < kBucketSlots) atomicAdd(&wc[v], 1);
+    }
+    __syncthreads();
+    // slot totals and offsets; then each wave's first position per slot
+    int tot = 0;
+    if (tid < kBucketSlots) {
+#pragma unroll
+        for (int w = 0; w < kBucketW; ++w) tot += cur[w][tid];
+    }
+    int all;
+    const int base = block_excl_scan<kBucketNT>(tot, wsum, &all);
+    if (tid < kBucketSlots) {
+        if (s0 + tid < N1) {
+            bj.mcount[(size_t)b * N1 + s0 + tid] = tot;
+            bj.mstart[(size_t)b * N1 + s0 + tid] = g * Nv + base;
+        }
+        int run = base;
+#pragma unroll
+        for (int w = 0; w < kBucketW; ++w) {
+            const int c = cur[w][tid];
+            cur[w][tid] = run;
+            run += c;
+        }
+    }
+    __syncthreads();
+    // pass 2: placement in token order
+    for (int c0 = t0; c0 < t1; c0 += 64) {
+        const int j = c0 + lane;
+        const int v = (j < t1) ? sa[j] - s0 : -1;
+        const bool rel = v >= 0 && v < kBucketSlots;
+        const unsigned long long same = same_slot_lanes(v, __ballot(rel));
+        if (rel) {
+            lst[wc[v] + __popcll(same & lt)] = j;
+            if ((same & lt) == 0ull) wc[v] += __popcll(same);
+        }
+    }
+}
 
 // ---- head-aware score: v and the top-N_2 (Eq. v, Sec. 4.4) ---------------
 constexpr int kSelU = 16;
@@ -305,9 +480,10 @@ __device__ __forceinline__ float select_sum(const SelectJob &sj, const float *pb
 
 // Workgroup of NT threads, sample b: v[j] = select_sum for every column, then
 // the top-budget of v (lower index first among equal scores), ascending.
+// vs: LDS of EMAX * NT floats (unused with one column per thread).
 template <int NT, int EMAX>
-__device__ __forceinline__ void score_select_block(const SelectJob &sj, int b) {
-    __shared__ TopkSmem sm;
+__device__ __forceinline__ void score_select_block(const SelectJob &sj, int b, TopkSmem &sm,
+                                                   float *vs) {
     const int N = sj.N, nparts = sj.nparts;
     const float *pb = sj.partial + (size_t)b * nparts * N;
     float *vb = sj.v + (size_t)b * N;
@@ -324,7 +500,6 @@ __device__ __forceinline__ void score_select_block(const SelectJob &sj, int b) {
         // the sums with the columns spread over the lanes (each load of a
         // part then covers contiguous columns), handed to block_topk's
         // ownership (E consecutive columns per thread) through LDS
-        __shared__ float vs[EMAX * NT];
 #pragma unroll
         for (int e = 0; e < EMAX; ++e) {
             const int j = t + e * NT;
@@ -344,5 +519,23 @@ __device__ __forceinline__ void score_select_block(const SelectJob &sj, int b) {
     block_topk<NT, EMAX>(key, N, sj.budget, sj.kept + (size_t)b * sj.budget, nullptr,
                          sj.slot_of ? sj.slot_of + (size_t)b * N : nullptr, sm);
 }
+
+// What the merge launch of the one-call step carries besides the merge: the
+// merged rows of the slots the head-aware top-N_2 kept, written straight to
+// their compacted places, and the compaction of K and V to those slots.
+struct MergeCarry {
+    const int32_t *slot_of2;  // [B][N1] position of each slot among the N_2 kept, or -1
+    char *hidden2;            // [B][N2] rows of d_bytes
+    int N2;
+    GatherJob gj;             // K and V of the N_2 kept slots
+};
+
+// What the member-list merge carries: that compaction, or, where the score's
+// column sums are only just complete (its split form), the top-N_2.
+constexpr int kMergeSelCols = 8;  // columns per thread of the carried top-N_2
+struct MergeCsrCarry {
+    MergeCarry mc;
+    SelectJob sj;  // nblocks 0: none; N <= 256 kMergeSelCols
+};
 
 }  // namespace pv

@@ -12,6 +12,9 @@ struct ReduceJob;
 struct SelectJob;
 struct GramJob;
 struct MergeCarry;
+struct MergeCsrCarry;
+struct AssignJob;
+struct BucketJob;
 
 // Element types of the inputs (values of pv_dtype).
 constexpr int kF32 = 0;
@@ -112,7 +115,7 @@ hipError_t launch_bucket(const int32_t *assign, int B, int Nv, int N1, int32_t *
                          int32_t *mstart, int32_t *mlist, hipStream_t st);
 hipError_t launch_merge_csr(int dt, const void *vis, int B, int Nv, int d, int N1,
                             const int32_t *mcount, const int32_t *mstart, const int32_t *mlist,
-                            void *merged, hipStream_t st);
+                            void *merged, hipStream_t st, const MergeCsrCarry *with = nullptr);
 // Whether the merge reads member lists built by the bucket kernel instead of
 // scanning the assignment in every workgroup: for batches (one extra launch
 // is then cheap next to the work), and whenever the scans would read more
@@ -206,6 +209,22 @@ hipError_t launch_gram_score(int dt, const void *q, const void *k_full, const in
                              int n_heads, float *partial, const GramJob &gj, hipStream_t st);
 hipError_t launch_reduce_select_gather(const ReduceJob &rj, const SelectJob &sj,
                                        const GatherJob &gj, hipStream_t st);
+
+// The score chain of the one-call step with member lists, carried by the
+// launches of the Gram's argmax and of the member lists.
+enum SharedScore { kSharedNone = 0, kSharedRows, kSharedSplit };
+int shared_score_form(int dt, int B, int H, int n_heads, int Nt, int N, int hd);
+struct ScoreChain {
+    int form, dt;
+    const void *q, *k_full;  // k_full: [B][H][n_src][hd], read through kept
+    const int32_t *heads;    // host list [B][n_heads]
+    int B, H, Nt, N, n_src, hd, n_heads;
+    const int32_t *kept;     // [B][N]
+    float *partial, *stats;
+};
+hipError_t launch_assign_score(const ScoreChain &c, const AssignJob &aj, hipStream_t st);
+hipError_t launch_bucket_carry(const ScoreChain &c, const BucketJob &bj, const SelectJob &sj,
+                               const GatherJob &gj, hipStream_t st);
 
 // ---- compaction (Sec. 4.1)
 constexpr int kMaxGather = 4;

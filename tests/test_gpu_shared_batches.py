@@ -1,0 +1,81 @@
+"""The one-call step with member lists: the score chain and the K/V compaction in the
+launches of the Gram's argmax and of the member lists, against the separate launches byte
+for byte (which the pipeline's own tests hold against the oracle)."""
+
+from __future__ import annotations
+
+import numpy as np
+import pytest
+
+from paper_2608_25332_amd import workloads as W
+from parity_util import to_dev
+from test_gpu_pipeline import _assert_same, _both
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _gpu():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+
+
+# (B, Nv, Nt, d, H, hd, n_heads, N1, N2, dtype)
+CASES = [
+    (2, 300, 17, 512, 4, 128, 2, 100, 30, "bf16"),    # 16-row blocks, two key chunks; split-k argmax
+    (3, 257, 16, 72, 4, 64, 1, 64, 64, "f32"),        # one chunk of fp32 rows, padded d, N2 = N1
+    (2, 260, 5, 512, 4, 104, 4, 256, 1, "bf16"),      # four chunks, rows of 208 bytes, 4 pruned
+    (2, 2100, 9, 64, 4, 128, 2, 200, 50, "bf16"),     # 1024-thread member lists
+    (16, 576, 64, 1024, 8, 128, 4, 192, 64, "bf16"),  # wide split-k tiles
+    (100, 600, 3, 64, 4, 128, 1, 200, 20, "bf16"),    # full-k Gram with two column tiles
+    (130, 300, 70, 64, 2, 128, 1, 128, 20, "bf16"),   # one column tile: no finish beside the score
+    (1, 900, 33, 64, 6, 128, 3, 300, 77, "bf16"),     # split score (three to nine chunks), split-k
+    (2, 700, 130, 256, 4, 32, 2, 321, 100, "f32"),    # 128-byte fp32 rows, a chunk of one key
+    (1, 2500, 20, 64, 4, 64, 4, 1200, 333, "bf16"),   # 128-byte rows, 1024 threads
+    (1, 700, 8, 128, 3, 120, 2, 500, 20, "bf16"),     # split score on rows of 240 bytes
+    (2, 4608, 40, 128, 4, 64, 2, 1152, 200, "f32"),   # full-k Gram with nine column tiles
+    (1, 2400, 7, 64, 3, 128, 2, 2300, 5, "bf16"),     # top-N2 of more than 2048 keys
+]
+
+
+@pytest.mark.parametrize("B,Nv,Nt,d,H,hd,nh,N1,N2,dt", CASES)
+def test_shared_launches_equal_separate(B, Nv, Nt, d, H, hd, nh, N1, N2, dt):
+    print(f"[shared batches] B={B} Nv={Nv} Nt={Nt} d={d} hd={hd} heads={nh} N1={N1} N2={N2} {dt}", flush=True)
+    rng = np.random.default_rng(B * 1000 + Nv + N1)
+
+    def draw(*shape):
+        x = rng.standard_normal(shape, dtype=np.float32)
+        return to_dev(W.bf16_round(x) if dt == "bf16" else x, dt)
+
+    ins = (draw(B, Nv, d), draw(B, Nt, d), draw(B, H, Nt, hd), draw(B, H, Nv, hd), draw(B, H, Nv, hd))
+    heads = np.stack([rng.permutation(H)[:nh] for _ in range(B)]).astype(np.int32)
+    _assert_same(*_both(ins, heads, N1, N2))
+
+
+def test_shared_launches_in_a_graph():
+    """Captured once and replayed on changing inputs, with eager work between the replays."""
+    from paper_2608_25332_amd import provip
+    g = torch.Generator(device="cuda:0")
+    g.manual_seed(5)
+    B, Nv, Nt, d, H, hd, N1, N2 = 4, 320, 20, 256, 4, 128, 120, 40
+
+    def draw(*shape):
+        return torch.randn(shape, generator=g, device="cuda:0").bfloat16()
+
+    ins = [draw(B, Nv, d), draw(B, Nt, d), draw(B, H, Nt, hd), draw(B, H, Nv, hd), draw(B, H, Nv, hd)]
+    heads = np.tile(np.array([[1, 3]], np.int32), (B, 1))
+    out = provip.pv_prune_pipeline(*ins, heads, N1, N2)
+    ws = out.pop("workspace")
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        provip.pv_prune_pipeline(*ins, heads, N1, N2, out=out, workspace=ws)
+    for _ in range(3):
+        for t in ins:
+            t.copy_(draw(*t.shape))
+        ref = provip.pv_prune_pipeline(*ins, heads, N1, N2, separate=True)
+        graph.replay()
+        torch.cuda.synchronize()
+        _assert_same(out, ref)
