@@ -239,7 +239,22 @@ struct StepCarry {
     pv::SelectJob select;  // nblocks 0: not carried
     pv::GatherJob gather;
     pv::MergeCsrCarry merge;
+    // the visual heads first (the progressive schedule): the confidence before
+    // the Gram, its top-N_vis beside the argmax, then the score on that list
+    bool visual = false;
+    const int32_t *row_mask = nullptr;
+    float *conf_part = nullptr, *conf = nullptr;
+    int32_t *vis_heads = nullptr;
 };
+
+// The launches of the argmax with what rides in them.
+hipError_t launch_assign(const StepCarry &c, const pv::AssignJob &aj, hipStream_t st) {
+    const pv::ScoreChain &s = c.score;
+    if (!c.visual) return pv::launch_assign_score(s, aj, st);
+    const hipError_t e = pv::launch_assign_conf(aj, c.conf_part, s.B, s.H, s.Nt, c.conf, s.n_heads,
+                                                c.vis_heads, st);
+    return e != hipSuccess ? e : pv::launch_assign_score(s, pv::AssignJob{}, st);
+}
 
 // The kernels of the dedup up to the top-N_1: the cosine to the anchors,
 // centring and max-pool into p, and the selection (kept, the pruned list
@@ -333,6 +348,12 @@ int dedup_impl(const void *vis, const void *anchors, int B, int Nv, int Nt, int 
             return PV_ERR_HIP;
         sm = fork->stream;
     }
+    if (carry && carry->visual) {
+        const pv::ScoreChain &s = carry->score;
+        if (pv::launch_head_conf_indexed(dt, s.q, s.k_full, carry->row_mask, B, s.H, s.Nt, s.N,
+                                         s.n_src, s.kept, s.hd, carry->conf_part, sm) != hipSuccess)
+            return PV_ERR_HIP;
+    }
     if (need_assign && P.Mp > 0) {
         if (P.gram_big) {
             if (!tr.launch("gram_tile", [&] {
@@ -345,7 +366,7 @@ int dedup_impl(const void *vis, const void *anchors, int B, int Nv, int Nt, int 
                 if (P.ntn > 1)
                     aj.f = pv::FinishJob{P.best_val, P.best_slot, P.ntn, P.Mp, Nv, P.pruned, asg,
                                          B * ((P.Mp + pv::kFinNT - 1) / pv::kFinNT)};
-                if (pv::launch_assign_score(carry->score, aj, sm) != hipSuccess) return PV_ERR_HIP;
+                if (launch_assign(*carry, aj, sm) != hipSuccess) return PV_ERR_HIP;
             } else if (P.ntn > 1) {
                 if (!tr.launch("gram_finish", [&] {
                         return pv::launch_gram_finish(P.best_val, P.best_slot, B, P.ntn, P.Mp, Nv,
@@ -364,7 +385,7 @@ int dedup_impl(const void *vis, const void *anchors, int B, int Nv, int Nt, int 
                 aj.r = pv::ReduceJob{P.gpart, B, P.Mp, budget, Nv, P.ks_gram, P.invn, P.pruned, kept,
                                      asg, B * ((P.Mp + pv::kReduceRowsPerBlock - 1) /
                                                pv::kReduceRowsPerBlock)};
-                if (pv::launch_assign_score(carry->score, aj, sm) != hipSuccess) return PV_ERR_HIP;
+                if (launch_assign(*carry, aj, sm) != hipSuccess) return PV_ERR_HIP;
             } else if (!tr.launch("gram_reduce", [&] {
                     return pv::launch_gram_reduce(P.gpart, B, P.Mp, budget, Nv, P.ks_gram, P.invn,
                                                   P.pruned, kept, asg, sm);
@@ -1201,7 +1222,7 @@ namespace {
 
 struct ProgPlan {
     size_t text, dedup, vh, head_b, head_c;
-    int32_t *count, *k2loc, *k3loc;
+    int32_t *count, *k2loc, *k3loc, *slot_of2;
     char *ks, *km;
     char *ws_text, *ws_dedup, *ws_vh, *ws_head_b, *ws_head_c;
     size_t bytes;
@@ -1224,6 +1245,7 @@ ProgPlan plan_prog(void *ws, int B, int Nv, int Nt, int d, int H, int hd, int es
     P.count = c.take<int32_t>((size_t)B);
     P.k2loc = c.take<int32_t>((size_t)B * N2);
     P.k3loc = c.take<int32_t>((size_t)B * N3);
+    P.slot_of2 = c.take<int32_t>((size_t)B * N1);
     P.ks = c.take<char>((size_t)B * H * N1 * hd * esz);
     P.km = c.take<char>((size_t)B * H * N2 * hd * esz);
     P.bytes = c.off + kAlign;
@@ -1264,48 +1286,108 @@ int progressive_impl(const void *text, const void *vis, const void *q_s, const v
     rc = text_impl(text, B, Nt, d, dtype, text_mask, P.count, nullptr, P.ws_text, P.text, stream,
                    nullptr, 0, 1, nullptr, nullptr);
     if (rc != PV_OK) return rc;
-    // pruning before the LLM on the critical rows (Sec. 4.3), with the merge
-    rc = dedup_impl(vis, text, B, Nv, Nt, d, dtype, N1, kept1, nullptr, assign, merged,
-                    P.ws_dedup, P.dedup, stream, nullptr, 0, 1, nullptr, nullptr, nullptr,
-                    text_mask);
-    if (rc != PV_OK) return rc;
-    // the shallow layer's keys of the N1 retained tokens
+    // Pruning before the LLM on the critical rows (Sec. 4.3), with the merge;
+    // then, on the shallow layer, the visual heads over the critical rows and
+    // head-aware pruning on them (Sec. 4.4, equations for C^h, V_l, S^vis and
+    // v).  With member lists the second chain, which needs only the kept list,
+    // reads its keys through that list and rides in the first one's launches
+    // (as in the one-call step); else the calls are made in turn.
     pv::GatherArgs ga;
-    {
-        const pv_gather_desc g = kv_desc(k_s_all, P.ks, H, Nv, N1, row_kv);
-        if ((rc = make_gather(&g, 1, kept1, B, N1, ga)) != PV_OK) return rc;
-        if (pv::launch_gather(ga, kept1, B, N1, st) != hipSuccess) return PV_ERR_HIP;
-    }
-    // visual heads over the critical rows, then head-aware pruning on them
-    // (Sec. 4.4, equations for C^h, V_l, S^vis and v)
-    rc = vis_heads_impl(q_s, P.ks, B, H, Nt, N1, hd, dtype, n_vis, vis_heads, conf, P.ws_vh,
-                        P.vh, stream, nullptr, 0, 1, nullptr, nullptr, text_mask);
-    if (rc != PV_OK) return rc;
-    rc = head_impl(q_s, P.ks, nullptr, vis_heads, n_vis, B, H, Nt, N1, hd, dtype, N2, P.k2loc,
-                   score2, P.ws_head_b, P.head_b, stream, nullptr, 0, 1, nullptr, nullptr);
-    if (rc != PV_OK) return rc;
-    // survivors of the shallow layer: token indices, merged rows, and the
-    // middle layer's keys of those tokens
-    if (pv::launch_compose_index(kept1, P.k2loc, B, N1, N2, kept2, st) != hipSuccess)
-        return PV_ERR_HIP;
-    {
-        const pv_gather_desc g = kv_desc(merged, hidden2, 1, N1, N2, row_h);
-        if ((rc = make_gather(&g, 1, P.k2loc, B, N2, ga)) != PV_OK) return rc;
-        if (pv::launch_gather(ga, P.k2loc, B, N2, st) != hipSuccess) return PV_ERR_HIP;
-        const pv_gather_desc gk = kv_desc(k_m_all, P.km, H, Nv, N2, row_kv);
-        if ((rc = make_gather(&gk, 1, kept2, B, N2, ga)) != PV_OK) return rc;
-        if (pv::launch_gather(ga, kept2, B, N2, st) != hipSuccess) return PV_ERR_HIP;
+    const int dt = (dtype == PV_BF16) ? pv::kBF16 : pv::kF32;
+    const int form = pv::shared_score_form(dt, B, H, n_vis, Nt, N1, hd);
+    if (N1 < Nv && form != pv::kSharedNone && pv::conf_indexed_supported(dt, N1, hd) &&
+        (form == pv::kSharedRows || N1 <= pv::kMergeSelCols * 256) &&
+        pv::merge_uses_lists(B, N1, padded_d(d, esz) * esz)) {
+        const bool rows = form == pv::kSharedRows;
+        const HeadPlan Hb = plan_head((char *)(((uintptr_t)P.ws_head_b + kAlign - 1) / kAlign * kAlign), B,
+                                      Nt, N1, n_vis, score2 == nullptr);
+        pv::ScoreChain chain{form, dt, q_s, k_s_all, nullptr, B, H, Nt, N1, Nv, hd, n_vis, kept1,
+                             Hb.partial, Hb.stats};
+        chain.heads_dev = vis_heads;
+        pv::SelectJob sj{Hb.partial, n_vis * (rows ? Hb.nrb : 1), N1,
+                         (float)(1.0 / ((double)Nt * (double)n_vis)), score2 ? score2 : Hb.v, N2,
+                         P.k2loc, B, nullptr};
+        sj.base = kept1;
+        sj.composed = kept2;
+        StepCarry sc{chain, sj, pv::GatherJob{}, pv::MergeCsrCarry{}};
+        sc.visual = true;
+        sc.row_mask = text_mask;
+        sc.conf_part = (float *)(((uintptr_t)P.ws_vh + kAlign - 1) / kAlign * kAlign);
+        sc.conf = conf;
+        sc.vis_heads = vis_heads;
+        if (rows) {  // the merge also writes the rows of the N_2 kept slots
+            sc.select.slot_of = P.slot_of2;
+            sc.merge.mc = pv::MergeCarry{P.slot_of2, (char *)hidden2, N2, pv::GatherJob{}};
+        } else {
+            sc.select.nblocks = 0;
+            sc.merge.sj = sj;
+        }
+        rc = dedup_impl(vis, text, B, Nv, Nt, d, dtype, N1, kept1, nullptr, assign, merged,
+                        P.ws_dedup, P.dedup, stream, nullptr, 0, 1, nullptr, nullptr, nullptr,
+                        text_mask, &sc);
+        if (rc != PV_OK) return rc;
+        if (!rows) {
+            const pv_gather_desc g = kv_desc(merged, hidden2, 1, N1, N2, row_h);
+            if ((rc = make_gather(&g, 1, P.k2loc, B, N2, ga)) != PV_OK) return rc;
+            if (pv::launch_gather(ga, P.k2loc, B, N2, st) != hipSuccess) return PV_ERR_HIP;
+        }
+    } else {
+        rc = dedup_impl(vis, text, B, Nv, Nt, d, dtype, N1, kept1, nullptr, assign, merged,
+                        P.ws_dedup, P.dedup, stream, nullptr, 0, 1, nullptr, nullptr, nullptr,
+                        text_mask);
+        if (rc != PV_OK) return rc;
+        // the shallow layer's keys of the N1 retained tokens
+        {
+            const pv_gather_desc g = kv_desc(k_s_all, P.ks, H, Nv, N1, row_kv);
+            if ((rc = make_gather(&g, 1, kept1, B, N1, ga)) != PV_OK) return rc;
+            if (pv::launch_gather(ga, kept1, B, N1, st) != hipSuccess) return PV_ERR_HIP;
+        }
+        // visual heads over the critical rows, then head-aware pruning on them
+        // (Sec. 4.4, equations for C^h, V_l, S^vis and v)
+        rc = vis_heads_impl(q_s, P.ks, B, H, Nt, N1, hd, dtype, n_vis, vis_heads, conf, P.ws_vh,
+                            P.vh, stream, nullptr, 0, 1, nullptr, nullptr, text_mask);
+        if (rc != PV_OK) return rc;
+        rc = head_impl(q_s, P.ks, nullptr, vis_heads, n_vis, B, H, Nt, N1, hd, dtype, N2, P.k2loc,
+                       score2, P.ws_head_b, P.head_b, stream, nullptr, 0, 1, nullptr, nullptr);
+        if (rc != PV_OK) return rc;
+        // survivors of the shallow layer: token indices and merged rows
+        if (pv::launch_compose_index(kept1, P.k2loc, B, N1, N2, kept2, st) != hipSuccess)
+            return PV_ERR_HIP;
+        {
+            const pv_gather_desc g = kv_desc(merged, hidden2, 1, N1, N2, row_h);
+            if ((rc = make_gather(&g, 1, P.k2loc, B, N2, ga)) != PV_OK) return rc;
+            if (pv::launch_gather(ga, P.k2loc, B, N2, st) != hipSuccess) return PV_ERR_HIP;
+        }
     }
     // the middle layer: every head (the all-head aggregation, no head
-    // identification)
+    // identification), on the keys of the survivors
     std::vector<int32_t> all((size_t)B * H);
     for (int b = 0; b < B; ++b)
         for (int h = 0; h < H; ++h) all[(size_t)b * H + h] = h;
-    rc = head_impl(q_m, P.km, all.data(), nullptr, H, B, H, Nt, N2, hd, dtype, N3, P.k3loc,
-                   score3, P.ws_head_c, P.head_c, stream, nullptr, 0, 1, nullptr, nullptr);
-    if (rc != PV_OK) return rc;
-    if (pv::launch_compose_index(kept2, P.k3loc, B, N2, N3, kept3, st) != hipSuccess)
-        return PV_ERR_HIP;
+    const int form3 = pv::score_uses_head_form(dt, B, H, H, Nt, N2, hd)
+                          ? pv::kWholeHead : pv::shared_score_form(dt, B, H, H, Nt, N2, hd);
+    if (form3 != pv::kSharedNone) {  // read through their list
+        const HeadPlan Hc = plan_head((char *)(((uintptr_t)P.ws_head_c + kAlign - 1) / kAlign * kAlign), B,
+                                      Nt, N2, H, score3 == nullptr);
+        const pv::ScoreChain chain{form3, dt, q_m, k_m_all, all.data(), B, H, Nt, N2, Nv, hd, H,
+                                   kept2, Hc.partial, Hc.stats};
+        if (pv::launch_score_chain(chain, st) != hipSuccess) return PV_ERR_HIP;
+        pv::SelectJob sj{Hc.partial, H * (form3 == pv::kSharedRows ? Hc.nrb : 1), N2,
+                         (float)(1.0 / ((double)Nt * (double)H)), score3 ? score3 : Hc.v, N3,
+                         P.k3loc, B, nullptr};
+        sj.base = kept2;
+        sj.composed = kept3;
+        if (pv::launch_select_job(sj, st) != hipSuccess) return PV_ERR_HIP;
+    } else {
+        const pv_gather_desc gk = kv_desc(k_m_all, P.km, H, Nv, N2, row_kv);
+        if ((rc = make_gather(&gk, 1, kept2, B, N2, ga)) != PV_OK) return rc;
+        if (pv::launch_gather(ga, kept2, B, N2, st) != hipSuccess) return PV_ERR_HIP;
+        rc = head_impl(q_m, P.km, all.data(), nullptr, H, B, H, Nt, N2, hd, dtype, N3, P.k3loc,
+                       score3, P.ws_head_c, P.head_c, stream, nullptr, 0, 1, nullptr, nullptr);
+        if (rc != PV_OK) return rc;
+        if (pv::launch_compose_index(kept2, P.k3loc, B, N2, N3, kept3, st) != hipSuccess)
+            return PV_ERR_HIP;
+    }
     {
         const pv_gather_desc g = kv_desc(hidden2, hidden3, 1, N2, N3, row_h);
         if ((rc = make_gather(&g, 1, P.k3loc, B, N3, ga)) != PV_OK) return rc;

@@ -443,11 +443,16 @@ __global__ __launch_bounds__(kScoreNT) void score_partial_kernel(
 // exp2f, on 16-row blocks, took 30.0 us at that size, a rescale of the sums in
 // every chunk 17.0.)
 // ----------------------------------------------------------------------------
-template <int DT, int NKS, int RW, int KW>
+//
+// IDX: key j is row kidx[b][j] of k ([B][H][n_src][hd]), N <= kConfIdx; the
+// list is staged in LDS once.  (8 x 32 heads x 192 of 576 keys: 9.4 us, against
+// 8.5 on compacted keys and 6.4 for the compaction.)
+constexpr int kConfIdx = 2048;
+template <int DT, int NKS, int RW, int KW, bool IDX = false>
 __global__ __launch_bounds__(64 * RW * KW) void head_conf_kernel(
     const char *__restrict__ q, const char *__restrict__ k, const int32_t *__restrict__ row_mask,
     const float *__restrict__ row_lse, int H, int Nt, int N, int row_bytes, float scale_log2e,
-    float *__restrict__ partial) {
+    float *__restrict__ partial, const int32_t *__restrict__ kidx = nullptr, int n_src = 0) {
     using S = ScoreStage<NKS>;
     constexpr int NW = RW * KW, ROWS = 16 * RW;
     constexpr int KB = 4 / KW;  // key blocks of a chunk per wave
@@ -457,6 +462,7 @@ __global__ __launch_bounds__(64 * RW * KW) void head_conf_kernel(
     __shared__ float sm_m[NW][16], sm_l[NW][16], sm_s[NW][16];
     __shared__ float var[RW][16];
     __shared__ int any_row;
+    __shared__ int32_t krow[IDX ? kConfIdx : 1];
     const int nrb = (Nt + 15) / 16, nblk = (Nt + ROWS - 1) / ROWS;
     const int L = xcd_tile(blockIdx.x, gridDim.x);
     const int rb = L % nblk, h = (L / nblk) % H, b = L / (nblk * H);
@@ -464,7 +470,12 @@ __global__ __launch_bounds__(64 * RW * KW) void head_conf_kernel(
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int rw = wave % RW, kw = wave / RW;
     const char *qb = q + ((size_t)b * H + h) * Nt * row_bytes;
-    const char *kb = k + ((size_t)b * H + h) * N * row_bytes;
+    const char *kb = k + ((size_t)b * H + h) * (IDX ? n_src : N) * row_bytes;
+    if constexpr (IDX) {  // ordinary loads, retired before the first direct-to-LDS load
+        for (int i = tid; i < N; i += 64 * NW)
+            krow[i] = min(max(kidx[(size_t)b * N + i], 0), n_src - 1);
+        __syncthreads();
+    }
     const int nch = (N + kScoreCK - 1) / kScoreCK;
 
     int srow[S::IPW], sbyte[S::IPW];
@@ -478,9 +489,11 @@ __global__ __launch_bounds__(64 * RW * KW) void head_conf_kernel(
     auto issue = [&](int ch) {
         char *dst = ring + (ch % S::NS) * S::STAGE + wave * S::IPW * 1024;
 #pragma unroll
-        for (int t = 0; t < S::IPW; ++t)
-            lds_dma16(row_piece(kb, min(ch * kScoreCK + srow[t], N - 1), row_bytes, sbyte[t]),
-                      dst + t * 1024);
+        for (int t = 0; t < S::IPW; ++t) {
+            int row = min(ch * kScoreCK + srow[t], N - 1);
+            if constexpr (IDX) row = lds_read4_now(krow + row);
+            lds_dma16(row_piece(kb, row, row_bytes, sbyte[t]), dst + t * 1024);
+        }
     };
     const bool loads = wave < 4;
     for (int p = wave; loads && p < NKS * RW; p += 4) {  // the query rows, 1 KiB per load
@@ -755,12 +768,12 @@ __device__ __forceinline__ void head_chunk_logits(const char *kb, const uint4 (&
         for (int kq = 0; kq < 4; ++kq) out[kq] = mma16<DT>(qf[s], kf[kq][s], out[kq]);
 }
 
-template <int DT, int NKS>
+template <int DT, int NKS, bool IDX>
 __global__ __launch_bounds__(kScoreNT) void score_head_kernel(
     const char *__restrict__ q, const char *__restrict__ k, HeadArgs8 heads,
     const int32_t *__restrict__ heads_dev, int head_src, const float *__restrict__ row_lse, int b0,
     int H, int Nt, int N, int n_heads, int row_bytes, float scale_log2e,
-    float *__restrict__ partial) {
+    float *__restrict__ partial, const int32_t *__restrict__ kidx, int n_src) {
     using S = ScoreStage<NKS>;
     constexpr int MAXC = kHeadMaxChunks;
     // the key chunks in dynamic LDS, nch of them (so that three workgroups
@@ -779,7 +792,8 @@ __global__ __launch_bounds__(kScoreNT) void score_head_kernel(
         h = (int)((heads.w[e >> 2] >> ((e & 3) * 8)) & 0xFFu);
     }
     const char *qb = q + ((size_t)b * H + h) * Nt * row_bytes;
-    const char *kb = k + ((size_t)b * H + h) * N * row_bytes;
+    // IDX: key j is row kidx[b][j] of k ([B][H][n_src][hd])
+    const char *kb = k + ((size_t)b * H + h) * (IDX ? n_src : N) * row_bytes;
     const int nch = (N + kScoreCK - 1) / kScoreCK;  // <= MAXC (host-checked)
 
     // every load of the kernel is issued up front: this wave's query rows
@@ -791,6 +805,16 @@ __global__ __launch_bounds__(kScoreNT) void score_head_kernel(
     uint4 qf[NKS];
     auto issue = [&](auto full) {
         constexpr bool FULL = decltype(full)::value;
+        int krow[MAXC][S::IPW];
+        if constexpr (IDX) {  // every index first, then the rows they name
+#pragma unroll
+            for (int ch = 0; ch < MAXC; ++ch)
+#pragma unroll
+                for (int t = 0; t < S::IPW; ++t) {
+                    const int r = ((wave * S::IPW + t) * 64 + lane) / S::PPR;
+                    krow[ch][t] = kidx[(size_t)b * N + min(ch * kScoreCK + r, N - 1)];
+                }
+        }
         if (rows_live) {
             const int row = min(wave * 16 + (lane & 15), Nt - 1);
 #pragma unroll
@@ -804,7 +828,8 @@ __global__ __launch_bounds__(kScoreNT) void score_head_kernel(
                 for (int t = 0; t < S::IPW; ++t) {
                     const int pos = (wave * S::IPW + t) * 64 + lane;
                     const int r = pos / S::PPR, slot = pos % S::PPR;
-                    const int row = min(ch * kScoreCK + r, N - 1);  // past the end: last key
+                    int row = min(ch * kScoreCK + r, N - 1);  // past the end: last key
+                    if constexpr (IDX) row = min(max(krow[ch][t], 0), n_src - 1);
                     lds_dma16(row_at<FULL, S::RB>(kb, row, row_bytes, (slot ^ (r & S::SWZ)) << 4),
                               kbuf(ch) + (wave * S::IPW + t) * 1024);
                 }
@@ -1194,15 +1219,16 @@ static hipError_t score_dt(int nks, const ScoreLaunch &a) {
 // 2, 2 / 4, 1 / 4, 2), 32 heads of 128: 4 x 128 rows x 960 keys 24.5 / 16.6 / 17.5 / 15.4;
 // 8 x 64 x 192 11.9 / 7.4 / 6.8 / 7.3; 1 x 64 x 192 (32 workgroups at RW = 4)
 // 5.7 / 5.8 / 6.6 / 7.0; 1 x 128 x 4096 (64 of them) 29 / 39 / 54 / 42.
-template <int DT, int NKS>
+template <int DT, int NKS, bool IDX>
 static hipError_t head_conf_go(const char *q, const char *k, const int32_t *row_mask,
                                const float *row_lse, int B, int H, int Nt, int N, int row_bytes,
-                               float sl2e, float *partial, hipStream_t st) {
+                               float sl2e, float *partial, const int32_t *kidx, int n_src,
+                               hipStream_t st) {
     auto wgs = [&](int rw) { return (long long)((Nt + 16 * rw - 1) / (16 * rw)) * H * B; };
 #define PV_CONF_GO(rw, kw)                                                                         \
-    hipLaunchKernelGGL((head_conf_kernel<DT, NKS, rw, kw>), dim3((unsigned)wgs(rw)),               \
+    hipLaunchKernelGGL((head_conf_kernel<DT, NKS, rw, kw, IDX>), dim3((unsigned)wgs(rw)),               \
                        dim3(64 * rw * kw), 0, st, q, k, row_mask, row_lse, H, Nt, N, row_bytes, sl2e, \
-                       partial)
+                       partial, kidx, n_src)
     // (the query rows of the wider blocks would not fit beside a wide ring)
     if constexpr (NKS <= 8) {
         if (Nt > 32 && wgs(4) >= kConfFill) {
@@ -1232,9 +1258,14 @@ static hipError_t score_head_go(const ScoreLaunch &a) {
                 ha.w[i >> 2] |= (uint32_t)(a.heads_host[(size_t)b0 * a.n_heads + i] & 0xFF)
                                 << ((i & 3) * 8);
         const size_t kbytes = (size_t)((a.N + kScoreCK - 1) / kScoreCK) * ScoreStage<NKS>::STAGE;
-        hipLaunchKernelGGL((score_head_kernel<DT, NKS>), dim3(a.n_heads * nb), dim3(kScoreNT),
-                           kbytes, a.st, (const char *)a.q, (const char *)a.k, ha, a.heads_dev, a.src,
-                           a.row_lse, b0, a.H, a.Nt, a.N, a.n_heads, a.row_bytes, a.sl2e, a.partial);
+#define PV_HEAD_GO(idx)                                                                           \
+    hipLaunchKernelGGL((score_head_kernel<DT, NKS, idx>), dim3(a.n_heads * nb), dim3(kScoreNT),   \
+                       kbytes, a.st, (const char *)a.q, (const char *)a.k, ha, a.heads_dev, a.src, \
+                       a.row_lse, b0, a.H, a.Nt, a.N, a.n_heads, a.row_bytes, a.sl2e, a.partial,  \
+                       a.kidx, a.n_src)
+        if (a.kidx) PV_HEAD_GO(true);
+        else PV_HEAD_GO(false);
+#undef PV_HEAD_GO
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
@@ -1276,8 +1307,11 @@ static hipError_t score_split_go(const ScoreLaunch &a, float2 *stats) {
 
 template <int DT, int NKS>
 static hipError_t score_split_nks(const ScoreLaunch &a, float2 *stats) {
-    return a.row_bytes == NKS * 64 ? score_split_go<true, false, DT, NKS>(a, stats)
-                                   : score_split_go<false, false, DT, NKS>(a, stats);
+    const bool full = a.row_bytes == NKS * 64;
+    if (a.kidx)  // (on whole rows only, see shared_score_form)
+        return full ? score_split_go<true, true, DT, NKS>(a, stats) : hipErrorInvalidValue;
+    return full ? score_split_go<true, false, DT, NKS>(a, stats)
+                : score_split_go<false, false, DT, NKS>(a, stats);
 }
 
 template <int DT>
@@ -1345,12 +1379,38 @@ hipError_t launch_head_conf(int dt, const void *q, const void *k, const int32_t 
     const char *qc = (const char *)q, *kc = (const char *)k;
 #define PV_NKS_CASE(n)                                                                            \
     case n:                                                                                       \
-        return dt == kBF16 ? head_conf_go<kBF16, n>(qc, kc, row_mask, row_lse, B, H, Nt, N,       \
-                                                    row_bytes, sl2e, partial, st)                 \
-                           : head_conf_go<kF32, n>(qc, kc, row_mask, row_lse, B, H, Nt, N,        \
-                                                   row_bytes, sl2e, partial, st);
+        return dt == kBF16 ? head_conf_go<kBF16, n, false>(qc, kc, row_mask, row_lse, B, H, Nt,   \
+                                                           N, row_bytes, sl2e, partial, nullptr,  \
+                                                           0, st)                                 \
+                           : head_conf_go<kF32, n, false>(qc, kc, row_mask, row_lse, B, H, Nt, N, \
+                                                          row_bytes, sl2e, partial, nullptr, 0,   \
+                                                          st);
     switch (head_windows(dt, hd)) { PV_NKS_CASES }
 #undef PV_NKS_CASE
+    return hipErrorInvalidValue;
+}
+
+bool conf_indexed_supported(int dt, int N, int hd) {
+    const int nks = head_windows(dt, hd);
+    return (nks == 2 || nks == 4) && N <= kConfIdx;
+}
+
+hipError_t launch_head_conf_indexed(int dt, const void *q, const void *k_full,
+                                    const int32_t *row_mask, int B, int H, int Nt, int N, int n_src,
+                                    const int32_t *kidx, int hd, float *partial, hipStream_t st) {
+    if (!conf_indexed_supported(dt, N, hd)) return hipErrorInvalidValue;
+    const int row_bytes = hd * ((dt == kBF16) ? 2 : 4), nks = head_windows(dt, hd);
+    const float sl2e = scale_log2e_of(hd);
+    const char *qc = (const char *)q, *kc = (const char *)k_full;
+#define PV_CI_CASE(dtv, n)                                                                        \
+    if (dt == dtv && nks == n)                                                                    \
+        return head_conf_go<dtv, n, true>(qc, kc, row_mask, nullptr, B, H, Nt, N, row_bytes,      \
+                                          sl2e, partial, kidx, n_src, st);
+    PV_CI_CASE(kBF16, 2)
+    PV_CI_CASE(kBF16, 4)
+    PV_CI_CASE(kF32, 2)
+    PV_CI_CASE(kF32, 4)
+#undef PV_CI_CASE
     return hipErrorInvalidValue;
 }
 
@@ -1426,9 +1486,10 @@ __global__ __launch_bounds__(kScoreNT) void reduce_select_gather_kernel(ReduceJo
 // the merge's carry the step 124.1 -> 113.9 us; 2 x 4608 x 10 KB 217.4 -> 204.
 template <int DT, int MAXC>
 __global__ __launch_bounds__(kScoreNT) void assign_score_kernel(
-    const char *__restrict__ q, const char *__restrict__ k_full, HeadArgs heads, int H, int Nt,
-    int N, int n_src, const int32_t *__restrict__ kidx, int n_heads, int row_bytes,
-    float scale_log2e, float *__restrict__ partial, int n_score, AssignJob aj) {
+    const char *__restrict__ q, const char *__restrict__ k_full, HeadArgs heads,
+    const int32_t *__restrict__ heads_dev, int head_src, int H, int Nt, int N, int n_src,
+    const int32_t *__restrict__ kidx, int n_heads, int row_bytes, float scale_log2e,
+    float *__restrict__ partial, int n_score, AssignJob aj) {
     // two chunks, so that four workgroups fit on a CU: with three chunks (two
     // or three workgroups) the argmax's rows had too few waves in flight and the
     // launch took as long as its two halves apart
@@ -1438,8 +1499,8 @@ __global__ __launch_bounds__(kScoreNT) void assign_score_kernel(
         assign_block(aj, (int)blockIdx.x - n_score);
         return;
     }
-    score_partial_block<DT, 4, MAXC, true, NS>(q, k_full, heads, nullptr, kHeadsArg, nullptr, 0, H, Nt, N,
-                                           n_heads, row_bytes, scale_log2e, partial, 0, n_score,
+    score_partial_block<DT, 4, MAXC, true, NS>(q, k_full, heads, heads_dev, head_src, nullptr, 0, H, Nt,
+                                           N, n_heads, row_bytes, scale_log2e, partial, 0, n_score,
                                            kidx, n_src, ring);
 }
 
@@ -1504,7 +1565,7 @@ int shared_score_form(int dt, int B, int H, int n_heads, int Nt, int N, int hd) 
 }
 
 static ScoreLaunch shared_score(const ScoreChain &c) {
-    ScoreLaunch a{c.q, c.k_full, c.heads, nullptr, kHeadsArg, nullptr, c.B, c.H, c.Nt, c.N, c.n_heads,
+    ScoreLaunch a{c.q, c.k_full, c.heads, c.heads_dev, c.heads_dev ? kHeadsDevice : kHeadsArg, nullptr, c.B, c.H, c.Nt, c.N, c.n_heads,
                   c.hd * ((c.dt == kBF16) ? 2 : 4), scale_log2e_of(c.hd), c.partial, nullptr};
     a.kidx = c.kept;
     a.n_src = c.n_src;
@@ -1513,7 +1574,8 @@ static ScoreLaunch shared_score(const ScoreChain &c) {
 
 static HeadArgs shared_heads(const ScoreChain &c) {
     HeadArgs ha;
-    for (int i = 0; i < kMaxHeadArgs; ++i) ha.h[i] = i < c.B * c.n_heads ? c.heads[i] : 0;
+    for (int i = 0; i < kMaxHeadArgs; ++i)
+        ha.h[i] = !c.heads_dev && i < c.B * c.n_heads ? c.heads[i] : 0;
     return ha;
 }
 
@@ -1544,7 +1606,7 @@ hipError_t launch_assign_score(const ScoreChain &c, const AssignJob &aj, hipStre
     if (c.dt == dtv && nch <= mc) {                                                               \
         hipLaunchKernelGGL((assign_score_kernel<dtv, mc>), dim3(n_score + n_assign),              \
                            dim3(kScoreNT), 0, st, (const char *)c.q, (const char *)c.k_full, ha,  \
-                           c.H, c.Nt, c.N, c.n_src, c.kept, c.n_heads, a.row_bytes, a.sl2e,       \
+                           a.heads_dev, a.src, c.H, c.Nt, c.N, c.n_src, c.kept, c.n_heads, a.row_bytes, a.sl2e,       \
                            c.partial, n_score, aj);                                               \
         return hipGetLastError();                                                                 \
     }
@@ -1556,6 +1618,19 @@ hipError_t launch_assign_score(const ScoreChain &c, const AssignJob &aj, hipStre
     PV_AS_CASE(kF32, 4)
 #undef PV_AS_CASE
     return hipErrorInvalidValue;
+}
+
+hipError_t launch_score_chain(const ScoreChain &c, hipStream_t st) {
+    if (c.form == kSharedRows) return launch_assign_score(c, AssignJob{}, st);
+    ScoreLaunch a = shared_score(c);
+    a.st = st;
+    const int nks = head_windows(c.dt, c.hd);
+    if (c.form == kSharedSplit)
+        return c.dt == kBF16 ? score_split_dt<kBF16>(nks, a, (float2 *)c.stats)
+                             : score_split_dt<kF32>(nks, a, (float2 *)c.stats);
+    if (c.form != kWholeHead || (nks != 2 && nks != 4)) return hipErrorInvalidValue;
+    if (c.dt == kBF16) return nks == 2 ? score_head_go<kBF16, 2>(a) : score_head_go<kBF16, 4>(a);
+    return nks == 2 ? score_head_go<kF32, 2>(a) : score_head_go<kF32, 4>(a);
 }
 
 hipError_t launch_bucket_carry(const ScoreChain &c, const BucketJob &bj, const SelectJob &sj,
@@ -1646,11 +1721,10 @@ hipError_t launch_reduce_select_gather(const ReduceJob &rj, const SelectJob &sj,
 // head h added in order; the n_vis heads of largest C (ties to the lower
 // head id) are written in ascending order.
 // ----------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void conf_select_kernel(const float *__restrict__ part, int H,
-                                                          int nrb, float *__restrict__ conf,
-                                                          int n_vis, int32_t *__restrict__ heads) {
+__device__ __forceinline__ void conf_select_block(const float *__restrict__ part, int H, int nrb,
+                                                  float *__restrict__ conf, int n_vis,
+                                                  int32_t *__restrict__ heads, int b) {
     __shared__ TopkSmem sm;
-    const int b = blockIdx.x;
     const int E = topk_per_thread(H, 256), h0 = threadIdx.x * E;
     uint32_t key[2];
 #pragma unroll
@@ -1668,6 +1742,31 @@ __global__ __launch_bounds__(256) void conf_select_kernel(const float *__restric
     block_topk<256, 2>(key, H, n_vis, heads + (size_t)b * n_vis, nullptr, nullptr, sm);
 }
 
+__global__ __launch_bounds__(256) void conf_select_kernel(const float *__restrict__ part, int H,
+                                                          int nrb, float *__restrict__ conf,
+                                                          int n_vis, int32_t *__restrict__ heads) {
+    conf_select_block(part, H, nrb, conf, n_vis, heads, blockIdx.x);
+}
+
+// The same (n_conf workgroups, one per sample) beside the Gram's argmax.
+__global__ __launch_bounds__(256) void assign_conf_kernel(const float *__restrict__ part, int H,
+                                                          int nrb, float *__restrict__ conf,
+                                                          int n_vis, int32_t *__restrict__ heads,
+                                                          int n_conf, AssignJob aj) {
+    if ((int)blockIdx.x < n_conf)
+        conf_select_block(part, H, nrb, conf, n_vis, heads, blockIdx.x);
+    else
+        assign_block(aj, (int)blockIdx.x - n_conf);
+}
+
+hipError_t launch_assign_conf(const AssignJob &aj, const float *partial, int B, int H, int Nt,
+                              float *conf, int n_vis, int32_t *heads, hipStream_t st) {
+    if (H > 512) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(assign_conf_kernel, dim3(B + aj.r.nblocks + aj.f.nblocks), dim3(256), 0, st,
+                       partial, H, (Nt + 15) / 16, conf, n_vis, heads, B, aj);
+    return hipGetLastError();
+}
+
 hipError_t launch_conf_select(const float *partial, int B, int H, int Nt, float *conf, int n_vis,
                               int32_t *heads, hipStream_t st) {
     if (H > 512) return hipErrorInvalidValue;
@@ -1678,11 +1777,15 @@ hipError_t launch_conf_select(const float *partial, int B, int H, int Nt, float 
 
 hipError_t launch_score_select(const float *partial, int B, int nparts, int N, float inv_norm,
                                float *v, int budget, int32_t *kept, hipStream_t st) {
+    return launch_select_job(SelectJob{partial, nparts, N, inv_norm, v, budget, kept, B, nullptr}, st);
+}
+
+hipError_t launch_select_job(const SelectJob &sj, hipStream_t st) {
     // as many threads as keys where possible: each thread's partial sums are
     // then all in flight at once
-    const SelectJob sj{partial, nparts, N, inv_norm, v, budget, kept, 0};
+    const int N = sj.N;
 #define PV_SEL_CASE(nt, e) \
-    hipLaunchKernelGGL((score_select_kernel<nt, e>), dim3(B), dim3(nt), 0, st, sj)
+    hipLaunchKernelGGL((score_select_kernel<nt, e>), dim3(sj.nblocks), dim3(nt), 0, st, sj)
     if (N <= 256)
         PV_SEL_CASE(256, 1);
     else if (N <= 1024)

@@ -227,7 +227,8 @@ __host__ __device__ constexpr int topk_per_thread(int n, int NT) { return (n + N
 // largest keys, lower index first among equal keys, and writes
 //   kept[0..k)       the kept indices, ascending,
 //   rest[0..n-k)     the other indices, ascending (if rest != nullptr),
-//   slot_of[j]       position of j in kept, or -1 (if slot_of != nullptr).
+//   slot_of[j]       position of j in kept, or -1 (if slot_of != nullptr),
+//   composed[0..k)   base[kept[..]] (if composed != nullptr).
 // Thread t owns the E = ceil(n / NT) <= EMAX consecutive indices starting at
 // t * E and passes their keys in key[] (entries past n are ignored).  The keys
 // are order-preserving images of the scores (order_key), so comparing keys
@@ -246,7 +247,8 @@ __host__ __device__ constexpr int topk_per_thread(int n, int NT) { return (n + N
 template <int NT, int EMAX>
 __device__ __forceinline__ void block_topk(const uint32_t (&key)[EMAX], int n, int k,
                                            int32_t *kept, int32_t *rest, int32_t *slot_of,
-                                           TopkSmem &sm) {
+                                           TopkSmem &sm, const int32_t *base = nullptr,
+                                           int32_t *composed = nullptr) {
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     constexpr int NW = NT / 64;
     const int E = topk_per_thread(n, NT);
@@ -352,6 +354,7 @@ __device__ __forceinline__ void block_topk(const uint32_t (&key)[EMAX], int n, i
             if (keep) kept[pos] = j;
             else if (rest) rest[j - pos] = j;
             if (slot_of) slot_of[j] = keep ? pos : -1;
+            if (composed && keep) composed[pos] = base[j];
             gt_before += m > prefix;
             eq_before += m == prefix;
         }

@@ -459,6 +459,8 @@ struct SelectJob {
     int32_t *kept;         // [B][budget]
     int nblocks;           // samples carried by another launch; 0: none
     int32_t *slot_of;      // [B][N] position of each column in kept, or -1 (may be NULL)
+    const int32_t *base = nullptr;  // [B][N], with composed [B][budget] = base[kept]
+    int32_t *composed = nullptr;    // (may be NULL)
 };
 
 // inv_norm x the partials of column j added in part order, loaded in blocks
@@ -517,7 +519,9 @@ __device__ __forceinline__ void score_select_block(const SelectJob &sj, int b, T
         }
     }
     block_topk<NT, EMAX>(key, N, sj.budget, sj.kept + (size_t)b * sj.budget, nullptr,
-                         sj.slot_of ? sj.slot_of + (size_t)b * N : nullptr, sm);
+                         sj.slot_of ? sj.slot_of + (size_t)b * N : nullptr, sm,
+                         sj.composed ? sj.base + (size_t)b * N : nullptr,
+                         sj.composed ? sj.composed + (size_t)b * sj.budget : nullptr);
 }
 
 // What the merge launch of the one-call step carries besides the merge: the

@@ -69,6 +69,14 @@ __device__ __forceinline__ uint4 lds_read16(const char *p) {
     asm volatile("ds_read_b128 %0, %1" : "=v"(r) : "v"(addr) : "memory");
     return uint4{r.x, r.y, r.z, r.w};
 }
+// Four bytes, waited for in place: an ordinary LDS read would first drain every
+// direct-to-LDS load in flight.
+__device__ __forceinline__ int lds_read4_now(const int32_t *p) {
+    int r;
+    const unsigned addr = (unsigned)(uintptr_t)p;
+    asm volatile("ds_read_b32 %0, %1\n\ts_waitcnt lgkmcnt(0)" : "=v"(r) : "v"(addr) : "memory");
+    return r;
+}
 __device__ __forceinline__ void lds_wait() { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); }
 // Wait until at most N LDS reads of this wave are outstanding (they complete
 // in issue order; N <= 15).

@@ -1,0 +1,75 @@
+"""The schedule with the score chain on the launches of the dedup's, keys read through the
+kept lists, against the library's calls made in turn (which read compacted keys): the same
+bits in every output, over the forms that either side can take."""
+
+from __future__ import annotations
+
+import numpy as np
+import pytest
+
+from paper_2608_25332_amd import workloads as W
+from parity_util import to_dev
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _gpu():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+
+
+# (B, Nv, Nt, d, H, hd, N1, n_vis, N2, N3, dtype): the shallow layer's form / the middle layer's
+FORMS = [
+    (4, 300, 64, 256, 32, 128, 130, 6, 65, 20, "bf16"),    # 16-row blocks / whole heads, N2 past a chunk
+    (2, 300, 17, 256, 4, 104, 100, 2, 64, 64, "bf16"),     # rows of 208 bytes / 16-row blocks
+    (3, 257, 33, 72, 6, 64, 256, 6, 256, 1, "f32"),        # the widest lists of both, one token pruned
+    (2, 2500, 20, 64, 8, 64, 900, 2, 300, 100, "bf16"),    # split / split, 1024-thread member lists
+    (1, 3000, 40, 64, 4, 32, 2048, 1, 257, 9, "f32"),      # the longest list of the confidence
+    (1, 3000, 40, 64, 4, 32, 2049, 1, 257, 9, "f32"),      # one past it: calls in turn
+    (16, 200, 70, 64, 16, 128, 100, 8, 50, 20, "bf16"),    # 128 pairs of more than 64 rows
+    (16, 200, 40, 64, 16, 128, 100, 8, 50, 20, "bf16"),    # whole heads on both layers
+    (2, 400, 9, 128, 6, 80, 200, 3, 70, 20, "bf16"),       # a width of neither: calls in turn
+    (1, 90, 8, 1024, 4, 128, 30, 2, 20, 5, "bf16"),        # the plain merge: calls in turn
+    (2, 128, 8, 64, 4, 128, 128, 2, 20, 5, "bf16"),        # nothing pruned before the layers
+]
+
+
+@pytest.mark.parametrize("B,Nv,Nt,d,H,hd,N1,n_vis,N2,N3,dt", FORMS)
+def test_progressive_forms_equal_the_calls(B, Nv, Nt, d, H, hd, N1, n_vis, N2, N3, dt):
+    from paper_2608_25332_amd import provip
+    print(f"[progressive form] B={B} Nv={Nv} Nt={Nt} d={d} H={H} hd={hd} {N1}/{n_vis}/{N2}/{N3} {dt}", flush=True)
+    rng = np.random.default_rng(B * 100 + Nv + N1)
+
+    def draw(*shape, scale=1.0):
+        x = rng.standard_normal(shape, dtype=np.float32) * np.float32(scale)
+        return to_dev(W.bf16_round(x) if dt == "bf16" else x, dt)
+
+    text, vis = draw(B, Nt, d, scale=0.1), draw(B, Nv, d)
+    q_s, k_s, q_m, k_m = (draw(B, H, n, hd) for n in (Nt, Nv, Nt, Nv))
+    o = provip.pv_prune_progressive(text, vis, q_s, k_s, q_m, k_m, N1, n_vis, N2, N3)
+    for n, t in o.items():
+        if n != "workspace":
+            t.view(torch.uint8).fill_(0x5A)
+    o["workspace"].fill_(0xFF)
+    ws = o.pop("workspace")
+    provip.pv_prune_progressive(text, vis, q_s, k_s, q_m, k_m, N1, n_vis, N2, N3, out=o, workspace=ws)
+    ct = provip.pv_critical_text(text)
+    d1 = provip.pv_prune_dedup(vis, text, N1, want_score=False, anchor_mask=ct["mask"])
+    ks = provip.pv_prune_gather(k_s, d1["kept"])
+    vh = provip.pv_visual_heads(q_s, ks, n_vis, row_mask=ct["mask"])
+    h2 = provip.pv_prune_head_aware(q_s, ks, vh["heads"], N2)
+    kept2 = torch.gather(d1["kept"], 1, h2["kept"].long()).to(torch.int32)
+    hid2 = provip.pv_prune_gather(d1["merged"], h2["kept"])
+    every = np.tile(np.arange(H, dtype=np.int32), (B, 1))
+    h3 = provip.pv_prune_head_aware(q_m, provip.pv_prune_gather(k_m, kept2), every, N3)
+    kept3 = torch.gather(kept2, 1, h3["kept"].long()).to(torch.int32)
+    torch.cuda.synchronize()
+    want = {"text_mask": ct["mask"], "kept1": d1["kept"], "assign": d1["assign"],
+            "merged": d1["merged"], "vis_heads": vh["heads"], "conf": vh["conf"], "kept2": kept2,
+            "score2": h2["score"], "hidden2": hid2, "kept3": kept3, "score3": h3["score"],
+            "hidden3": provip.pv_prune_gather(hid2, h3["kept"])}
+    for n, t in want.items():
+        assert torch.equal(o[n].view(torch.uint8), t.view(torch.uint8)), n
