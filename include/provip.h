@@ -32,11 +32,9 @@
  *   - Results are deterministic: two calls on the same inputs return the same
  *     bits (no floating-point atomics; every reduction has a fixed order).
  *   - Widths: an embedding width d or head width hd may be any multiple of 8
- *     in range.  The matrix-core kernels stream 128-byte chunks of embedding
- *     rows; a call whose embedding rows have another width first copies them,
- *     zero-padded, into its workspace (zeros change no dot product and no
- *     norm), and the workspace queries include those copies.  Head rows of
- *     any such width are read in place.
+ *     in range; rows are read in place whatever their width (the pieces that
+ *     the kernels stream past a row's end count as zeros, which change no dot
+ *     product and no norm).
  */
 #ifndef PROVIP_H
 #define PROVIP_H

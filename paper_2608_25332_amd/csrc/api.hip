@@ -37,14 +37,6 @@ bool aligned16(const void *p) { return ((uintptr_t)p & 15u) == 0; }
 
 size_t round_up(size_t x) { return (x + kAlign - 1) / kAlign * kAlign; }
 
-// Widths the matrix-core kernels stream: embedding rows in 128-byte k chunks,
-// head rows in multiples of 32 elements.  An embedding row of another width
-// (any multiple of 8 elements) is copied into a zero-padded row of the next
-// such width first; the head kernels read zeros past the end of a row.  Zeros
-// change no dot product and no norm.
-int padded_d(int d, int esz) { return (d * esz + 127) / 128 * 128 / esz; }
-int padded_hd(int hd) { return (hd + 31) / 32 * 32; }
-
 // Launches the kernels of one call.  With events, events[i] is recorded
 // before kernel i and events[n] after the last one; with reps > 1 every
 // kernel is launched reps times back to back between its two events (the
@@ -118,7 +110,7 @@ struct DedupPlan {
 DedupPlan plan_dedup(void *ws, int B, int Nv, int Nt, int d, int esz, int budget, bool want_p,
                      bool want_assign, bool want_merged) {
     DedupPlan P;
-    P.nch = d * esz / 128;
+    P.nch = (d * esz + 127) / 128;
     const int T = pv::kSplitTile;
     // wide cosine tiles: two workgroups per CU (512 for the chip)
     P.ks_cos = pv::cos_uses_wide_tiles(Nt, Nv)
@@ -200,15 +192,11 @@ DedupPlan plan_dedup(void *ws, int B, int Nv, int Nt, int d, int esz, int budget
     return P;
 }
 
-// Workspace of a dedup call: its plan at the streamed width, plus the padded
-// copies of the visual tokens and the anchors when d is not that width.
 size_t dedup_total_bytes(int B, int Nv, int Nt, int d, int esz, int budget, bool want_p,
                          bool want_assign, bool want_merged) {
-    const int dp = padded_d(d, esz);
-    size_t b = round_up(plan_dedup(nullptr, B, Nv, Nt, dp, esz, budget, want_p, want_assign,
-                                   want_merged).bytes);
-    if (dp != d) b += round_up((size_t)B * Nv * dp * esz) + round_up((size_t)B * Nt * dp * esz);
-    return b + kAlign;
+    return round_up(plan_dedup(nullptr, B, Nv, Nt, d, esz, budget, want_p, want_assign,
+                               want_merged).bytes) +
+           kAlign;
 }
 
 int check_dedup(const void *vis, const void *anchors, int B, int Nv, int Nt, int d, int dtype,
@@ -305,7 +293,6 @@ int dedup_impl(const void *vis, const void *anchors, int B, int Nv, int Nt, int 
     if (anchor_mask && (uintptr_t)anchor_mask % 4) return PV_ERR_ALIGN;
     const bool need_assign = assign != nullptr || merged != nullptr;
     const int esz = (dtype == PV_BF16) ? 2 : 4;
-    const int dp = padded_d(d, esz);  // the width the products stream
     if (!workspace) return PV_ERR_WORKSPACE;
     if (ws_bytes < dedup_total_bytes(B, Nv, Nt, d, esz, budget, score == nullptr,
                                      need_assign && !assign, merged != nullptr))
@@ -315,7 +302,7 @@ int dedup_impl(const void *vis, const void *anchors, int B, int Nv, int Nt, int 
         if (p && !aligned16(p)) return PV_ERR_ALIGN;
     // carve from a 256-aligned start
     char *wsa = (char *)(((uintptr_t)workspace + kAlign - 1) / kAlign * kAlign);
-    DedupPlan P = plan_dedup(wsa, B, Nv, Nt, dp, esz, budget, score == nullptr,
+    DedupPlan P = plan_dedup(wsa, B, Nv, Nt, d, esz, budget, score == nullptr,
                              need_assign && !assign, merged != nullptr);
     float *p = score ? score : P.p;
     int32_t *asg = assign ? assign : P.assign;
@@ -323,22 +310,7 @@ int dedup_impl(const void *vis, const void *anchors, int B, int Nv, int Nt, int 
     hipStream_t st = (hipStream_t)stream;
     Trace tr{events, n_events, names, reps, st};
     if (!tr.handles_ok()) return PV_ERR_NULL;
-    // the rows the products read: the inputs, or their zero-padded copies
-    const void *vis_k = vis, *anc_k = anchors;
-    if (dp != d) {
-        char *vp = wsa + round_up(P.bytes);
-        char *ap = vp + round_up((size_t)B * Nv * dp * esz);
-        if (!tr.launch("pad", [&] {
-                return pv::launch_pad_rows(vis, vp, (long long)B * Nv, d * esz, dp * esz, st);
-            }) ||
-            !tr.launch("pad", [&] {
-                return pv::launch_pad_rows(anchors, ap, (long long)B * Nt, d * esz, dp * esz, st);
-            }))
-            return PV_ERR_HIP;
-        vis_k = vp;
-        anc_k = ap;
-    }
-    if (!launch_front(tr, P, dt, vis_k, anc_k, anchor_mask, B, Nv, Nt, dp, budget, p, kept,
+    if (!launch_front(tr, P, dt, vis, anchors, anchor_mask, B, Nv, Nt, d, budget, p, kept,
                       need_assign ? asg : nullptr, st))
         return PV_ERR_HIP;
     hipStream_t sm = st;  // stream of the assignment and merge kernels
@@ -357,7 +329,7 @@ int dedup_impl(const void *vis, const void *anchors, int B, int Nv, int Nt, int 
     if (need_assign && P.Mp > 0) {
         if (P.gram_big) {
             if (!tr.launch("gram_tile", [&] {
-                    return pv::launch_gram_tile(dt, vis_k, B, Nv, dp, kept, budget, P.pruned, P.Mp,
+                    return pv::launch_gram_tile(dt, vis, B, Nv, d, kept, budget, P.pruned, P.Mp,
                                                 P.invn, P.best_val, P.best_slot, asg, sm);
                 }))
                 return PV_ERR_HIP;
@@ -376,7 +348,7 @@ int dedup_impl(const void *vis, const void *anchors, int B, int Nv, int Nt, int 
             }
         } else {
             if (!tr.launch("gram_partial", [&] {
-                    return pv::launch_gram_partial(dt, vis_k, B, Nv, dp, kept, budget, P.pruned,
+                    return pv::launch_gram_partial(dt, vis, B, Nv, d, kept, budget, P.pruned,
                                                    P.Mp, P.ks_gram, P.gpart, P.gram_wide, sm);
                 }))
                 return PV_ERR_HIP;
@@ -566,18 +538,13 @@ struct TextPlan {
 
 TextPlan plan_text(void *ws, int B, int Nt, int d, int esz);
 
-// Workspace of the critical-text call, with a zero-padded copy of the text
-// rows when d is not a streamed width.
 size_t text_total_bytes(int B, int Nt, int d, int esz) {
-    const int dp = padded_d(d, esz);
-    size_t b = round_up(plan_text(nullptr, B, Nt, dp, esz).bytes);
-    if (dp != d) b += round_up((size_t)B * Nt * dp * esz);
-    return b + kAlign;
+    return round_up(plan_text(nullptr, B, Nt, d, esz).bytes) + kAlign;
 }
 
 TextPlan plan_text(void *ws, int B, int Nt, int d, int esz) {
     TextPlan P;
-    const int nch = d * esz / 128;
+    const int nch = (d * esz + 127) / 128;
     const bool wide = pv::cos_uses_wide_tiles(Nt, Nt);
     const long long n = (Nt + (wide ? pv::kWideTile : pv::kSplitTile) - 1) /
                         (wide ? pv::kWideTile : pv::kSplitTile);
@@ -607,25 +574,15 @@ int text_impl(const void *text, int B, int Nt, int d, int dtype, int32_t *mask, 
                           (const void *)workspace})
         if (p && !aligned16(p)) return PV_ERR_ALIGN;
     char *wsa = (char *)(((uintptr_t)workspace + kAlign - 1) / kAlign * kAlign);
-    const int dp = padded_d(d, esz);  // the width the product streams
-    TextPlan P = plan_text(wsa, B, Nt, dp, esz);
+    TextPlan P = plan_text(wsa, B, Nt, d, esz);
     const int dt = (dtype == PV_BF16) ? pv::kBF16 : pv::kF32;
     hipStream_t st = (hipStream_t)stream;
     Trace tr{events, n_events, names, reps, st};
     if (!tr.handles_ok()) return PV_ERR_NULL;
-    const void *text_k = text;
-    if (dp != d) {
-        char *tp = wsa + round_up(P.bytes);
-        if (!tr.launch("pad", [&] {
-                return pv::launch_pad_rows(text, tp, (long long)B * Nt, d * esz, dp * esz, st);
-            }))
-            return PV_ERR_HIP;
-        text_k = tp;
-    }
     // E E^T: the text rows are both operands
     if (!tr.launch("text_gram", [&] {
-            return P.ks ? pv::launch_text_gram(dt, text_k, B, Nt, dp, P.ks, P.part, st)
-                        : pv::launch_text_gram_stream(text_k, B, Nt, dp, P.G, st);
+            return P.ks ? pv::launch_text_gram(dt, text, B, Nt, d, P.ks, P.part, st)
+                        : pv::launch_text_gram_stream(text, B, Nt, d, P.G, st);
         }))
         return PV_ERR_HIP;
     if (!tr.launch("text_rows", [&] {
@@ -1066,7 +1023,7 @@ int pipeline_impl(const void *vis, const void *anchors, const void *q, const voi
     // the split-k Gram and the plain merge, and the score its 16-row blocks
     // with every logit in registers (the same kernels' arithmetic as the
     // separate calls, so the same bits)
-    const bool carry = !force_separate && padded_d(d, esz) == d && padded_hd(hd) == hd &&
+    const bool carry = !force_separate && d * esz % 128 == 0 && hd % 32 == 0 &&
                        P.Mp > 0 && !P.gram_big && !P.gram_wide && !P.lists && N1 <= 256 &&
                        pv::gram_score_supported(dt, B, n_heads, N1, hd) &&
                        !pv::score_uses_head_form(dt, B, H, n_heads, Nt, N1, hd) &&
@@ -1075,7 +1032,7 @@ int pipeline_impl(const void *vis, const void *anchors, const void *q, const voi
     // launches of the argmax and of the member lists
     const int form = pv::shared_score_form(dt, B, H, n_heads, Nt, N1, hd);
     if (!force_separate && !carry && P.Mp > 0 && form != pv::kSharedNone &&
-        pv::merge_uses_lists(B, N1, padded_d(d, esz) * esz)) {
+        pv::merge_uses_lists(B, N1, d * esz)) {
         const HeadPlan Hh = plan_head(ws_head, B, Nt, N1, n_heads, false);
         const int parts = n_heads * (form == pv::kSharedRows ? Hh.nrb : 1);
         const float inv_norm = (float)(1.0 / ((double)Nt * (double)n_heads));
@@ -1297,7 +1254,7 @@ int progressive_impl(const void *text, const void *vis, const void *q_s, const v
     const int form = pv::shared_score_form(dt, B, H, n_vis, Nt, N1, hd);
     if (N1 < Nv && form != pv::kSharedNone && pv::conf_indexed_supported(dt, N1, hd) &&
         (form == pv::kSharedRows || N1 <= pv::kMergeSelCols * 256) &&
-        pv::merge_uses_lists(B, N1, padded_d(d, esz) * esz)) {
+        pv::merge_uses_lists(B, N1, d * esz)) {
         const bool rows = form == pv::kSharedRows;
         const HeadPlan Hb = plan_head((char *)(((uintptr_t)P.ws_head_b + kAlign - 1) / kAlign * kAlign), B,
                                       Nt, N1, n_vis, score2 == nullptr);

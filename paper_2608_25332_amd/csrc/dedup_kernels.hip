@@ -28,6 +28,8 @@
 #include <math.h>
 #include <string.h>
 
+#include <type_traits>
+
 namespace pv {
 
 // cos_partial: 1-D grid over (sample, k slice, anchor tile, token tile) in XCD
@@ -40,7 +42,7 @@ namespace pv {
 // (three workgroups per CU), or 128 with two stages (two per CU) when there
 // are more than 64 anchors, which then halves the rows each CU loads per
 // output.
-template <int DT, int NS, int BT>
+template <int DT, int NS, int BT, bool TAIL>
 __global__ __launch_bounds__(256) void cos_partial_kernel(
     const char *__restrict__ vis, const char *__restrict__ anchors, int B, int Nv, int Nt,
     int d_bytes, int njt, int nit, int KS, float *__restrict__ part, float *__restrict__ ssv,
@@ -62,11 +64,11 @@ __global__ __launch_bounds__(256) void cos_partial_kernel(
         if (r < BT) return abase + (size_t)min(i0 + r, Nt - 1) * d_bytes;
         return vbase + (size_t)min(j0 + r - BT, Nv - 1) * d_bytes;
     };
-    const int nch = d_bytes / G::CHUNK;
+    const int nch = G::chunks(d_bytes);
     const int c0 = (int)(((long long)nch * ks) / KS), c1 = (int)(((long long)nch * (ks + 1)) / KS);
     f32x4_t acc[G::FM][G::FN];
     float sa[G::FM], sb[G::FN];
-    G::template run<true>(row_ptr, c0, c1, acc, sa, sb, jt == 0, it == 0);
+    G::template run<true, TAIL>(row_ptr, d_bytes, c0, c1, acc, sa, sb, jt == 0, it == 0);
     const size_t kb = (size_t)ks * B + b;
     float *pb = part + kb * Nt * Nv;
 #pragma unroll
@@ -168,7 +170,7 @@ __global__ __launch_bounds__(256) void cos_reduce_kernel(
 // ----------------------------------------------------------------------------
 constexpr int kFT = 16;   // tile edge
 
-template <int DT, int NW, int kFNS>
+template <int DT, int NW, int kFNS, bool TAIL>
 __global__ __launch_bounds__(64 * NW) void cos_full_kernel(
     const char *__restrict__ vis, const char *__restrict__ anchors, int Nv, int Nt, int d_bytes,
     int nit, int njt, float *__restrict__ M, float *__restrict__ rowsum,
@@ -188,7 +190,7 @@ __global__ __launch_bounds__(64 * NW) void cos_full_kernel(
     const int i0 = it * kFT, j0 = jt * kFT;
     const char *abase = anchors + (size_t)b * Nt * d_bytes;
     const char *vbase = vis + (size_t)b * Nv * d_bytes;
-    const int nch = d_bytes / 128;
+    const int nch = (d_bytes + 127) / 128;
     const int c0 = nch * wave / NW, c1 = nch * (wave + 1) / NW;
     const int nc = c1 - c0;
 
@@ -204,9 +206,16 @@ __global__ __launch_bounds__(64 * NW) void cos_full_kernel(
     }
     auto issue = [&](int i) {
         char *dst = ring[wave][i % kFNS];
+        const int at = (c0 + i) * 128;
+        if (!TAIL || at + 128 <= d_bytes) {
 #pragma unroll
-        for (int q = 0; q < IPW; ++q)
-            lds_dma16(src[q] + (size_t)i * 128, dst + q * 1024);
+            for (int q = 0; q < IPW; ++q) lds_dma16(src[q] + (size_t)i * 128, dst + q * 1024);
+        } else {  // the row's last chunk: zeros past its end
+            const int off = ((lane & 7) ^ ((lane >> 3) & 7)) << 4;
+#pragma unroll
+            for (int q = 0; q < IPW; ++q)
+                lds_dma16(at + off < d_bytes ? src[q] + (size_t)i * 128 : zero16(), dst + q * 1024);
+        }
     };
 #pragma unroll
     for (int pp = 0; pp < kFNS - 1; ++pp)
@@ -674,12 +683,12 @@ __global__ __launch_bounds__(kFinNT) void gram_finish_kernel(FinishJob j) {
     gram_finish_row(j, blockIdx.x * kFinNT + threadIdx.x, blockIdx.y);
 }
 
-template <int DT, int NS, int BM, int BN>
+template <int DT, int NS, int BM, int BN, bool TAIL>
 __global__ __launch_bounds__(256) void gram_partial_kernel(
     const char *__restrict__ vis, int B, int Nv, int d_bytes, const int32_t *__restrict__ kept,
     int N1, const int32_t *__restrict__ pruned, int Mp, int ntm, int ntn, int KS,
     float *__restrict__ part) {
-    gram_partial_tile<DT, NS, false, BM, BN>(vis, B, Nv, d_bytes, kept, N1, pruned, Mp, ntm, ntn,
+    gram_partial_tile<DT, NS, TAIL, false, BM, BN>(vis, B, Nv, d_bytes, kept, N1, pruned, Mp, ntm, ntn,
                                              KS, part, B * KS * ntn * ntm, blockIdx.x);
 }
 
@@ -704,7 +713,7 @@ __global__ __launch_bounds__(128) void gram_reduce_kernel(ReduceJob j) {
 // another stream's copies share the CU's load path.
 // Writes the best (cosine, slot) of every pruned row within this kept tile,
 // or the slot itself when there is only one kept tile.
-template <int DT, int BM, int BN, int WM, int WN, int NS, int NP>
+template <int DT, int BM, int BN, int WM, int WN, int NS, int NP, bool TAIL>
 __global__ __launch_bounds__(64 * (WM * WN + NP)) void gram_tile_kernel(
     const char *__restrict__ vis, int Nv, int d_bytes, const int32_t *__restrict__ kept, int N1,
     const int32_t *__restrict__ pruned, int Mp, const float *__restrict__ invn, int ntm, int ntn,
@@ -737,7 +746,7 @@ __global__ __launch_bounds__(64 * (WM * WN + NP)) void gram_tile_kernel(
     __shared__ __attribute__((aligned(16))) char ring[G::LDS_BYTES];
     // matrix waves past the last pruned row or kept slot of an edge tile skip
     // their MFMAs (the epilogue ignores those rows and slots)
-    G::template run_pc<NP>(ring, row_ptr, 0, d_bytes / G::CHUNK, acc, Mp - m0, N1 - n0);
+    G::template run_pc<NP, TAIL>(ring, row_ptr, d_bytes, 0, G::chunks(d_bytes), acc, Mp - m0, N1 - n0);
 
     // producer waves hold no products
     if (__builtin_amdgcn_readfirstlane(wave) < WM * WN) {
@@ -1112,14 +1121,24 @@ __global__ __launch_bounds__(256) void cos_reduce4_kernel(
 // ----------------------------------------------------------------------------
 // launchers
 // ----------------------------------------------------------------------------
+// f(true) for rows that end within a 128-byte chunk, else f(false).
+template <typename F>
+static void with_tail(int d_bytes, F f) {
+    if (d_bytes % 128 != 0) f(std::true_type{});
+    else f(std::false_type{});
+}
+
 template <int DT, int NS, int BT>
 static void cos_partial_go(const void *vis, const void *anchors, int B, int Nv, int Nt,
                            int d_bytes, int KS, float *part, float *ssv, float *ssa,
                            hipStream_t st) {
     const int njt = (Nv + BT - 1) / BT, nit = (Nt + BT - 1) / BT;
     const dim3 grid(B * KS * nit * njt);
-    hipLaunchKernelGGL((cos_partial_kernel<DT, NS, BT>), grid, dim3(256), 0, st, (const char *)vis,
-                       (const char *)anchors, B, Nv, Nt, d_bytes, njt, nit, KS, part, ssv, ssa);
+    with_tail(d_bytes, [&](auto tail) {
+        hipLaunchKernelGGL((cos_partial_kernel<DT, NS, BT, decltype(tail)::value>), grid, dim3(256), 0,
+                           st, (const char *)vis, (const char *)anchors, B, Nv, Nt, d_bytes, njt, nit,
+                           KS, part, ssv, ssa);
+    });
 }
 
 hipError_t launch_cos_partial(int dt, const void *vis, const void *anchors, int B, int Nv, int Nt,
@@ -1181,14 +1200,17 @@ hipError_t launch_cos_full(int dt, const void *vis, const void *anchors, int B, 
     const int d_bytes = d * ((dt == kBF16) ? 2 : 4);
     const int nit = (Nt + kFT - 1) / kFT, njt = (Nv + kFT - 1) / kFT;
     const dim3 grid(B * nit * njt);
-    if (dt == kBF16)
-        hipLaunchKernelGGL((cos_full_kernel<kBF16, kFullW, kFullNS>), grid, dim3(64 * kFullW), 0, st,
-                           (const char *)vis, (const char *)anchors, Nv, Nt, d_bytes, nit, njt, M,
-                           rowsum, invn);
-    else
-        hipLaunchKernelGGL((cos_full_kernel<kF32, kFullW, kFullNS>), grid, dim3(64 * kFullW), 0, st,
-                           (const char *)vis, (const char *)anchors, Nv, Nt, d_bytes, nit, njt, M,
-                           rowsum, invn);
+    with_tail(d_bytes, [&](auto tail) {
+        constexpr bool TAIL = decltype(tail)::value;
+        if (dt == kBF16)
+            hipLaunchKernelGGL((cos_full_kernel<kBF16, kFullW, kFullNS, TAIL>), grid, dim3(64 * kFullW),
+                               0, st, (const char *)vis, (const char *)anchors, Nv, Nt, d_bytes, nit,
+                               njt, M, rowsum, invn);
+        else
+            hipLaunchKernelGGL((cos_full_kernel<kF32, kFullW, kFullNS, TAIL>), grid, dim3(64 * kFullW),
+                               0, st, (const char *)vis, (const char *)anchors, Nv, Nt, d_bytes, nit,
+                               njt, M, rowsum, invn);
+    });
     return hipGetLastError();
 }
 
@@ -1220,7 +1242,7 @@ hipError_t launch_cos_stream(int dt, const void *vis, const void *anchors, int B
 // text_gram: the self-similarity of the text rows on split-k tiles of the
 // upper triangle (it equals its transpose bit for bit, so each product is
 // formed once): partial products part[ks][b][i][j] and [j][i].
-template <int DT, int NS, int BT>
+template <int DT, int NS, int BT, bool TAIL>
 __global__ __launch_bounds__(256) void text_gram_kernel(const char *__restrict__ text, int B, int Nt,
                                                         int d_bytes, int nt, int KS,
                                                         float *__restrict__ part) {
@@ -1238,11 +1260,11 @@ __global__ __launch_bounds__(256) void text_gram_kernel(const char *__restrict__
     auto row_ptr = [&](int r) -> const char * {
         return base + (size_t)min(r < BT ? i0 + r : j0 + r - BT, Nt - 1) * d_bytes;
     };
-    const int nch = d_bytes / G::CHUNK;
+    const int nch = G::chunks(d_bytes);
     const int c0 = (int)(((long long)nch * ks) / KS), c1 = (int)(((long long)nch * (ks + 1)) / KS);
     f32x4_t acc[G::FM][G::FN];
     float sa[G::FM], sb[G::FN];
-    G::template run<false>(row_ptr, c0, c1, acc, sa, sb);
+    G::template run<false, TAIL>(row_ptr, d_bytes, c0, c1, acc, sa, sb);
     float *pb = part + ((size_t)ks * B + b) * Nt * Nt;
 #pragma unroll
     for (int fm = 0; fm < G::FM; ++fm)
@@ -1266,16 +1288,19 @@ hipError_t launch_text_gram(int dt, const void *text, int B, int Nt, int d, int 
     const int T = cos_uses_wide_tiles(Nt, Nt) ? kWideTile : kSplitTile;
     const int nt = (Nt + T - 1) / T;
     const dim3 grid(B * KS * (nt * (nt + 1) / 2));
-#define PV_TEXT_CASE(d, ns, t) \
-    hipLaunchKernelGGL((text_gram_kernel<d, ns, t>), grid, dim3(256), 0, st, (const char *)text, B, Nt, \
-                       d_bytes, nt, KS, part)
-    if (dt == kBF16) {
-        if (T == kWideTile) PV_TEXT_CASE(kBF16, 2, kWideTile);
-        else PV_TEXT_CASE(kBF16, kSplitNS, kPT);
-    } else {
-        if (T == kWideTile) PV_TEXT_CASE(kF32, 2, kWideTile);
-        else PV_TEXT_CASE(kF32, kSplitNS, kPT);
-    }
+#define PV_TEXT_CASE(d, ns, t)                                                                     \
+    hipLaunchKernelGGL((text_gram_kernel<d, ns, t, TAIL>), grid, dim3(256), 0, st, (const char *)text, \
+                       B, Nt, d_bytes, nt, KS, part)
+    with_tail(d_bytes, [&](auto tail) {
+        constexpr bool TAIL = decltype(tail)::value;
+        if (dt == kBF16) {
+            if (T == kWideTile) PV_TEXT_CASE(kBF16, 2, kWideTile);
+            else PV_TEXT_CASE(kBF16, kSplitNS, kPT);
+        } else {
+            if (T == kWideTile) PV_TEXT_CASE(kF32, 2, kWideTile);
+            else PV_TEXT_CASE(kF32, kSplitNS, kPT);
+        }
+    });
 #undef PV_TEXT_CASE
     return hipGetLastError();
 }
@@ -1323,10 +1348,13 @@ static hipError_t gram_tile_go(const void *vis, int B, int Nv, int d, const int3
     const int esz = (DT == kBF16) ? 2 : 4;
     const int ntn = (N1 + kGramTileN - 1) / kGramTileN;
     const int ntm = (Mp + kGramTileM - 1) / kGramTileM;
-    hipLaunchKernelGGL((gram_tile_kernel<DT, kGramTileM, kGramTileN, 4, 2, 3, kGramProducers>),
-                       dim3(B * ntm * ntn), dim3(64 * (8 + kGramProducers)), 0, st,
-                       (const char *)vis, Nv, d * esz, kept, N1, pruned, Mp, invn, ntm, ntn,
-                       best_val, best_slot, assign);
+    with_tail(d * esz, [&](auto tail) {
+        hipLaunchKernelGGL((gram_tile_kernel<DT, kGramTileM, kGramTileN, 4, 2, 3, kGramProducers,
+                                             decltype(tail)::value>),
+                           dim3(B * ntm * ntn), dim3(64 * (8 + kGramProducers)), 0, st,
+                           (const char *)vis, Nv, d * esz, kept, N1, pruned, Mp, invn, ntm, ntn,
+                           best_val, best_slot, assign);
+    });
     return hipGetLastError();
 }
 
@@ -1335,9 +1363,11 @@ static void gram_partial_go(const void *vis, int B, int Nv, int d_bytes, const i
                             int N1, const int32_t *pruned, int Mp, int KS, float *part,
                             hipStream_t st) {
     const int ntm = (Mp + BM - 1) / BM, ntn = (N1 + BN - 1) / BN;
-    hipLaunchKernelGGL((gram_partial_kernel<DT, NS, BM, BN>), dim3(B * KS * ntm * ntn), dim3(256),
-                       0, st, (const char *)vis, B, Nv, d_bytes, kept, N1, pruned, Mp, ntm, ntn,
-                       KS, part);
+    with_tail(d_bytes, [&](auto tail) {
+        hipLaunchKernelGGL((gram_partial_kernel<DT, NS, BM, BN, decltype(tail)::value>),
+                           dim3(B * KS * ntm * ntn), dim3(256), 0, st, (const char *)vis, B, Nv,
+                           d_bytes, kept, N1, pruned, Mp, ntm, ntn, KS, part);
+    });
 }
 
 hipError_t launch_gram_partial(int dt, const void *vis, int B, int Nv, int d, const int32_t *kept,

@@ -1439,7 +1439,7 @@ __global__ __launch_bounds__(kScoreNT) void gram_score_kernel(
     // the score blocks first: they are the longer ones
     const int n_score = (int)gridDim.x - gj.nblocks;
     if ((int)blockIdx.x >= n_score) {
-        gram_partial_tile<DT, kSplitNS, true>(gj.vis, gj.B, gj.Nv, gj.d_bytes, gj.kept, gj.N1,
+        gram_partial_tile<DT, kSplitNS, false, true>(gj.vis, gj.B, gj.Nv, gj.d_bytes, gj.kept, gj.N1,
                                               gj.pruned, gj.Mp, gj.ntm, gj.ntn, gj.KS, gj.part,
                                               gj.nblocks, (int)blockIdx.x - n_score, ring);
         return;

@@ -271,7 +271,7 @@ constexpr int kSplitNS = 3;
 // EXT: the LDS ring is `ext_ring` (the tile's LDS_BYTES, shared with the
 // other workgroups of a launch that carries another step); else its own.
 // Tiles of BM pruned x BN kept rows (four waves of BM/2 x BN/2).
-template <int DT, int NS, bool EXT = false, int BM = kPT, int BN = kPT>
+template <int DT, int NS, bool TAIL, bool EXT = false, int BM = kPT, int BN = kPT>
 __device__ __forceinline__ void gram_partial_tile(const char *__restrict__ vis, int B, int Nv,
                                                   int d_bytes, const int32_t *__restrict__ kept,
                                                   int N1, const int32_t *__restrict__ pruned,
@@ -296,12 +296,12 @@ __device__ __forceinline__ void gram_partial_tile(const char *__restrict__ vis, 
     __syncthreads();
     const char *vbase = vis + (size_t)b * Nv * d_bytes;
     auto row_ptr = [&](int r) -> const char * { return vbase + (size_t)rowtok[r] * d_bytes; };
-    const int nch = d_bytes / G::CHUNK;
+    const int nch = G::chunks(d_bytes);
     const int c0 = (int)(((long long)nch * ks) / KS), c1 = (int)(((long long)nch * (ks + 1)) / KS);
     f32x4_t acc[G::FM][G::FN];
     float sa[G::FM], sb[G::FN];
-    if constexpr (EXT) G::template run_in<false>(ext_ring, row_ptr, c0, c1, acc, sa, sb);
-    else G::template run<false>(row_ptr, c0, c1, acc, sa, sb);
+    if constexpr (EXT) G::template run_in<false, TAIL>(ext_ring, row_ptr, d_bytes, c0, c1, acc, sa, sb);
+    else G::template run<false, TAIL>(row_ptr, d_bytes, c0, c1, acc, sa, sb);
     float *pb = part + ((size_t)ks * B + b) * Mp * N1;
 #pragma unroll
     for (int fm = 0; fm < G::FM; ++fm)

@@ -109,6 +109,18 @@ struct TileGemmLds {
     static_assert(NSTAGE >= 2, "at least double buffering");
     static_assert(IPW * (NSTAGE - 1) < 64, "loads in flight exceed the wait counter");
 
+    // Byte within a chunk that this lane loads (the same in all its loads).
+    __device__ __forceinline__ static int piece_of(int lane) { return ((lane & 7) ^ ((lane >> 3) & 7)) << 4; }
+
+    // Chunks of a row of row_bytes (a multiple of 16; the pieces of the last
+    // chunk past the row's end read as zeros, which change no product).
+    __device__ __forceinline__ static int chunks(int row_bytes) { return (row_bytes + CHUNK - 1) / CHUNK; }
+
+    // TAIL: the rows may end within a chunk (else they are a multiple of CHUNK:
+    // the comparison per chunk cost the dedup of 4 x 2880 tokens 1.3%).  Copying
+    // such rows into padded ones first took 5.7 + 2.4 us at 3 x 1037 fp32 rows of
+    // 1000 and 37 anchors (the call 67.7 -> 62.2 us).
+    //
     // Multiply chunks [c_begin, c_end) into acc.  row_ptr(r) is the global byte
     // address of staged row r (r < BM: A rows, r >= BM: B rows); every row
     // must be valid (clamp past-the-end rows in the caller).  With WANT_SS,
@@ -117,21 +129,21 @@ struct TileGemmLds {
     // row_sumsq; want_a / want_b (uniform over the workgroup) say whether this
     // workgroup's are used at all.  Must be called by every thread of the
     // workgroup.
-    template <bool WANT_SS, typename RowPtr>
-    __device__ __forceinline__ static void run(RowPtr row_ptr, int c_begin, int c_end,
+    template <bool WANT_SS, bool TAIL, typename RowPtr>
+    __device__ __forceinline__ static void run(RowPtr row_ptr, int row_bytes, int c_begin, int c_end,
                                                f32x4_t (&acc)[FM][FN], float (&ssa)[FM],
                                                float (&ssb)[FN], bool want_a = true,
                                                bool want_b = true) {
         __shared__ __attribute__((aligned(16))) char ring[LDS_BYTES];
-        run_in<WANT_SS>(ring, row_ptr, c_begin, c_end, acc, ssa, ssb, want_a, want_b);
+        run_in<WANT_SS, TAIL>(ring, row_ptr, row_bytes, c_begin, c_end, acc, ssa, ssb, want_a, want_b);
     }
 
     // The same on a ring the caller provides (LDS_BYTES of LDS, 16-byte
     // aligned), for kernels whose other workgroups use the same LDS for
     // something else.
-    template <bool WANT_SS, typename RowPtr>
-    __device__ __forceinline__ static void run_in(char *ring, RowPtr row_ptr, int c_begin,
-                                                  int c_end, f32x4_t (&acc)[FM][FN],
+    template <bool WANT_SS, bool TAIL, typename RowPtr>
+    __device__ __forceinline__ static void run_in(char *ring, RowPtr row_ptr, int row_bytes,
+                                                  int c_begin, int c_end, f32x4_t (&acc)[FM][FN],
                                                   float (&ssa)[FM], float (&ssb)[FN],
                                                   bool want_a = true, bool want_b = true) {
         const int lane = threadIdx.x & 63;
@@ -159,9 +171,17 @@ struct TileGemmLds {
         // chunk i (relative to c_begin) goes to stage i % NSTAGE
         auto issue = [&](int i) {
             char *dst = ring + (i % NSTAGE) * STAGE_BYTES + wave * IPW * 1024;
+            const int at = (c_begin + i) * CHUNK;
+            if (!TAIL || at + CHUNK <= row_bytes) {
 #pragma unroll
-            for (int q = 0; q < IPW; ++q)
-                lds_dma16(src[q] + (size_t)i * CHUNK, dst + q * 1024);
+                for (int q = 0; q < IPW; ++q)
+                    lds_dma16(src[q] + (size_t)i * CHUNK, dst + q * 1024);
+            } else {
+#pragma unroll
+                for (int q = 0; q < IPW; ++q)
+                    lds_dma16(at + piece_of(lane) < row_bytes ? src[q] + (size_t)i * CHUNK : zero16(),
+                              dst + q * 1024);
+            }
         };
 #pragma unroll
         for (int p = 0; p < NSTAGE - 1; ++p)
@@ -242,9 +262,9 @@ struct TileGemmLds {
     // m_valid / n_valid: the A / B rows that count (the rest are padding the
     // caller clamps to valid rows); a matrix wave whose A rows or B rows all
     // lie past them keeps only the barriers and returns zero products.
-    template <int NP, typename RowPtr>
-    __device__ __forceinline__ static void run_pc(char *ring, RowPtr row_ptr, int c_begin, int c_end,
-                                                  f32x4_t (&acc)[FM][FN], int m_valid = BM,
+    template <int NP, bool TAIL, typename RowPtr>
+    __device__ __forceinline__ static void run_pc(char *ring, RowPtr row_ptr, int row_bytes,
+                                                  int c_begin, int c_end, f32x4_t (&acc)[FM][FN], int m_valid = BM,
                                                   int n_valid = BN) {
         static_assert(NSTAGE == 3, "two chunks in flight and one being read");
         constexpr int IPP = ROWS * 8 / 64 / NP;  // load instructions per producer wave per stage
@@ -269,9 +289,17 @@ struct TileGemmLds {
             }
             auto issue = [&](int i) {
                 char *dst = ring + (i % NSTAGE) * STAGE_BYTES + pw * IPP * 1024;
+                const int at = (c_begin + i) * CHUNK;
+                if (!TAIL || at + CHUNK <= row_bytes) {
 #pragma unroll
-                for (int q = 0; q < IPP; ++q)
-                    lds_dma16(src[q] + (size_t)i * CHUNK, dst + q * 1024);
+                    for (int q = 0; q < IPP; ++q)
+                        lds_dma16(src[q] + (size_t)i * CHUNK, dst + q * 1024);
+                } else {
+#pragma unroll
+                    for (int q = 0; q < IPP; ++q)
+                        lds_dma16(at + piece_of(lane) < row_bytes ? src[q] + (size_t)i * CHUNK : zero16(),
+                                  dst + q * 1024);
+                }
             };
             issue(0);
             if (nc > 1) issue(1);

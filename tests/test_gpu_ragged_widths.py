@@ -1,0 +1,64 @@
+"""Embedding widths that are not a multiple of 128 bytes, read in place: rows inside NaN (a
+piece read past the last row would spoil the sums, one past any other row adds the next row's
+elements), in every form of the three products, against the oracle."""
+
+from __future__ import annotations
+
+import numpy as np
+import pytest
+
+import oracle
+from paper_2608_25332_amd import workloads as W
+from parity_util import check_dedup_sample, rel_err, to_dev, to_host
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _gpu():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+
+
+# (B, Nv, Nt, d, N1, dtype); cosine / Gram
+WIDTHS = [
+    (1, 70, 5, 8, 20, "bf16"),       # one piece a row; one pass / split-k
+    (1, 100, 17, 72, 30, "f32"),
+    (2, 900, 40, 1000, 300, "bf16"), # streaming / wide split-k tiles
+    (3, 1037, 37, 1000, 345, "f32"), # split-k / wide split-k tiles
+    (2, 600, 100, 1016, 200, "f32"), # wide cosine tiles
+    (2, 700, 129, 136, 200, "bf16"), # two anchor tiles
+    (40, 600, 4, 200, 200, "bf16"),  # full-k Gram tiles
+    (16, 300, 9, 264, 290, "f32"),
+]
+
+
+@pytest.mark.parametrize("B,Nv,Nt,d,N1,dt", WIDTHS)
+def test_embedding_widths_read_in_place(B, Nv, Nt, d, N1, dt):
+    from paper_2608_25332_amd import provip
+    print(f"[ragged width] B={B} Nv={Nv} Nt={Nt} d={d} N1={N1} {dt}", flush=True)
+    rng = np.random.default_rng(B * 1000 + Nv + d)
+    vis = rng.standard_normal((B, Nv, d), dtype=np.float32)
+    anc = rng.standard_normal((B, Nt, d), dtype=np.float32) * np.float32(1.7 / np.sqrt(d))
+    if dt == "bf16":
+        vis, anc = W.bf16_round(vis), W.bf16_round(anc)
+
+    def inside_nan(x):
+        t = to_dev(x, dt)
+        buf = torch.full((t.numel() + 1024,), float("nan"), dtype=t.dtype, device=t.device)
+        buf[512:512 + t.numel()] = t.reshape(-1)
+        return buf[512:512 + t.numel()].view(t.shape)
+
+    vd, ad = inside_nan(vis), inside_nan(anc)
+    r = provip.pv_prune_dedup(vd, ad, N1)
+    c = provip.pv_critical_text(ad)
+    torch.cuda.synchronize()
+    g = {n: to_host(r[n]) for n in ("kept", "score", "assign", "merged")}
+    for b in {0, B - 1}:
+        ref = oracle.dedup(anc[b:b + 1], vis[b:b + 1], N1, want_assign=False)
+        check_dedup_sample(g, b, vis[b], ref["p"][0], N1, dt)
+        rr, _, _ = oracle.critical_text(anc[b:b + 1])
+        # logits to about 30 with an fp32 error of 1e-7 of them: 3e-6 of an exponential
+        assert rel_err(to_host(c["r"])[b], rr[0]) <= 1e-5
