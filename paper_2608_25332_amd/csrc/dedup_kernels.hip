@@ -569,13 +569,14 @@ __global__ __launch_bounds__(str_threads(A)) void cos_stream_kernel(
 }
 
 // ----------------------------------------------------------------------------
-// center: grid (ceil(Nv / 64), B), 256 threads.  Two phases, each with all of
+// center: grid (ceil(Nv / 64), B), NT threads.  Two phases, each with all of
 // its loads in flight before the first is used, so that a phase costs one
-// memory latency: the row means from the per-tile partial sums (4 threads per
-// row, each adding every fourth tile in tile order, the four partials then
-// added in order), and the max over the rows (4 threads per token).
+// memory latency: the row means from the per-tile partial sums (TPR threads per
+// row, each adding every TPR-th tile in tile order, the partials then added in
+// order), and the max over the rows (NT / 64 threads per token).  The kernel is
+// its chain of latencies, so with many rows or many tiles 1024 threads take it
+// in one pass where 256 need several (the rule is at its launch).
 // ----------------------------------------------------------------------------
-constexpr int kCenNT = 256;
 constexpr int kCenTok = 64;
 constexpr int kCenU = 16;  // loads in flight per thread
 
@@ -595,15 +596,20 @@ __device__ __forceinline__ float strided_sum(const float *__restrict__ base, siz
     return s;
 }
 
-__global__ __launch_bounds__(kCenNT) void center_kernel(const float *__restrict__ M,
-                                                        const float *__restrict__ rowsum,
-                                                        const int32_t *__restrict__ row_mask,
-                                                        int njt, int Nt, int Nv,
-                                                        float *__restrict__ p) {
+template <int NT, int TPR>
+__global__ __launch_bounds__(NT) void center_kernel(const float *__restrict__ M,
+                                                    const float *__restrict__ rowsum,
+                                                    const int32_t *__restrict__ row_mask,
+                                                    int njt, int Nt, int Nv,
+                                                    float *__restrict__ p) {
+    constexpr int ROWS = NT / TPR;     // row means per pass
+    constexpr int G = NT / kCenTok;    // threads per token
+    constexpr int U = G <= 4 ? 16 : 8; // rows in flight per thread
     // [0, Nt): row means; [Nt, 2 Nt): the same with +inf for rows that are
     // not anchors (a row at +inf never wins the max)
     extern __shared__ float mu[];
-    __shared__ float rpart[4][kCenTok];
+    __shared__ float rpart[TPR][ROWS];
+    __shared__ float best[G][kCenTok];
     __shared__ int any_row;
     const int b = blockIdx.y, tid = threadIdx.x;
     const int jl = tid & (kCenTok - 1), g = tid / kCenTok;
@@ -611,19 +617,22 @@ __global__ __launch_bounds__(kCenNT) void center_kernel(const float *__restrict_
     // the first block of this thread's column of M does not depend on the
     // row means: its loads are in flight during the first phase
     const float *col = M + (size_t)b * Nt * Nv + min(j, Nv - 1);
-    float v0[kCenU];
+    float v0[U];
 #pragma unroll
-    for (int u = 0; u < kCenU; ++u) v0[u] = col[(size_t)min(g + 4 * u, Nt - 1) * Nv];
+    for (int u = 0; u < U; ++u) v0[u] = col[(size_t)min(g + G * u, Nt - 1) * Nv];
     if (tid == 0) any_row = row_mask ? 0 : 1;
-    for (int r0 = 0; r0 < Nt; r0 += kCenTok) {
-        const int i = r0 + (tid >> 2), q = tid & 3;
+    for (int r0 = 0; r0 < Nt; r0 += ROWS) {
+        const int i = r0 + tid % ROWS, q = tid / ROWS;
         float s = 0.f;
-        if (i < Nt) s = strided_sum(rowsum + (size_t)b * njt * Nt + i, Nt, q, 4, njt);
-        rpart[q][tid >> 2] = s;
+        if (i < Nt) s = strided_sum(rowsum + (size_t)b * njt * Nt + i, Nt, q, TPR, njt);
+        rpart[q][tid % ROWS] = s;
         __syncthreads();
-        if (tid < kCenTok && r0 + tid < Nt) {
+        if (tid < ROWS && r0 + tid < Nt) {
             const int ii = r0 + tid;
-            const float m = (((rpart[0][tid] + rpart[1][tid]) + rpart[2][tid]) + rpart[3][tid]) / (float)Nv;
+            float m = rpart[0][tid];
+#pragma unroll
+            for (int t = 1; t < TPR; ++t) m += rpart[t][tid];
+            m /= (float)Nv;
             const bool use = !row_mask || row_mask[(size_t)b * Nt + ii] != 0;
             mu[ii] = m;
             mu[Nt + ii] = use ? m : INFINITY;
@@ -636,21 +645,24 @@ __global__ __launch_bounds__(kCenNT) void center_kernel(const float *__restrict_
     float m = -INFINITY;
     if (j < Nv) {
 #pragma unroll
-        for (int u = 0; u < kCenU; ++u)
-            if (g + 4 * u < Nt) m = fmaxf(m, v0[u] - mrow[g + 4 * u]);
-        for (int i0 = g + 4 * kCenU; i0 < Nt; i0 += 4 * kCenU) {
-            float v[kCenU];
+        for (int u = 0; u < U; ++u)
+            if (g + G * u < Nt) m = fmaxf(m, v0[u] - mrow[g + G * u]);
+        for (int i0 = g + G * U; i0 < Nt; i0 += G * U) {
+            float v[U];
 #pragma unroll
-            for (int u = 0; u < kCenU; ++u) v[u] = col[(size_t)min(i0 + 4 * u, Nt - 1) * Nv];
+            for (int u = 0; u < U; ++u) v[u] = col[(size_t)min(i0 + G * u, Nt - 1) * Nv];
 #pragma unroll
-            for (int u = 0; u < kCenU; ++u)
-                if (i0 + 4 * u < Nt) m = fmaxf(m, v[u] - mrow[i0 + 4 * u]);
+            for (int u = 0; u < U; ++u)
+                if (i0 + G * u < Nt) m = fmaxf(m, v[u] - mrow[i0 + G * u]);
         }
     }
-    rpart[g][jl] = m;
+    best[g][jl] = m;
     __syncthreads();
-    if (g == 0 && j < Nv)
-        p[(size_t)b * Nv + j] = fmaxf(fmaxf(rpart[0][jl], rpart[1][jl]), fmaxf(rpart[2][jl], rpart[3][jl]));
+    if (g == 0 && j < Nv) {
+#pragma unroll
+        for (int t = 1; t < G; ++t) m = fmaxf(m, best[t][jl]);
+        p[(size_t)b * Nv + j] = m;
+    }
 }
 
 // ----------------------------------------------------------------------------
@@ -1316,9 +1328,18 @@ hipError_t launch_text_gram_stream(const void *text, int B, int Nt, int d, float
 
 hipError_t launch_center(const float *M, const float *rowsum, const int32_t *row_mask, int njt,
                          int B, int Nt, int Nv, float *p, hipStream_t st) {
-    dim3 grid((Nv + kCenTok - 1) / kCenTok, B);
-    hipLaunchKernelGGL(center_kernel, grid, dim3(kCenNT), 2 * (size_t)Nt * sizeof(float), st, M, rowsum,
-                       row_mask, njt, Nt, Nv, p);
+    const dim3 grid((Nv + kCenTok - 1) / kCenTok, B);
+    const size_t lds = 2 * (size_t)Nt * sizeof(float);
+    // more rows than one pass of 256 threads takes, or more tiles than their
+    // loads of one round cover (measured: 128 rows, 64 tiles a sample at 4 x 2880
+    // tokens 6.4 -> 4.7 us; 128 rows, 128 tiles at 2 x 4608 7.8 -> 4.9 us; with
+    // 64 rows and 15 tiles 256 threads are as fast on a quarter of the waves)
+    if (Nt > kCenTok || njt > 4 * kCenU)
+        hipLaunchKernelGGL((center_kernel<1024, 8>), grid, dim3(1024), lds, st, M, rowsum, row_mask,
+                           njt, Nt, Nv, p);
+    else
+        hipLaunchKernelGGL((center_kernel<256, 4>), grid, dim3(256), lds, st, M, rowsum, row_mask,
+                           njt, Nt, Nv, p);
     return hipGetLastError();
 }
 

@@ -1,0 +1,43 @@
+"""Centring and max-pool on 256 and on 1024 threads against the oracle."""
+
+from __future__ import annotations
+
+import numpy as np
+import pytest
+
+import oracle
+from parity_util import rel_err, to_dev, to_host
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _gpu():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+
+
+# (B, Nv, Nt, d, N1, masked): the centring on 1024 threads (more than 64 rows, or more than 64
+# row-sum tiles) at its edges: a second pass of 128 rows, partial row groups, one token past a block
+CENTER = [(1, 65, 65, 64, 20, False), (2, 130, 128, 64, 40, True), (1, 200, 129, 128, 60, True),
+          (1, 1025, 9, 64, 300, False), (1, 1040, 257, 64, 300, True), (3, 64, 100, 72, 64, False)]
+
+
+@pytest.mark.parametrize("B,Nv,Nt,d,N1,masked", CENTER)
+def test_centring_forms(B, Nv, Nt, d, N1, masked):
+    from paper_2608_25332_amd import provip
+    print(f"[center] B={B} Nv={Nv} Nt={Nt} d={d} masked={masked}", flush=True)
+    rng = np.random.default_rng(Nv + Nt)
+    vis = rng.standard_normal((B, Nv, d), dtype=np.float32)
+    anc = rng.standard_normal((B, Nt, d), dtype=np.float32)
+    mask = (rng.random((B, Nt)) < 0.5).astype(np.int32)
+    mask[0] = 0  # an empty mask means every row
+    m = torch.from_numpy(mask).to("cuda:0") if masked else None
+    r = provip.pv_prune_dedup(to_dev(vis, "f32"), to_dev(anc, "f32"), N1, anchor_mask=m)
+    torch.cuda.synchronize()
+    for b in range(B):
+        rows = mask[b].astype(bool) if masked and mask[b].any() else slice(None)
+        p = oracle.maxpool(oracle.center(oracle.cosine(anc[b][rows], vis[b])))
+        assert rel_err(to_host(r["score"])[b], p) <= 1e-5
