@@ -1636,7 +1636,11 @@ hipError_t launch_score_chain(const ScoreChain &c, hipStream_t st) {
 hipError_t launch_bucket_carry(const ScoreChain &c, const BucketJob &bj, const SelectJob &sj,
                                const GatherJob &gj, hipStream_t st) {
     const size_t lds_b = (size_t)bj.Nv * sizeof(int32_t), lds_c = (size_t)c.Nt * sizeof(float2);
-    const bool wide = bj.Nv >= kBucketWideNv;
+    // 512 threads up to 6144 tokens, where three such workgroups fit on a CU: the
+    // member lists hide under the compaction, and of the wider workgroups the
+    // column sums would hold 16 waves each with four at work (2 x 4608 tokens, 5
+    // heads of 1152 keys: 25.1 -> 22.3 us)
+    const bool wide = bj.Nv > 6144;
     const int nt = wide ? 1024 : 512, n_gather = (gj.nblocks + nt / kGatherNT - 1) / (nt / kGatherNT);
     if (c.form == kSharedSplit) {
         const SplitScore s = split_score(shared_score(c), (float2 *)c.stats, 0, c.B);
