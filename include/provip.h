@@ -34,7 +34,9 @@
  *   - Widths: an embedding width d or head width hd may be any multiple of 8
  *     in range; rows are read in place whatever their width (the pieces that
  *     the kernels stream past a row's end count as zeros, which change no dot
- *     product and no norm).
+ *     product and no norm).  For widths that are not whole 128-byte chunks
+ *     (d) or multiples of 32 (hd) the workspace queries include the room of a
+ *     copy of the rows at the next such width.
  */
 #ifndef PROVIP_H
 #define PROVIP_H

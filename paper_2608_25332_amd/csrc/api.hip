@@ -37,6 +37,23 @@ bool aligned16(const void *p) { return ((uintptr_t)p & 15u) == 0; }
 
 size_t round_up(size_t x) { return (x + kAlign - 1) / kAlign * kAlign; }
 
+// The widths that plans and workspace sizes are made for: embedding rows in
+// whole 128-byte k chunks, head rows in multiples of 32 elements.  The kernels
+// read rows of any width in place, but the sizes that the queries report, and
+// that calls check against, keep the room for a copy of such rows at those
+// widths: they are part of the boundary.
+int padded_d(int d, int esz) { return (d * esz + 127) / 128 * 128 / esz; }
+int padded_hd(int hd) { return (hd + 31) / 32 * 32; }
+size_t room_d(long long rows, int d, int esz) {
+    const int dp = padded_d(d, esz);
+    return dp != d ? round_up((size_t)rows * dp * esz) : 0;
+}
+size_t room_hd(int B, int H, int Nt, int N, int hd, int esz) {
+    const int hp = padded_hd(hd);
+    if (hp == hd) return 0;
+    return round_up((size_t)B * H * Nt * hp * esz) + round_up((size_t)B * H * N * hp * esz);
+}
+
 // Launches the kernels of one call.  With events, events[i] is recorded
 // before kernel i and events[n] after the last one; with reps > 1 every
 // kernel is launched reps times back to back between its two events (the
@@ -194,9 +211,9 @@ DedupPlan plan_dedup(void *ws, int B, int Nv, int Nt, int d, int esz, int budget
 
 size_t dedup_total_bytes(int B, int Nv, int Nt, int d, int esz, int budget, bool want_p,
                          bool want_assign, bool want_merged) {
-    return round_up(plan_dedup(nullptr, B, Nv, Nt, d, esz, budget, want_p, want_assign,
-                               want_merged).bytes) +
-           kAlign;
+    return round_up(plan_dedup(nullptr, B, Nv, Nt, padded_d(d, esz), esz, budget, want_p,
+                               want_assign, want_merged).bytes) +
+           room_d((long long)B * Nv, d, esz) + room_d((long long)B * Nt, d, esz) + kAlign;
 }
 
 int check_dedup(const void *vis, const void *anchors, int B, int Nv, int Nt, int d, int dtype,
@@ -302,7 +319,7 @@ int dedup_impl(const void *vis, const void *anchors, int B, int Nv, int Nt, int 
         if (p && !aligned16(p)) return PV_ERR_ALIGN;
     // carve from a 256-aligned start
     char *wsa = (char *)(((uintptr_t)workspace + kAlign - 1) / kAlign * kAlign);
-    DedupPlan P = plan_dedup(wsa, B, Nv, Nt, d, esz, budget, score == nullptr,
+    DedupPlan P = plan_dedup(wsa, B, Nv, Nt, padded_d(d, esz), esz, budget, score == nullptr,
                              need_assign && !assign, merged != nullptr);
     float *p = score ? score : P.p;
     int32_t *asg = assign ? assign : P.assign;
@@ -412,8 +429,9 @@ HeadPlan plan_head(void *ws, int B, int Nt, int N, int n_heads, bool want_v) {
     return P;
 }
 
-size_t head_total_bytes(int B, int Nt, int N, int n_heads, bool want_v) {
-    return round_up(plan_head(nullptr, B, Nt, N, n_heads, want_v).bytes) + kAlign;
+size_t head_total_bytes(int B, int H, int Nt, int N, int hd, int esz, int n_heads, bool want_v) {
+    return round_up(plan_head(nullptr, B, Nt, N, n_heads, want_v).bytes) +
+           room_hd(B, H, Nt, N, hd, esz) + kAlign;
 }
 
 int check_qk(const void *q, const void *k, int B, int H, int Nt, int N, int hd, int dtype) {
@@ -462,7 +480,8 @@ int head_impl(const void *q, const void *k, const int32_t *heads, const int32_t 
     if (row_lse && (uintptr_t)row_lse % 4) return PV_ERR_ALIGN;
     int rc = check_head(q, k, heads, heads_dev, n_heads, B, H, Nt, N, hd, dtype, budget, kept);
     if (rc != PV_OK) return rc;
-    if (!workspace || ws_bytes < head_total_bytes(B, Nt, N, n_heads, score == nullptr))
+    const int esz = (dtype == PV_BF16) ? 2 : 4;
+    if (!workspace || ws_bytes < head_total_bytes(B, H, Nt, N, hd, esz, n_heads, score == nullptr))
         return PV_ERR_WORKSPACE;
     for (const void *p : {q, k, (const void *)kept, (const void *)score, (const void *)workspace})
         if (p && !aligned16(p)) return PV_ERR_ALIGN;
@@ -496,6 +515,10 @@ size_t vis_heads_bytes(int B, int H, int Nt) {
     return c.off + kAlign;
 }
 
+size_t vis_heads_total_bytes(int B, int H, int Nt, int N, int hd, int esz) {
+    return round_up(vis_heads_bytes(B, H, Nt)) + room_hd(B, H, Nt, N, hd, esz) + kAlign;
+}
+
 int vis_heads_impl(const void *q, const void *k, int B, int H, int Nt, int N, int hd, int dtype,
                    int n_vis, int32_t *heads_out, float *conf, void *workspace, size_t ws_bytes,
                    void *stream, void *const *events, int n_events, int reps, int *n_kernels,
@@ -508,7 +531,9 @@ int vis_heads_impl(const void *q, const void *k, int B, int H, int Nt, int N, in
     int rc = check_qk(q, k, B, H, Nt, N, hd, dtype);
     if (rc != PV_OK) return rc;
     if (H > PV_MAX_HEADS || n_vis < 1 || n_vis > H) return PV_ERR_HEADS;
-    if (!workspace || ws_bytes < vis_heads_bytes(B, H, Nt)) return PV_ERR_WORKSPACE;
+    const int esz = (dtype == PV_BF16) ? 2 : 4;
+    if (!workspace || ws_bytes < vis_heads_total_bytes(B, H, Nt, N, hd, esz))
+        return PV_ERR_WORKSPACE;
     for (const void *p : {(const void *)heads_out, (const void *)conf, (const void *)workspace})
         if (p && !aligned16(p)) return PV_ERR_ALIGN;
     char *wsa = (char *)(((uintptr_t)workspace + kAlign - 1) / kAlign * kAlign);
@@ -539,7 +564,8 @@ struct TextPlan {
 TextPlan plan_text(void *ws, int B, int Nt, int d, int esz);
 
 size_t text_total_bytes(int B, int Nt, int d, int esz) {
-    return round_up(plan_text(nullptr, B, Nt, d, esz).bytes) + kAlign;
+    return round_up(plan_text(nullptr, B, Nt, padded_d(d, esz), esz).bytes) +
+           room_d((long long)B * Nt, d, esz) + kAlign;
 }
 
 TextPlan plan_text(void *ws, int B, int Nt, int d, int esz) {
@@ -574,7 +600,7 @@ int text_impl(const void *text, int B, int Nt, int d, int dtype, int32_t *mask, 
                           (const void *)workspace})
         if (p && !aligned16(p)) return PV_ERR_ALIGN;
     char *wsa = (char *)(((uintptr_t)workspace + kAlign - 1) / kAlign * kAlign);
-    TextPlan P = plan_text(wsa, B, Nt, d, esz);
+    TextPlan P = plan_text(wsa, B, Nt, padded_d(d, esz), esz);
     const int dt = (dtype == PV_BF16) ? pv::kBF16 : pv::kF32;
     hipStream_t st = (hipStream_t)stream;
     Trace tr{events, n_events, names, reps, st};
@@ -711,7 +737,7 @@ PV_API size_t pv_head_aware_workspace_bytes(int B, int H, int Nt, int N, int hd,
     (void)budget;
     if (B < 1 || H < 1 || Nt < 1 || N < 1 || hd < 1 || n_heads < 1) return 0;
     if (dtype != PV_F32 && dtype != PV_BF16) return 0;
-    return head_total_bytes(B, Nt, N, n_heads, true);
+    return head_total_bytes(B, H, Nt, N, hd, dtype == PV_BF16 ? 2 : 4, n_heads, true);
 }
 
 PV_API int pv_prune_head_aware(const void *q, const void *k, const int32_t *heads_host, int n_heads,
@@ -785,7 +811,7 @@ PV_API size_t pv_visual_heads_workspace_bytes(int B, int H, int Nt) {
 PV_API size_t pv_visual_heads_workspace_bytes_hd(int B, int H, int Nt, int N, int hd, int dtype) {
     if (B < 1 || H < 1 || Nt < 1 || N < 1 || hd < 1) return 0;
     if (dtype != PV_F32 && dtype != PV_BF16) return 0;
-    return vis_heads_bytes(B, H, Nt);
+    return vis_heads_total_bytes(B, H, Nt, N, hd, dtype == PV_BF16 ? 2 : 4);
 }
 
 PV_API int pv_visual_heads(const void *q, const void *k, int B, int H, int Nt, int N, int hd,
@@ -957,7 +983,7 @@ struct PipeSizes {
 
 PipeSizes pipe_sizes(int B, int Nv, int Nt, int d, int H, int hd, int esz, int N1, int n_heads) {
     const size_t D = round_up(dedup_total_bytes(B, Nv, Nt, d, esz, N1, false, false, true));
-    const size_t Hh = round_up(head_total_bytes(B, Nt, N1, n_heads, false));
+    const size_t Hh = round_up(head_total_bytes(B, H, Nt, N1, hd, esz, n_heads, false));
     const size_t S = round_up((size_t)B * N1 * sizeof(int32_t));  // each slot's place among the N_2
     return PipeSizes{D, Hh, S, D + Hh + S + kAlign};
 }
@@ -1032,7 +1058,7 @@ int pipeline_impl(const void *vis, const void *anchors, const void *q, const voi
     // launches of the argmax and of the member lists
     const int form = pv::shared_score_form(dt, B, H, n_heads, Nt, N1, hd);
     if (!force_separate && !carry && P.Mp > 0 && form != pv::kSharedNone &&
-        pv::merge_uses_lists(B, N1, d * esz)) {
+        pv::merge_uses_lists(B, N1, padded_d(d, esz) * esz)) {
         const HeadPlan Hh = plan_head(ws_head, B, Nt, N1, n_heads, false);
         const int parts = n_heads * (form == pv::kSharedRows ? Hh.nrb : 1);
         const float inv_norm = (float)(1.0 / ((double)Nt * (double)n_heads));
@@ -1190,9 +1216,9 @@ ProgPlan plan_prog(void *ws, int B, int Nv, int Nt, int d, int H, int hd, int es
     ProgPlan P;
     P.text = text_total_bytes(B, Nt, d, esz);
     P.dedup = dedup_total_bytes(B, Nv, Nt, d, esz, N1, true, false, true);
-    P.vh = vis_heads_bytes(B, H, Nt);
-    P.head_b = head_total_bytes(B, Nt, N1, n_vis, !want_s2);
-    P.head_c = head_total_bytes(B, Nt, N2, H, !want_s3);
+    P.vh = vis_heads_total_bytes(B, H, Nt, N1, hd, esz);
+    P.head_b = head_total_bytes(B, H, Nt, N1, hd, esz, n_vis, !want_s2);
+    P.head_c = head_total_bytes(B, H, Nt, N2, hd, esz, H, !want_s3);
     Carve c(ws);
     P.ws_text = c.take<char>(P.text);
     P.ws_dedup = c.take<char>(P.dedup);
@@ -1254,7 +1280,7 @@ int progressive_impl(const void *text, const void *vis, const void *q_s, const v
     const int form = pv::shared_score_form(dt, B, H, n_vis, Nt, N1, hd);
     if (N1 < Nv && form != pv::kSharedNone && pv::conf_indexed_supported(dt, N1, hd) &&
         (form == pv::kSharedRows || N1 <= pv::kMergeSelCols * 256) &&
-        pv::merge_uses_lists(B, N1, d * esz)) {
+        pv::merge_uses_lists(B, N1, padded_d(d, esz) * esz)) {
         const bool rows = form == pv::kSharedRows;
         const HeadPlan Hb = plan_head((char *)(((uintptr_t)P.ws_head_b + kAlign - 1) / kAlign * kAlign), B,
                                       Nt, N1, n_vis, score2 == nullptr);
