@@ -115,6 +115,7 @@ struct DedupPlan {
     int ks_cos, njt;               // cosine: k slices, token tiles of the row sums
     int Mp;
     bool gram_big;                 // full-k 128x128 tiles (operands streamed into LDS)
+    int gram_tn;                   // its columns per tile
     int ks_gram, ntn;              // split-k slices (small) / column tiles (big)
     bool gram_wide;                // split-k Gram on the wide tiles
     // workspace
@@ -172,7 +173,12 @@ DedupPlan plan_dedup(void *ws, int B, int Nv, int Nt, int d, int esz, int budget
             P.ks_gram = ksw;
         }
     }
-    P.ntn = P.gram_big ? (budget + pv::kGramTileN - 1) / pv::kGramTileN : 1;
+    P.gram_tn = pv::kGramTileN;
+    if (!P.gram_big && esz == 4 && pv::gram_f32_full(B, Mp1, budget, P.nch, P.ks_gram)) {
+        P.gram_big = true;
+        P.gram_tn = pv::kGramF32Tile;
+    }
+    P.ntn = P.gram_big ? (budget + P.gram_tn - 1) / P.gram_tn : 1;
     Carve c(ws);
     if (P.cos_full || P.cos_tok) {
         P.cpart = P.ssv = P.ssa = nullptr;
@@ -347,7 +353,8 @@ int dedup_impl(const void *vis, const void *anchors, int B, int Nv, int Nt, int 
         if (P.gram_big) {
             if (!tr.launch("gram_tile", [&] {
                     return pv::launch_gram_tile(dt, vis, B, Nv, d, kept, budget, P.pruned, P.Mp,
-                                                P.invn, P.best_val, P.best_slot, asg, sm);
+                                                P.invn, P.best_val, P.best_slot, asg, P.gram_tn,
+                                                sm);
                 }))
                 return PV_ERR_HIP;
             if (carry) {

@@ -725,7 +725,7 @@ __global__ __launch_bounds__(128) void gram_reduce_kernel(ReduceJob j) {
 // another stream's copies share the CU's load path.
 // Writes the best (cosine, slot) of every pruned row within this kept tile,
 // or the slot itself when there is only one kept tile.
-template <int DT, int BM, int BN, int WM, int WN, int NS, int NP, bool TAIL>
+template <int DT, int BM, int BN, int WM, int WN, int NS, int NP, bool TAIL, int CHAIN = 0>
 __global__ __launch_bounds__(64 * (WM * WN + NP)) void gram_tile_kernel(
     const char *__restrict__ vis, int Nv, int d_bytes, const int32_t *__restrict__ kept, int N1,
     const int32_t *__restrict__ pruned, int Mp, const float *__restrict__ invn, int ntm, int ntn,
@@ -758,7 +758,7 @@ __global__ __launch_bounds__(64 * (WM * WN + NP)) void gram_tile_kernel(
     __shared__ __attribute__((aligned(16))) char ring[G::LDS_BYTES];
     // matrix waves past the last pruned row or kept slot of an edge tile skip
     // their MFMAs (the epilogue ignores those rows and slots)
-    G::template run_pc<NP, TAIL>(ring, row_ptr, d_bytes, 0, G::chunks(d_bytes), acc, Mp - m0, N1 - n0);
+    G::template run_pc<NP, TAIL, CHAIN>(ring, row_ptr, d_bytes, 0, G::chunks(d_bytes), acc, Mp - m0, N1 - n0);
 
     // producer waves hold no products
     if (__builtin_amdgcn_readfirstlane(wave) < WM * WN) {
@@ -1433,9 +1433,32 @@ hipError_t launch_gram_reduce(const float *part, int B, int Mp, int N1, int Nv, 
     return hipGetLastError();
 }
 
+// The full-k form on kGramF32Tile square tiles: four matrix waves of 32 x 32 and
+// two producers.  An fp32 MFMA takes 32 clocks, so one matrix wave per SIMD
+// keeps its matrix core busy, and a tile this small is bound by it, not by its
+// loads (six stages in place of three changed nothing).  8 chunks (256
+// elements) are added up on their own.
+static void gram_f32_go(const void *vis, int Nv, int d_bytes, const int32_t *kept, int N1,
+                        const int32_t *pruned, int Mp, const float *invn, int B, float *best_val,
+                        int32_t *best_slot, int32_t *assign, hipStream_t st) {
+    constexpr int T = kGramF32Tile, NP = 2;
+    const int ntn = (N1 + T - 1) / T, ntm = (Mp + T - 1) / T;
+    with_tail(d_bytes, [&](auto tail) {
+        hipLaunchKernelGGL((gram_tile_kernel<kF32, T, T, 2, 2, 3, NP, decltype(tail)::value, 8>),
+                           dim3(B * ntm * ntn), dim3(64 * (4 + NP)), 0, st, (const char *)vis, Nv,
+                           d_bytes, kept, N1, pruned, Mp, invn, ntm, ntn, best_val, best_slot, assign);
+    });
+}
+
 hipError_t launch_gram_tile(int dt, const void *vis, int B, int Nv, int d, const int32_t *kept,
                             int N1, const int32_t *pruned, int Mp, const float *invn,
-                            float *best_val, int32_t *best_slot, int32_t *assign, hipStream_t st) {
+                            float *best_val, int32_t *best_slot, int32_t *assign, int tile_n,
+                            hipStream_t st) {
+    if (tile_n == kGramF32Tile) {
+        if (dt != kF32) return hipErrorInvalidValue;
+        gram_f32_go(vis, Nv, d * 4, kept, N1, pruned, Mp, invn, B, best_val, best_slot, assign, st);
+        return hipGetLastError();
+    }
     if (dt == kBF16)
         return gram_tile_go<kBF16>(vis, B, Nv, d, kept, N1, pruned, Mp, invn, best_val, best_slot,
                                    assign, st);

@@ -104,9 +104,26 @@ hipError_t launch_gram_reduce(const float *part, int B, int Mp, int N1, int Nv, 
 // chosen when the product holds at least 128 such tiles (enough work to keep
 // every CU busy without split-k).
 constexpr int kGramTileM = 256, kGramTileN = 128, kGramProducers = 4;
+// fp32 products too small for those tiles: full-k tiles of kGramF32Tile rows and
+// columns (tile_n of launch_gram_tile) where they undercut the split form.  Both
+// are bound by the matrix cores: a tile takes about 0.6 us per 128-byte chunk, one
+// wave of tiles after the other over the 256 CUs, and 8 us to begin and end; the
+// split form spreads its chunks evenly (0.55 us each) but writes and reads back
+// ks fp32 partial products (4.5 and 3.3 MB/us) and needs a second launch.
+// Measured at 3 x 692 x 345 of 1000: 26.3 + 7.1 us split, 27.6 + 4.8 us full.
+constexpr int kGramF32Tile = 64;
+inline bool gram_f32_full(int B, int Mp, int N1, int nch, int ks_split) {
+    const long long T = kGramF32Tile, tiles = ((Mp + T - 1) / T) * ((N1 + T - 1) / T) * B;
+    if (tiles < 64) return false;  // most CUs would have none
+    const double full = (double)((tiles + 255) / 256) * nch * 0.6 + 8.0;
+    const double split = (double)tiles * nch * 0.55 / 256 +
+                         4.0 * ks_split * B * (double)Mp * N1 * (1 / 3.3e6 + 1 / 4.5e6) + 9.0;
+    return full < split;
+}
 hipError_t launch_gram_tile(int dt, const void *vis, int B, int Nv, int d, const int32_t *kept,
                             int N1, const int32_t *pruned, int Mp, const float *invn,
-                            float *best_val, int32_t *best_slot, int32_t *assign, hipStream_t st);
+                            float *best_val, int32_t *best_slot, int32_t *assign, int tile_n,
+                            hipStream_t st);
 hipError_t launch_gram_finish(const float *best_val, const int32_t *best_slot, int B, int ntn,
                               int Mp, int Nv, const int32_t *pruned, int32_t *assign,
                               hipStream_t st);

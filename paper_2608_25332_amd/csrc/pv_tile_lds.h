@@ -259,10 +259,13 @@ struct TileGemmLds {
     // chunk j and before its first read of chunk j + 1.  Both sides pass
     // nc + 2 barriers.  acc is meaningful in the matrix waves only.
     //
+    // CHAIN > 0: the products of CHAIN chunks are added up on their own, so that
+    // a long row's sum has no longer a chain of roundings than split-k slices.
+    //
     // m_valid / n_valid: the A / B rows that count (the rest are padding the
     // caller clamps to valid rows); a matrix wave whose A rows or B rows all
     // lie past them keeps only the barriers and returns zero products.
-    template <int NP, bool TAIL, typename RowPtr>
+    template <int NP, bool TAIL, int CHAIN = 0, typename RowPtr>
     __device__ __forceinline__ static void run_pc(char *ring, RowPtr row_ptr, int row_bytes,
                                                   int c_begin, int c_end, f32x4_t (&acc)[FM][FN], int m_valid = BM,
                                                   int n_valid = BN) {
@@ -348,6 +351,16 @@ struct TileGemmLds {
                     for (int g = 0; g < FN; ++g) acc[f][g] = mma16<DT>(a[f], b[g], acc[f][g]);
             };
             uint4 a0[FM], b0[FN], a1[FM], b1[FN];
+            f32x4_t total[CHAIN > 0 ? FM : 1][CHAIN > 0 ? FN : 1];
+            auto flush = [&](bool first) {
+#pragma unroll
+                for (int f = 0; f < FM; ++f)
+#pragma unroll
+                    for (int g = 0; g < FN; ++g) {
+                        total[f][g] = first ? acc[f][g] : total[f][g] + acc[f][g];
+                        acc[f][g] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+                    }
+            };
             bare_barrier();  // barrier 0
             read_w(0, 0, a0, b0);
             for (int i = 0; i < nc; ++i) {
@@ -366,6 +379,16 @@ struct TileGemmLds {
                 bare_barrier();  // barrier i + 1
                 if (i + 1 < nc) read_w(i + 1, 0, a0, b0);
                 mma_w(a1, b1);
+                if constexpr (CHAIN > 0)
+                    if (i % CHAIN == CHAIN - 1) flush(i == CHAIN - 1);
+            }
+            if constexpr (CHAIN > 0) {
+                if (nc >= CHAIN) {
+#pragma unroll
+                    for (int f = 0; f < FM; ++f)
+#pragma unroll
+                        for (int g = 0; g < FN; ++g) acc[f][g] += total[f][g];
+                }
             }
         }
         bare_barrier();  // the stages may be reused by a later call

@@ -32,6 +32,9 @@ WIDTHS = [
     (2, 700, 129, 136, 200, "bf16"), # two anchor tiles
     (40, 600, 4, 200, 200, "bf16"),  # full-k Gram tiles
     (16, 300, 9, 264, 290, "f32"),
+    (4, 900, 9, 520, 321, "f32"),    # fp32 full-k tiles: one column past a tile, a broken chunk
+    (20, 450, 5, 8, 64, "f32"),      # a single piece of a chunk, one column tile
+    (2, 1200, 5, 512, 391, "f32"),   # the same on whole chunks, one row past a tile
 ]
 
 
