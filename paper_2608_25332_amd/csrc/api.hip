@@ -120,8 +120,9 @@ struct DedupPlan {
     bool gram_wide;                // split-k Gram on the wide tiles
     // workspace
     bool lists;                    // merge reads bucketed member lists
-    float *cpart, *ssv, *ssa, *M, *rowsum, *invn, *p, *gpart, *best_val;
-    int32_t *pruned, *assign, *best_slot, *mcount, *mstart, *mlist;
+    float *cpart, *ssv, *ssa, *M, *rowsum, *invn, *p, *gpart;
+    unsigned long long *best;      // [B][Nv] the full-k Gram's maxima over its column tiles, or NULL
+    int32_t *pruned, *assign, *mcount, *mstart, *mlist;
     size_t bytes;
 };
 
@@ -195,12 +196,14 @@ DedupPlan plan_dedup(void *ws, int B, int Nv, int Nt, int d, int esz, int budget
     P.assign = want_assign ? c.take<int32_t>((size_t)B * Nv) : nullptr;
     if (P.gram_big) {
         P.gpart = nullptr;
-        P.best_val = c.take<float>((size_t)B * P.ntn * Mp1);
-        P.best_slot = c.take<int32_t>((size_t)B * P.ntn * Mp1);
+        // in the place of the cosines, which are done with by the top-N_1 (which
+        // clears the maxima)
+        if (P.ntn == 1) P.best = nullptr;
+        else if (Nt > 1) P.best = (unsigned long long *)P.M;
+        else P.best = c.take<unsigned long long>((size_t)B * Nv);
     } else {
         P.gpart = c.take<float>((size_t)P.ks_gram * B * Mp1 * budget);
-        P.best_val = nullptr;
-        P.best_slot = nullptr;
+        P.best = nullptr;
     }
     P.lists = want_merged && pv::merge_uses_lists(B, budget, d * esz);
     if (P.lists) {
@@ -301,7 +304,7 @@ bool launch_front(Trace &tr, const DedupPlan &P, int dt, const void *vis, const 
                return pv::launch_center(P.M, P.rowsum, anchor_mask, P.njt, B, Nt, Nv, p, st);
            }) &&
            tr.launch("select", [&] {
-               return pv::launch_select(p, B, Nv, budget, kept, P.pruned, slot_of, st);
+               return pv::launch_select(p, B, Nv, budget, kept, P.pruned, slot_of, P.best, st);
            });
 }
 
@@ -353,20 +356,14 @@ int dedup_impl(const void *vis, const void *anchors, int B, int Nv, int Nt, int 
         if (P.gram_big) {
             if (!tr.launch("gram_tile", [&] {
                     return pv::launch_gram_tile(dt, vis, B, Nv, d, kept, budget, P.pruned, P.Mp,
-                                                P.invn, P.best_val, P.best_slot, asg, P.gram_tn,
-                                                sm);
+                                                P.invn, P.best, asg, P.gram_tn, sm);
                 }))
                 return PV_ERR_HIP;
-            if (carry) {
-                pv::AssignJob aj{};
-                if (P.ntn > 1)
-                    aj.f = pv::FinishJob{P.best_val, P.best_slot, P.ntn, P.Mp, Nv, P.pruned, asg,
-                                         B * ((P.Mp + pv::kFinNT - 1) / pv::kFinNT)};
-                if (launch_assign(*carry, aj, sm) != hipSuccess) return PV_ERR_HIP;
-            } else if (P.ntn > 1) {
+            if (carry) {  // the argmax is complete, or completed by the member lists
+                if (launch_assign(*carry, pv::AssignJob{}, sm) != hipSuccess) return PV_ERR_HIP;
+            } else if (P.best && !(merged && P.lists)) {
                 if (!tr.launch("gram_finish", [&] {
-                        return pv::launch_gram_finish(P.best_val, P.best_slot, B, P.ntn, P.Mp, Nv,
-                                                      P.pruned, asg, sm);
+                        return pv::launch_gram_finish(P.best, B, Nv, asg, sm);
                     }))
                     return PV_ERR_HIP;
             }
@@ -392,12 +389,12 @@ int dedup_impl(const void *vis, const void *anchors, int B, int Nv, int Nt, int 
     if (merged && P.lists) {
         if (carry) {
             const int ng = (budget + pv::kBucketSlotsPerGroup - 1) / pv::kBucketSlotsPerGroup;
-            const pv::BucketJob bj{asg, Nv, budget, P.mcount, P.mstart, P.mlist, ng, ng * B};
+            const pv::BucketJob bj{asg, Nv, budget, P.best, P.mcount, P.mstart, P.mlist, ng, ng * B};
             if (pv::launch_bucket_carry(carry->score, bj, carry->select, carry->gather, sm) !=
                 hipSuccess)
                 return PV_ERR_HIP;
         } else if (!tr.launch("bucket", [&] {
-                return pv::launch_bucket(asg, B, Nv, budget, P.mcount, P.mstart, P.mlist, sm);
+                return pv::launch_bucket(asg, P.best, B, Nv, budget, P.mcount, P.mstart, P.mlist, sm);
             }))
             return PV_ERR_HIP;
         if (!tr.launch("merge", [&] {
@@ -918,7 +915,7 @@ PV_API int pv_select_topk(const float *scores, int B, int n, int k, int32_t *kep
     if (!aligned16(scores) || !aligned16(kept) || (rest && !aligned16(rest)) ||
         (slot_of && !aligned16(slot_of)))
         return PV_ERR_ALIGN;
-    if (pv::launch_select(scores, B, n, k, kept, rest, slot_of, (hipStream_t)stream) != hipSuccess)
+    if (pv::launch_select(scores, B, n, k, kept, rest, slot_of, nullptr, (hipStream_t)stream) != hipSuccess)
         return PV_ERR_HIP;
     return PV_OK;
 }

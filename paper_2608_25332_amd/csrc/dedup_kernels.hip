@@ -12,7 +12,7 @@
 //   gram_partial  pruned x kept Gram on MFMA, split over k
 //   gram_reduce   adds the k slices, cosine, row argmax -> assignment
 //     (large Grams instead: gram_tile, LDS-staged 128x128 full-k tiles with a
-//      fused argmax per column tile, then gram_finish across column tiles)
+//      argmax in the epilogue, an integer maximum across column tiles)
 //   merge         centroid <- mean of itself and its members
 // In the whole-step call (pv_prune_pipeline) gram_partial also carries the
 // K/V compaction of the kept tokens and merge the head-aware top-N_2, as
@@ -673,9 +673,12 @@ template <int NT, int EMAX>
 __global__ __launch_bounds__(NT) void select_kernel(const float *__restrict__ p, int Nv,
                                                     int budget, int32_t *__restrict__ kept,
                                                     int32_t *__restrict__ pruned,
-                                                    int32_t *__restrict__ slot_of) {
+                                                    int32_t *__restrict__ slot_of,
+                                                    unsigned long long *__restrict__ zero) {
     __shared__ TopkSmem sm;
     const int b = blockIdx.x;
+    if (zero)  // the Gram's maxima start here
+        for (int j = threadIdx.x; j < Nv; j += NT) zero[(size_t)b * Nv + j] = 0ull;
     const float *pb = p + (size_t)b * Nv;
     const int E = topk_per_thread(Nv, NT), j0 = threadIdx.x * E;
     uint32_t key[EMAX];
@@ -690,9 +693,13 @@ __global__ __launch_bounds__(NT) void select_kernel(const float *__restrict__ p,
 // Nearest centroid: best (cosine, slot) of every pruned row, with the total
 // order of `better` (higher cosine, then lower slot).
 // ----------------------------------------------------------------------------
-// gram_finish: grid (ceil(Mp / 256), B), one thread per pruned row.
-__global__ __launch_bounds__(kFinNT) void gram_finish_kernel(FinishJob j) {
-    gram_finish_row(j, blockIdx.x * kFinNT + threadIdx.x, blockIdx.y);
+// gram_finish: one thread per token.  The assignment out of the packed maxima,
+// where no member lists follow that would complete it.
+constexpr int kFinNT = 256;
+__global__ __launch_bounds__(kFinNT) void gram_finish_kernel(
+    const unsigned long long *__restrict__ best, long long n, int32_t *__restrict__ assign) {
+    const long long t = (long long)blockIdx.x * kFinNT + threadIdx.x;
+    if (t < n && assign[t] < 0) assign[t] = best_slot_of(best[t]);
 }
 
 template <int DT, int NS, int BM, int BN, bool TAIL>
@@ -723,13 +730,14 @@ __global__ __launch_bounds__(128) void gram_reduce_kernel(ReduceJob j) {
 // path to take them, between its MFMAs (measured: 29% of its time with
 // 128 x 128 tiles); with the producers the Gram also keeps its pace when
 // another stream's copies share the CU's load path.
-// Writes the best (cosine, slot) of every pruned row within this kept tile,
-// or the slot itself when there is only one kept tile.
+// Takes the best (cosine, slot) of every pruned row within this kept tile into
+// the maximum over the tiles (a launch of its own over the tiles' candidates took
+// 4.9 us at 4 x 1920 rows), or writes the slot when there is only one kept tile.
 template <int DT, int BM, int BN, int WM, int WN, int NS, int NP, bool TAIL, int CHAIN = 0>
 __global__ __launch_bounds__(64 * (WM * WN + NP)) void gram_tile_kernel(
     const char *__restrict__ vis, int Nv, int d_bytes, const int32_t *__restrict__ kept, int N1,
     const int32_t *__restrict__ pruned, int Mp, const float *__restrict__ invn, int ntm, int ntn,
-    float *__restrict__ best_val, int32_t *__restrict__ best_slot, int32_t *__restrict__ assign) {
+    unsigned long long *__restrict__ best, int32_t *__restrict__ assign) {
     using G = TileGemmLds<DT, BM, BN, WM, WN, NS>;
     constexpr int NTT = G::NT + 64 * NP;  // matrix waves, then producer waves
     __shared__ int32_t rowtok[G::ROWS];
@@ -800,12 +808,9 @@ __global__ __launch_bounds__(64 * (WM * WN + NP)) void gram_tile_kernel(
             }
         const int m = m0 + r;
         if (m < Mp) {
-            if (ntn == 1) {
-                assign[(size_t)b * Nv + rowtok[r]] = bs;
-            } else {
-                best_val[((size_t)b * ntn + nt) * Mp + m] = bv;
-                best_slot[((size_t)b * ntn + nt) * Mp + m] = bs;
-            }
+            const size_t at = (size_t)b * Nv + rowtok[r];
+            if (ntn == 1) assign[at] = bs;
+            else atomicMax(best + at, best_pack(bv, bs));
         }
     }
 }
@@ -1344,19 +1349,19 @@ hipError_t launch_center(const float *M, const float *rowsum, const int32_t *row
 }
 
 hipError_t launch_select(const float *p, int B, int Nv, int budget, int32_t *kept, int32_t *pruned,
-                         int32_t *slot_of, hipStream_t st) {
+                         int32_t *slot_of, unsigned long long *zero, hipStream_t st) {
     if (Nv <= 256 * 4)
         hipLaunchKernelGGL((select_kernel<256, 4>), dim3(B), dim3(256), 0, st, p, Nv, budget, kept,
-                           pruned, slot_of);
+                           pruned, slot_of, zero);
     else if (Nv <= 512 * 8)
         hipLaunchKernelGGL((select_kernel<512, 8>), dim3(B), dim3(512), 0, st, p, Nv, budget, kept,
-                           pruned, slot_of);
+                           pruned, slot_of, zero);
     else if (Nv <= 512 * 10)  // (measured at 4608 keys: 7.4 us against 8.1 with 1024 threads)
         hipLaunchKernelGGL((select_kernel<512, 10>), dim3(B), dim3(512), 0, st, p, Nv, budget,
-                           kept, pruned, slot_of);
+                           kept, pruned, slot_of, zero);
     else if (Nv <= 1024 * 16)
         hipLaunchKernelGGL((select_kernel<1024, 16>), dim3(B), dim3(1024), 0, st, p, Nv, budget,
-                           kept, pruned, slot_of);
+                           kept, pruned, slot_of, zero);
     else
         return hipErrorInvalidValue;
     return hipGetLastError();
@@ -1364,8 +1369,8 @@ hipError_t launch_select(const float *p, int B, int Nv, int budget, int32_t *kep
 
 template <int DT>
 static hipError_t gram_tile_go(const void *vis, int B, int Nv, int d, const int32_t *kept, int N1,
-                               const int32_t *pruned, int Mp, const float *invn, float *best_val,
-                               int32_t *best_slot, int32_t *assign, hipStream_t st) {
+                               const int32_t *pruned, int Mp, const float *invn,
+                               unsigned long long *best, int32_t *assign, hipStream_t st) {
     const int esz = (DT == kBF16) ? 2 : 4;
     const int ntn = (N1 + kGramTileN - 1) / kGramTileN;
     const int ntm = (Mp + kGramTileM - 1) / kGramTileM;
@@ -1374,7 +1379,7 @@ static hipError_t gram_tile_go(const void *vis, int B, int Nv, int d, const int3
                                              decltype(tail)::value>),
                            dim3(B * ntm * ntn), dim3(64 * (8 + kGramProducers)), 0, st,
                            (const char *)vis, Nv, d * esz, kept, N1, pruned, Mp, invn, ntm, ntn,
-                           best_val, best_slot, assign);
+                           best, assign);
     });
     return hipGetLastError();
 }
@@ -1439,46 +1444,41 @@ hipError_t launch_gram_reduce(const float *part, int B, int Mp, int N1, int Nv, 
 // loads (six stages in place of three changed nothing).  8 chunks (256
 // elements) are added up on their own.
 static void gram_f32_go(const void *vis, int Nv, int d_bytes, const int32_t *kept, int N1,
-                        const int32_t *pruned, int Mp, const float *invn, int B, float *best_val,
-                        int32_t *best_slot, int32_t *assign, hipStream_t st) {
+                        const int32_t *pruned, int Mp, const float *invn, int B,
+                        unsigned long long *best, int32_t *assign, hipStream_t st) {
     constexpr int T = kGramF32Tile, NP = 2;
     const int ntn = (N1 + T - 1) / T, ntm = (Mp + T - 1) / T;
     with_tail(d_bytes, [&](auto tail) {
         hipLaunchKernelGGL((gram_tile_kernel<kF32, T, T, 2, 2, 3, NP, decltype(tail)::value, 8>),
                            dim3(B * ntm * ntn), dim3(64 * (4 + NP)), 0, st, (const char *)vis, Nv,
-                           d_bytes, kept, N1, pruned, Mp, invn, ntm, ntn, best_val, best_slot, assign);
+                           d_bytes, kept, N1, pruned, Mp, invn, ntm, ntn, best, assign);
     });
 }
 
 hipError_t launch_gram_tile(int dt, const void *vis, int B, int Nv, int d, const int32_t *kept,
                             int N1, const int32_t *pruned, int Mp, const float *invn,
-                            float *best_val, int32_t *best_slot, int32_t *assign, int tile_n,
-                            hipStream_t st) {
+                            unsigned long long *best, int32_t *assign, int tile_n, hipStream_t st) {
     if (tile_n == kGramF32Tile) {
         if (dt != kF32) return hipErrorInvalidValue;
-        gram_f32_go(vis, Nv, d * 4, kept, N1, pruned, Mp, invn, B, best_val, best_slot, assign, st);
+        gram_f32_go(vis, Nv, d * 4, kept, N1, pruned, Mp, invn, B, best, assign, st);
         return hipGetLastError();
     }
-    if (dt == kBF16)
-        return gram_tile_go<kBF16>(vis, B, Nv, d, kept, N1, pruned, Mp, invn, best_val, best_slot,
-                                   assign, st);
-    return gram_tile_go<kF32>(vis, B, Nv, d, kept, N1, pruned, Mp, invn, best_val, best_slot,
-                              assign, st);
+    if (dt == kBF16) return gram_tile_go<kBF16>(vis, B, Nv, d, kept, N1, pruned, Mp, invn, best, assign, st);
+    return gram_tile_go<kF32>(vis, B, Nv, d, kept, N1, pruned, Mp, invn, best, assign, st);
 }
 
-hipError_t launch_gram_finish(const float *best_val, const int32_t *best_slot, int B, int ntn,
-                              int Mp, int Nv, const int32_t *pruned, int32_t *assign,
+hipError_t launch_gram_finish(const unsigned long long *best, int B, int Nv, int32_t *assign,
                               hipStream_t st) {
-    dim3 grid((Mp + kFinNT - 1) / kFinNT, B);
-    const FinishJob j{best_val, best_slot, ntn, Mp, Nv, pruned, assign, 0};
-    hipLaunchKernelGGL(gram_finish_kernel, grid, dim3(kFinNT), 0, st, j);
+    const long long n = (long long)B * Nv;
+    hipLaunchKernelGGL(gram_finish_kernel, dim3((unsigned)((n + kFinNT - 1) / kFinNT)), dim3(kFinNT), 0,
+                       st, best, n, assign);
     return hipGetLastError();
 }
 
-hipError_t launch_bucket(const int32_t *assign, int B, int Nv, int N1, int32_t *mcount,
+hipError_t launch_bucket(int32_t *assign, const unsigned long long *best, int B, int Nv, int N1, int32_t *mcount,
                          int32_t *mstart, int32_t *mlist, hipStream_t st) {
     const dim3 grid((N1 + kBucketSlots - 1) / kBucketSlots, B);
-    const BucketJob bj{assign, Nv, N1, mcount, mstart, mlist, (int)grid.x, (int)grid.x * B};
+    const BucketJob bj{assign, Nv, N1, best, mcount, mstart, mlist, (int)grid.x, (int)grid.x * B};
     const size_t lds = (size_t)Nv * sizeof(int32_t);
     if (Nv >= kBucketWideNv) hipLaunchKernelGGL(bucket_kernel<1024>, grid, dim3(1024), lds, st, bj);
     else hipLaunchKernelGGL(bucket_kernel<512>, grid, dim3(512), lds, st, bj);

@@ -1582,7 +1582,7 @@ static HeadArgs shared_heads(const ScoreChain &c) {
 hipError_t launch_assign_score(const ScoreChain &c, const AssignJob &aj, hipStream_t st) {
     const ScoreLaunch a = shared_score(c);
     const HeadArgs ha = shared_heads(c);
-    const int n_assign = aj.r.nblocks + aj.f.nblocks;
+    const int n_assign = aj.r.nblocks;
     if (c.form == kSharedSplit) {
         const SplitScore s = split_score(a, (float2 *)c.stats, 0, c.B);
         const int nks = head_windows(c.dt, c.hd);
@@ -1766,7 +1766,7 @@ __global__ __launch_bounds__(256) void assign_conf_kernel(const float *__restric
 hipError_t launch_assign_conf(const AssignJob &aj, const float *partial, int B, int H, int Nt,
                               float *conf, int n_vis, int32_t *heads, hipStream_t st) {
     if (H > 512) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(assign_conf_kernel, dim3(B + aj.r.nblocks + aj.f.nblocks), dim3(256), 0, st,
+    hipLaunchKernelGGL(assign_conf_kernel, dim3(B + aj.r.nblocks), dim3(256), 0, st,
                        partial, H, (Nt + 15) / 16, conf, n_vis, heads, B, aj);
     return hipGetLastError();
 }

@@ -178,51 +178,18 @@ __device__ __forceinline__ void gram_reduce_row(const ReduceJob &j, int m, int b
 // Rows of gram_reduce_row per carried workgroup (one per wave of 256).
 constexpr int kReduceRowsPerBlock = 4;
 
-// Best column tile of every pruned row of the full-k Gram, combined in tile
-// order with the total order above.
-struct FinishJob {
-    const float *best_val;     // [B][ntn][Mp]
-    const int32_t *best_slot;  // [B][ntn][Mp]
-    int ntn, Mp, Nv;
-    const int32_t *pruned;     // [B][Mp]
-    int32_t *assign;           // [B][Nv]
-    int nblocks;               // workgroups of kFinNT rows carried by another launch; 0: none
-};
-constexpr int kFinNT = 256;
-constexpr int kFinU = 16;
-
-// One thread, pruned row m of sample b.  The candidates of kFinU tiles are
-// loaded at once (a loop that compares each one as it arrives waits for every
-// load in turn); past the last tile the last one repeats, which cannot change
-// a maximum under a total order.
-__device__ __forceinline__ void gram_finish_row(const FinishJob &j, int m, int b) {
-    if (m >= j.Mp) return;
-    const int tok = j.pruned[(size_t)b * j.Mp + m];
-    float bv = -INFINITY;
-    int bs = 0x7FFFFFFF;
-    for (int t0 = 0; t0 < j.ntn; t0 += kFinU) {
-        float v[kFinU];
-        int s[kFinU];
-#pragma unroll
-        for (int u = 0; u < kFinU; ++u) {
-            const size_t at = ((size_t)b * j.ntn + min(t0 + u, j.ntn - 1)) * j.Mp + m;
-            v[u] = j.best_val[at];
-            s[u] = j.best_slot[at];
-        }
-#pragma unroll
-        for (int u = 0; u < kFinU; ++u)
-            if (better(v[u], s[u], bv, bs)) {
-                bv = v[u];
-                bs = s[u];
-            }
-    }
-    j.assign[(size_t)b * j.Nv + tok] = bs;
+// The full-k Gram's column tiles meet in one 64-bit integer maximum per pruned
+// token (device atomics in any order give the same bits): the image of the
+// cosine that orders as it does, then the slot complemented, so that a higher
+// cosine wins and then a lower slot.  Every candidate is above 0, the start.
+__device__ __forceinline__ unsigned long long best_pack(float v, int s) {
+    return ((unsigned long long)order_key(v) << 32) | (uint32_t)~s;
 }
+__device__ __forceinline__ int best_slot_of(unsigned long long best) { return (int)~(uint32_t)best; }
 
-// The Gram's argmax carried by another launch: one of the two forms, or none.
+// The split-k Gram's argmax carried by another launch (nblocks 0: none).
 struct AssignJob {
     ReduceJob r;
-    FinishJob f;
 };
 
 // Workgroup blk (of 256 threads) of the carried argmax; the slices loaded per
@@ -236,12 +203,6 @@ __device__ __forceinline__ void assign_block(const AssignJob &aj, int blk) {
         if (aj.r.KS <= 2) gram_reduce_row<2>(aj.r, m, b, lane);
         else if (aj.r.KS <= 4) gram_reduce_row<4>(aj.r, m, b, lane);
         else gram_reduce_row<8>(aj.r, m, b, lane);
-        return;
-    }
-    blk -= aj.r.nblocks;
-    if (blk < aj.f.nblocks) {
-        const int per = (aj.f.Mp + kFinNT - 1) / kFinNT;
-        gram_finish_row(aj.f, (blk % per) * kFinNT + (int)threadIdx.x, blk / per);
     }
 }
 
@@ -367,8 +328,12 @@ __device__ __forceinline__ unsigned long long same_slot_lanes(int v, unsigned lo
 }
 
 struct BucketJob {
-    const int32_t *assign;  // [B][Nv]
+    int32_t *assign;        // [B][Nv]
     int Nv, N1;
+    // [B][Nv], or NULL: the slot of a token whose assign is -1 is in here
+    // (best_pack); the sample's first workgroup then completes the assignment.
+    // Another one may find either value, which mean the same.
+    const unsigned long long *best;
     int32_t *mcount, *mstart, *mlist;
     int ngroups;            // groups of kBucketSlots slots
     int nblocks;            // workgroups (ngroups * B)
@@ -384,7 +349,8 @@ __device__ __forceinline__ void bucket_block(const BucketJob &bj, int g, int b, 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int s0 = g * kBucketSlots;
-    const int32_t *as = bj.assign + (size_t)b * Nv;
+    int32_t *as = bj.assign + (size_t)b * Nv;
+    const unsigned long long *bt = bj.best ? bj.best + (size_t)b * Nv : nullptr;
     int32_t *lst = bj.mlist + ((size_t)b * ngroups + g) * Nv;
     const unsigned long long lt = (1ull << lane) - 1ull;
 
@@ -394,6 +360,18 @@ __device__ __forceinline__ void bucket_block(const BucketJob &bj, int g, int b, 
         int v[8];
 #pragma unroll
         for (int u = 0; u < 8; ++u) v[u] = as[min(j0 + u * kBucketNT + tid, Nv - 1)];
+        if (bt) {
+            unsigned long long w[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) w[u] = bt[min(j0 + u * kBucketNT + tid, Nv - 1)];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) {
+                const int jt = j0 + u * kBucketNT + tid;
+                if (v[u] >= 0) continue;
+                v[u] = best_slot_of(w[u]);
+                if (g == 0 && jt < Nv) as[jt] = v[u];
+            }
+        }
 #pragma unroll
         for (int u = 0; u < 8; ++u)
             if (j0 + u * kBucketNT + tid < Nv) sa[j0 + u * kBucketNT + tid] = v[u];

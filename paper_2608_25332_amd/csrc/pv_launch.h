@@ -86,8 +86,9 @@ hipError_t launch_cos_reduce(const float *part, const float *ssv, const float *s
 // sample whose mask has no row set uses every row.
 hipError_t launch_center(const float *M, const float *rowsum, const int32_t *row_mask, int njt,
                          int B, int Nt, int Nv, float *p, hipStream_t st);
+// zero: [B][Nv], cleared on the way (may be NULL).
 hipError_t launch_select(const float *p, int B, int Nv, int budget, int32_t *kept, int32_t *pruned,
-                         int32_t *slot_of, hipStream_t st);
+                         int32_t *slot_of, unsigned long long *zero, hipStream_t st);
 // The split-k Gram's partial dot products part[KS][B][Mp][N1], on kSplitTile
 // square tiles (three workgroups per CU) or, with `wide`, on kGramWideM x
 // kGramWideN tiles (two per CU, each row loaded once for more outputs).
@@ -122,13 +123,11 @@ inline bool gram_f32_full(int B, int Mp, int N1, int nch, int ks_split) {
 }
 hipError_t launch_gram_tile(int dt, const void *vis, int B, int Nv, int d, const int32_t *kept,
                             int N1, const int32_t *pruned, int Mp, const float *invn,
-                            float *best_val, int32_t *best_slot, int32_t *assign, int tile_n,
-                            hipStream_t st);
-hipError_t launch_gram_finish(const float *best_val, const int32_t *best_slot, int B, int ntn,
-                              int Mp, int Nv, const int32_t *pruned, int32_t *assign,
+                            unsigned long long *best, int32_t *assign, int tile_n, hipStream_t st);
+hipError_t launch_gram_finish(const unsigned long long *best, int B, int Nv, int32_t *assign,
                               hipStream_t st);
 constexpr int kBucketSlotsPerGroup = 256;  // slots whose member lists one workgroup builds
-hipError_t launch_bucket(const int32_t *assign, int B, int Nv, int N1, int32_t *mcount,
+hipError_t launch_bucket(int32_t *assign, const unsigned long long *best, int B, int Nv, int N1, int32_t *mcount,
                          int32_t *mstart, int32_t *mlist, hipStream_t st);
 hipError_t launch_merge_csr(int dt, const void *vis, int B, int Nv, int d, int N1,
                             const int32_t *mcount, const int32_t *mstart, const int32_t *mlist,
