@@ -78,8 +78,9 @@ __device__ __forceinline__ const char *row_piece(const char *base, int row, int 
 
 // The same with FULL: the row is whole (row_bytes == RB), nothing to compare or
 // select.  (The comparison cost the whole-head form 1.1 us of 32 at 64 x 32
-// heads x 192 keys of 128.  A uniform branch around its loads costs nothing;
-// in the split form's short kernels the longer code cost 2 us of 11.)
+// heads x 192 keys of 128 and the 16-row blocks up to 5% on long fp32 rows.  A
+// uniform branch around the loads costs nothing there; in the split form's
+// short kernels the longer code cost 2 us of 11.)
 template <bool FULL, int RB>
 __device__ __forceinline__ const char *row_at(const char *base, int row, int row_bytes, int byte) {
     return FULL ? base + (size_t)row * RB + byte : row_piece(base, row, row_bytes, byte);
@@ -144,12 +145,17 @@ __device__ __forceinline__ void score_partial_block(
     }
     auto issue = [&](int ch) {
         char *dst = ring + (ch % NS) * S::STAGE + wave * S::IPW * 1024;
+        auto loads = [&](auto full) {
 #pragma unroll
-        for (int t = 0; t < S::IPW; ++t) {
-            const int key = min(ch * kScoreCK + srow[t], N - 1);  // past the end: last key
-            const int row = IDX ? krow[key] : key;
-            lds_dma16(row_piece(kb, row, row_bytes, sbyte[t]), dst + t * 1024);
-        }
+            for (int t = 0; t < S::IPW; ++t) {
+                const int key = min(ch * kScoreCK + srow[t], N - 1);  // past the end: last key
+                const int row = IDX ? krow[key] : key;
+                lds_dma16(row_at<decltype(full)::value, S::RB>(kb, row, row_bytes, sbyte[t]),
+                          dst + t * 1024);
+            }
+        };
+        if (row_bytes == S::RB) loads(std::true_type{});
+        else loads(std::false_type{});
     };
     // Every global load of the kernel is a direct-to-LDS load, and those
     // retire in the order they were issued, so a partial wait on the load
@@ -488,12 +494,17 @@ __global__ __launch_bounds__(64 * RW * KW) void head_conf_kernel(
     }
     auto issue = [&](int ch) {
         char *dst = ring + (ch % S::NS) * S::STAGE + wave * S::IPW * 1024;
+        auto loads = [&](auto full) {
 #pragma unroll
-        for (int t = 0; t < S::IPW; ++t) {
-            int row = min(ch * kScoreCK + srow[t], N - 1);
-            if constexpr (IDX) row = lds_read4_now(krow + row);
-            lds_dma16(row_piece(kb, row, row_bytes, sbyte[t]), dst + t * 1024);
-        }
+            for (int t = 0; t < S::IPW; ++t) {
+                int row = min(ch * kScoreCK + srow[t], N - 1);
+                if constexpr (IDX) row = lds_read4_now(krow + row);
+                lds_dma16(row_at<decltype(full)::value, S::RB>(kb, row, row_bytes, sbyte[t]),
+                          dst + t * 1024);
+            }
+        };
+        if (row_bytes == S::RB) loads(std::true_type{});
+        else loads(std::false_type{});
     };
     const bool loads = wave < 4;
     for (int p = wave; loads && p < NKS * RW; p += 4) {  // the query rows, 1 KiB per load
